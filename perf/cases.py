@@ -113,7 +113,8 @@ def _stream():
     return _STREAM
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """Weights, prompts, block states and drafts of a case, from the seed alone."""
     cfg = model(case["model"])
     n, B, N, P, G = case["batch"], case["block"], case["draft"], case["prefix"], case["gen"]
     rng = random.Random(seed)
@@ -124,34 +125,40 @@ def prepare(case, seed):
     if cfg["dtype"] == "bf16":
         w["embed"] *= 100.0                       # 0.02 -> 2: the embedding stays visible behind every layer
         w["lm_head"] = torch.roll(w["embed"], -shift, 0) * 0.125
+    s = dict(cfg=cfg, w=w, prompts=[synth.gen_prompt(cfg, rng.randrange(1 << 30), P) for _ in range(n)])
+    # the block: a quarter decoded already, the rest masked; drafts in the order of the masked positions,
+    # `accept` of them what the model predicts
+    toks, masks, drafts = [], [], []
+    for i in range(n):
+        open_ = sorted(rng.sample(range(B), max(min(B, N + 1), B - B // 4)))
+        row = [rng.randrange(V - 1) for _ in range(B)]
+        for p in open_:
+            row[p] = mask
+        toks.append(row)
+        masks.append(sum(1 << p for p in open_))
+        drafts.append([(p, sure if j < case["accept"] else (sure + 1 + rng.randrange(V - 2)) % (V - 1))
+                       for j, p in enumerate(open_[:min(N, len(open_) - 1)])])
+    s.update(toks=toks, masks=masks, drafts=drafts)
+    if case["kind"] == "prefill":
+        s["toks"], s["masks"] = [[mask] * B], [(1 << B) - 1]
+    if case["kind"] == "refresh":
+        s["sequence"] = list(s["prompts"][0]) + toks[0] + [mask] * (G - B)
+    return s
+
+
+def prepare(case, seed):
+    n, B, N, P, G = case["batch"], case["block"], case["draft"], case["prefix"], case["gen"]
+    s = _inputs(case, seed)
     torch.cuda.synchronize()                      # the library reads the weights on the decoding stream
     total = P + max(G, B)
     rows = max(P, total if case["kind"] == "refresh" else 0, n * (N + 1) * B)
     with torch.cuda.stream(_stream()):
-        eng = binding.SSD(cfg, w, max_seqs=n, max_seq_len=total, block=B, max_draft=N, max_rows=rows)
+        eng = binding.SSD(s.pop("cfg"), s.pop("w"), max_seqs=n, max_seq_len=total, block=B, max_draft=N, max_rows=rows)
         out = eng.new_out(n)
-        prompts = [synth.gen_prompt(cfg, rng.randrange(1 << 30), P) for _ in range(n)]
-        s = dict(case=case, eng=eng, out=out, prompts=prompts, seqs=list(range(n)), pos0=[P] * n)
+        s.update(case=case, eng=eng, out=out, seqs=list(range(n)), pos0=[P] * n)
         if case["kind"] in ("draft", "verify"):
             for i in range(n):
-                eng.prefill_kv(i, prompts[i], 0)
-        # the block: a quarter decoded already, the rest masked; drafts in the order of the masked positions,
-        # `accept` of them what the model predicts
-        toks, masks, drafts = [], [], []
-        for i in range(n):
-            open_ = sorted(rng.sample(range(B), max(min(B, N + 1), B - B // 4)))
-            row = [rng.randrange(V - 1) for _ in range(B)]
-            for p in open_:
-                row[p] = mask
-            toks.append(row)
-            masks.append(sum(1 << p for p in open_))
-            drafts.append([(p, sure if j < case["accept"] else (sure + 1 + rng.randrange(V - 2)) % (V - 1))
-                           for j, p in enumerate(open_[:min(N, len(open_) - 1)])])
-        s.update(toks=toks, masks=masks, drafts=drafts)
-        if case["kind"] == "prefill":
-            s["toks"], s["masks"] = [[mask] * B], [(1 << B) - 1]
-        if case["kind"] == "refresh":
-            s["sequence"] = list(prompts[0]) + toks[0] + [mask] * (G - B)
+                eng.prefill_kv(i, s["prompts"][i], 0)
         _stream().synchronize()
     return s
 
@@ -220,3 +227,81 @@ def tolerance(case):
     if case["model"] == "tiny":
         return {"rel": 2e-5, "max": 2e-4}
     return {"rel": 0.008, "max": 0.05}      # four times what the plain kernels differ from the matrix-core ones by
+
+
+def _rows64(cfg, w, tokens, pos, kv, keep, heads=8):
+    """The layers in 64 bits for sets of rows: tokens / pos [sets, rows], kv: per layer the cached (keys, values)
+    [positions, heads, channels] the rows see besides their own set's.  Returns the hidden rows and, with keep,
+    every layer's keys and values of the one set."""
+    dh, Hq, Hkv, F = cfg["head_dim"], cfg["n_q_heads"], cfg["n_kv_heads"], cfg["d_ffn"]
+    n, B = tokens.shape
+    f64 = torch.float64
+    norm = lambda x, g: x / torch.sqrt((x * x).mean(-1, keepdim=True) + cfg["rms_eps"]) * g.to(f64)
+    ang = pos.to(f64)[..., None] * cfg["rope_theta"] ** (torch.arange(dh // 2, device=pos.device, dtype=f64) * (-2.0 / dh))
+    cos, sin = torch.cos(ang)[:, :, None], torch.sin(ang)[:, :, None]
+    turn = lambda x: torch.cat([x[..., :dh // 2] * cos - x[..., dh // 2:] * sin, x[..., dh // 2:] * cos + x[..., :dh // 2] * sin], -1)
+    h, kept = w["embed"][tokens].to(f64), []
+    for l, lw in enumerate(w["layers"]):
+        x = norm(h, lw["norm1"]) @ lw["wqkv"].to(f64).T
+        q, k, v = (t.reshape(n, B, -1, dh) for t in x.split([Hq * dh, Hkv * dh, Hkv * dh], -1))
+        q, k = turn(q), turn(k)
+        if keep:
+            kept.append((k[0], v[0]))
+        if kv is not None:
+            k = torch.cat([kv[l][0].expand(n, -1, -1, -1), k], 1)
+            v = torch.cat([kv[l][1].expand(n, -1, -1, -1), v], 1)
+        a = torch.empty_like(q)
+        for i in range(n):
+            for h0 in range(0, Hq, heads):
+                hs = torch.arange(h0, min(Hq, h0 + heads), device=pos.device)
+                kk, vv = (t[i].transpose(0, 1)[hs // (Hq // Hkv)].contiguous() for t in (k, v))
+                p = torch.softmax(q[i][:, hs].transpose(0, 1).contiguous() @ kk.transpose(1, 2).contiguous() / math.sqrt(dh), -1)
+                a[i][:, hs] = (p @ vv).transpose(0, 1)
+        h = h + a.reshape(n, B, Hq * dh) @ lw["wo"].to(f64).T
+        x = norm(h, lw["norm2"]) @ lw["wgu"].to(f64).T
+        h = h + (torch.nn.functional.silu(x[..., :F]) * x[..., F:]) @ lw["wdown"].to(f64).T
+    return norm(h, w["final_norm"]), kept
+
+
+def _head64(cfg, w, x):
+    """Largest logit of every row and its softmax probability, the mask token left out."""
+    top, total = torch.full(x.shape[:-1], -math.inf, device=x.device, dtype=x.dtype), torch.zeros(x.shape[:-1], device=x.device, dtype=x.dtype)
+    for v0 in range(0, cfg["vocab"], 16384):
+        lg = x @ w["lm_head"][v0:v0 + 16384].to(x.dtype).T
+        if v0 <= cfg["mask_id"] < v0 + 16384:
+            lg[..., cfg["mask_id"] - v0] = -math.inf
+        new = torch.maximum(top, lg.amax(-1))
+        total = total * torch.exp(top - new) + torch.exp(lg - new[..., None]).sum(-1)
+        top = new
+    return top, 1.0 / total
+
+
+def exact(case, seed):
+    """The maximum logits and confidences in 64 bits (whole numbers have no such value, nor have tokens)."""
+    if case["kind"] == "generate":
+        return None
+    s = _inputs(case, seed)
+    cfg, w = s["cfg"], s["w"]
+    n, B, N, P, G = case["batch"], case["block"], case["draft"], case["prefix"], case["gen"]
+    dev = w["embed"].device
+    top = torch.zeros(n, N + 1, B, device=dev, dtype=torch.float64)
+    conf = torch.zeros_like(top)
+    span = lambda a, b: torch.arange(a, b, device=dev)
+    for i in range(n):
+        if case["kind"] == "refresh":
+            t = torch.tensor([[int(v) for v in s["sequence"]]], device=dev)
+            x = _rows64(cfg, w, t, span(0, P + G)[None], None, False)[0][:, P:P + B]
+        else:
+            prompt = torch.tensor([[int(v) for v in s["prompts"][i]]], device=dev)
+            kv = _rows64(cfg, w, prompt, span(0, P)[None], None, True)[1]
+            nodes = []
+            for j in range((len(s["drafts"][i]) if case["kind"] == "verify" else 0) + 1):
+                row = list(s["toks"][i])
+                for p, tok in s["drafts"][i][:j]:
+                    row[p] = tok
+                nodes.append(row)
+            t = torch.tensor(nodes, device=dev)
+            x = _rows64(cfg, w, t, span(P, P + B).expand(len(nodes), B), kv, False)[0]
+        top[i, :x.shape[0]], conf[i, :x.shape[0]] = _head64(cfg, w, x)
+    return dict(n_accept=None, acc_pos=None, acc_tok=None, n_next=None, next_pos=None, next_tok=None,
+                row_maxlogit=top, row_argmax=None, row_conf=conf)
