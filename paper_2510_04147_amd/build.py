@@ -10,7 +10,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libssd_mi355x.so")
 MEASURE_LIB = os.path.join(HERE, "libssd_measure.so")      # measurement kernels only, not part of the product
 SOURCES = ["kernels_mfma.hip", "kernels_mfma_f32.hip", "gemm_f32_wn3.hip", "gemm_f32_wn2.hip", "gemm_f32_wn4.hip",
-           "gemm_swiglu_wn3.hip", "gemm_swiglu_wn4.hip", "gemm_lmhead_wn4.hip", "ssd_api.hip", "kernels_plain.hip"]
+           "gemm_swiglu_wn3.hip", "gemm_swiglu_wn4.hip", "gemm_lmhead_wn4.hip",
+           "gemm_rows_f32.hip", "gemm_rows_swiglu.hip", "gemm_rows_lmhead.hip", "ssd_api.hip", "kernels_plain.hip"]
 MEASURE_SOURCES = ["measure.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -36,6 +36,43 @@ __device__ __forceinline__ uint16_t f2bf_m(float f) {
     return (uint16_t)(x >> 16);
 }
 
+// silu(gate) * up, rounded to bf16
+__device__ __forceinline__ uint16_t swiglu_bf16(float g, float u) {
+    return f2bf_m(g * __builtin_amdgcn_rcpf(1.0f + fast_exp(-g)) * u);
+}
+
+// LM head: (max, arg-max as float bits, sum of exp) of one row over the 32 vocabulary rows of tile nt; lane (lm, lh)
+// holds n = 8*(i/4) + 4*lh + i%4 of row lm.  The mask token takes no part.
+__device__ __forceinline__ void lm_tile_partial(const floatx16& v, int nt, int lh, int mask_id, float* p) {
+    float bm = -INFINITY;
+    int bi = 0x7fffffff;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int n = nt * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
+        if (n != mask_id && v[i] > bm) { bm = v[i]; bi = n; }
+    }
+    {
+        const float om = __shfl_xor(bm, 32, 64);
+        const int oi = __shfl_xor(bi, 32, 64);
+        if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
+    }
+    float se = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int n = nt * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
+        if (n != mask_id) se += fast_exp(v[i] - bm);
+    }
+    p[0] = bm;
+    p[1] = __int_as_float(bi);
+    p[2] = se + __shfl_xor(se, 32, 64);
+}
+
+// First chunk of a work-group's K walk: the work-groups start at different chunks, which spreads the grid's weight
+// streams over the HBM channels.  One start per 768 weight rows (a multiple of every n-block width) and
+// k-slice, so that the kernels for few and for many rows sum in the same order.
+__device__ __forceinline__ int gemm_k_start(int row, int bz, int nchunks) {
+    return (int)(((unsigned)(row / 768) * 5u + (unsigned)bz * 3u) % (unsigned)nchunks);
+}
 
 // ------------------------------------------------------------------------
 // GEMM.  Work-group = WN x WK waves.  Wave (wn, wk) owns one n-tile of 32
@@ -121,7 +158,7 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[r][mt][i] = 0.f;
 
-    const int rot = (int)((bx * 5u + bz * 3u) % (unsigned)nchunks);
+    const int rot = gemm_k_start(bx * (WN * R * 32), bz, nchunks);
     auto chunk_at = [&](int c) {
         c = c < nchunks - 1 ? c : nchunks - 1;
         c += rot;
@@ -343,7 +380,7 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
                                          acc[0][mt][(w + 2) * 4 + 2] + ou.z, acc[0][mt][(w + 2) * 4 + 3] + ou.w};
                     uint16_t o[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) o[j] = f2bf_m(gv[j] * __builtin_amdgcn_rcpf(1.0f + fast_exp(-gv[j])) * uv[j]);   // result rounded to bf16
+                    for (int j = 0; j < 4; ++j) o[j] = swiglu_bf16(gv[j], uv[j]);
                     const int m = m0 + mt * 32 + lm;
                     const int f = nt[0] * 16 + w * 8 + lh * 4;
                     if (m < M)
@@ -410,32 +447,14 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
             const int tile_out = (bx * WN + wn) * R + r;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                float bm = -INFINITY;
-                int bi = 0x7fffffff;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int n = nt[r] * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
-                    const float v = acc[r][mt][i];
-                    if (n != mask_id && v > bm) { bm = v; bi = n; }
-                }
-                {
-                    const float om = __shfl_xor(bm, 32, 64);
-                    const int oi = __shfl_xor(bi, 32, 64);
-                    if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
-                }
-                float se = 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int n = nt[r] * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
-                    if (n != mask_id) se += fast_exp(acc[r][mt][i] - bm);
-                }
-                se += __shfl_xor(se, 32, 64);
+                float p[3];
+                lm_tile_partial(acc[r][mt], nt[r], lh, mask_id, p);
                 const int m = m0 + mt * 32 + lm;
                 if (lh == 0 && m < M && tile_out < n_tiles_out && nt_ok[r]) {
                     float* o = out + ((size_t)m * n_tiles_out + tile_out) * 3;
-                    o[0] = bm;
-                    o[1] = __int_as_float(bi);
-                    o[2] = se;
+                    o[0] = p[0];
+                    o[1] = p[1];
+                    o[2] = p[2];
                 }
             }
         }
@@ -446,7 +465,7 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
 // launcher
 // ------------------------------------------------------------------------
 
-template <int WN, int WK, int R, int MT, int EPI, int NCH, int POLICY = 0>
+template <int WN, int WK, int R, int MT, int EPI, int NCH>
 static bool launch_one(const bf16_t* X, const uint4* Wp, void* out, int M, int N, int K, int split, size_t split_stride,
                        int mask_id, int n_tiles_out, int m_chunks, hipStream_t st) {
     constexpr int KC = WK * 32, ROWS = MT * 32, LDW = KC + 8;
@@ -457,7 +476,7 @@ static bool launch_one(const bf16_t* X, const uint4* Wp, void* out, int M, int N
                                        : (size_t)(WN / 2 + 1) * MT * 16 * 64 * 4;
     constexpr size_t smem = xbytes > rbytes ? xbytes : rbytes;
     static_assert(smem <= 160 * 1024, "LDS budget");
-    auto kern = k_gemm_mfma<WN, WK, R, MT, EPI, NCH, POLICY>;
+    auto kern = k_gemm_mfma<WN, WK, R, MT, EPI, NCH>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
@@ -483,14 +502,6 @@ static bool launch_mt(int mt, const bf16_t* X, const uint4* Wp, void* out, int M
     case v:                                                                                                     \
         return launch_one<WN, WK, R, v, EPI, NCH>(X, Wp, out, M, N, K, split, split_stride, mask_id,  \
                                                n_tiles_out, m_chunks, st);
-    // more than one row chunk: every chunk re-reads the weights, so they are loaded with the default
-    // cache policy (kernel option bit 5) and the later chunks find them in L2 / the Infinity Cache
-    if (mt == 5 && m_chunks > 1)
-        return launch_one<WN, WK, R, 5, EPI, NCH, 32>(X, Wp, out, M, N, K, split, split_stride, mask_id, n_tiles_out,
-                                                      m_chunks, st);
-    if (mt == 6 && m_chunks > 1)
-        return launch_one<WN, WK, R, 6, EPI, NCH, 32>(X, Wp, out, M, N, K, split, split_stride, mask_id, n_tiles_out,
-                                                      m_chunks, st);
     switch (mt) {
         SSD_MT_CASE(1)
         SSD_MT_CASE(2)
@@ -530,6 +541,11 @@ bool gemm_f32_wn4(const GemmArgs& a);     // narrow outputs, long K (down) and e
 bool gemm_swiglu_wn3(const GemmArgs& a);
 bool gemm_swiglu_wn4(const GemmArgs& a);
 bool gemm_lmhead_wn4(const GemmArgs& a);
+// the kernel for many rows (gemm_rows.h): mt row tiles of 32 rows per work-group, as gemm_rows_tile() says
+int gemm_rows_tile(int M, int N, int split);
+bool gemm_rows_f32(const GemmArgs& a, int mt);
+bool gemm_rows_swiglu(const GemmArgs& a, int mt);
+bool gemm_rows_lmhead(const GemmArgs& a, int mt);
 
 // Split along K across work-groups: a function of the weight shape only.
 static int pick_split(int K, int kc, int want) {

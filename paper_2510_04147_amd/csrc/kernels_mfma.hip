@@ -1,6 +1,6 @@
 // Matrix-core (MFMA) kernels for bf16 models on gfx950.
 //
-// Skinny weight-streaming GEMM  out[M,N] = X[M,K] * W[N,K]^T  for M <= 160 rows
+// Skinny weight-streaming GEMM  out[M,N] = X[M,K] * W[N,K]^T  for M <= 192 rows
 // per pass (the (N+1)*B rows of one verification forward, Eq. 5).  The weights
 // are the HBM stream; the design is built around that:
 //   * weights are repacked once, at context creation, into MFMA fragment
@@ -24,6 +24,7 @@
 //     consumer).  Both splits depend on the weight shape only, never on M, and
 //     a row's arithmetic never involves another row: a row is bit-identical in
 //     a 1-node and an (N+1)-node forward.
+// Forwards with more rows take k_gemm_rows (gemm_rows.h), which computes the same sums in the same order.
 #include "gemm_mfma.h"
 
 // ------------------------------------------------------------------------
@@ -56,14 +57,33 @@ void launch_pack_weights(const void* src, void* dst, int N, int K, int gate_rows
 
 int lm_tiles_mfma(int V) { return V / 32; }
 
+// Row tiles (of 32 rows) per work-group of k_gemm_rows, or 0: the few-row kernel takes the call.
+// Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of them;
+// beyond that it re-streams them per pass (gate/up of the 8B shape, us, few-row against k_gemm_rows: 200 rows 83 / 60,
+// 576 rows 150 / 114, 1000 rows 283 / 178).  Fewer than 128 work-groups leave half of the chip idle: then the
+// few-row kernel's narrower n-blocks spread better.  Among the tiles the fewest rounds over the 256 CUs win, a
+// round of 96, 128 or 160 rows costing 0.78 : 1 : 1.3 (measured at 640 and 1000 rows: 47, 59 and 78 us a
+// round; the 160-row tile has registers for one weight chunk in flight only, the others for three).
+int gemm_rows_tile(int M, int N, int split) {
+    if (M <= 192) return 0;
+    const int n_blocks = (N / 32 + 7) / 8, cost[3] = {78, 100, 130};
+    int best = 0, best_cost = 0;
+    for (int mt = 3; mt <= 5; ++mt) {
+        const long long wgs = (long long)n_blocks * split * ((M + mt * 32 - 1) / (mt * 32));
+        const long long c = (wgs + 255) / 256 * cost[mt - 3];
+        if (wgs >= 128 && (best == 0 || c < best_cost)) { best = mt; best_cost = (int)c; }
+    }
+    return best;
+}
+
 bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, void* out, int M, int* n_split,
                       hipStream_t st) {
     if (!W.packed) return false;
     const int N = W.N, K = W.K;
     constexpr int WK = 2, KC = WK * 32;
     if (K % KC) return false;
-    // rows per pass: 32 ... 192 in steps of 32; forwards with more rows re-stream the weights once per pass,
-    // in passes of 160 or 192 rows, whichever needs fewer.  The rows of a pass share nothing but the weight
+    // rows per pass: 32 ... 192 in steps of 32; more rows (of matrices too small for k_gemm_rows) re-stream the
+    // weights once per pass, in passes of 160 or 192 rows, whichever needs fewer.  The rows of a pass share nothing but the weight
     // fragments, so a row's sums do not depend on the choice.
     int mt = (M + 31) / 32;
     if (mt > 6) mt = (M + 191) / 192 < (M + 159) / 160 ? 6 : 5;
@@ -76,12 +96,14 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
         // channels each, any number of them per work-group; 96-row n-blocks give the 8B shape
         // (768 tiles) exactly one work-group per CU
         *n_split = 1;
+        if (const int rt = gemm_rows_tile(M, N, 1)) return gemm_rows_swiglu(a, rt);
         return (N / 32) % 3 == 0 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);
     }
     if (epi == EPI_LMHEAD) {
         *n_split = lm_tiles_mfma(N);
         a.mask_id = c->dm.mask_id;
         a.n_tiles_out = N / 32;
+        if (const int rt = gemm_rows_tile(M, N, 1)) return gemm_rows_lmhead(a, rt);
         return gemm_lmhead_wn4(a);
     }
     return launch_gemm_mfma_f32(c, x, wp, out, M, N, K, mt, m_chunks, n_split, st);
