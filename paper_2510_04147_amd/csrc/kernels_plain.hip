@@ -343,6 +343,38 @@ __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__
 #define PBN 64
 #define PBK 16
 
+// Fused LM-head reduction over 16 adjacent lanes that hold NJ consecutive logits each, from vocabulary row n0 of this
+// lane on: max logit, its lowest index, sum of exp(logit - max).  The mask token takes no part.
+template <int NJ>
+__device__ __forceinline__ void lm_row_partial(const float (&v)[NJ], int n0, int N, int mask_id, bool store, float* o) {
+    float bm = -INFINITY;
+    int bi = 0x7fffffff;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int n = n0 + j;
+        if (n < N && n != mask_id && v[j] > bm) { bm = v[j]; bi = n; }
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+        const float om = __shfl_xor(bm, off, 64);
+        const int oi = __shfl_xor(bi, off, 64);
+        if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
+    }
+    float se = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int n = n0 + j;
+        if (n < N && n != mask_id) se += expf(v[j] - bm);
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) se += __shfl_xor(se, off, 64);
+    if (store) {
+        o[0] = bm;
+        o[1] = __int_as_float(bi);
+        o[2] = se;
+    }
+}
+
 template <typename T, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, const T* __restrict__ W,
                                                     void* __restrict__ outv, int M, int N, int K, int up_off,
@@ -408,40 +440,105 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, con
                 }
             }
     } else {
-        // fused LM-head reduction: per row, over this tile's 64 vocabulary
-        // columns: max logit, its lowest index, sum of exp(logit - max).  The
-        // mask token takes no part.  The 16 threads of a row are 16 adjacent lanes.
+        // per row, over this tile's 64 vocabulary columns; the 16 threads of a row are 16 adjacent lanes
         float* out = (float*)outv;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float bm = -INFINITY;
-            int bi = 0x7fffffff;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int n = n0 + tx * 4 + j;
-                if (n < N && n != mask_id && acc[i][j] > bm) { bm = acc[i][j]; bi = n; }
-            }
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) {
-                const float om = __shfl_xor(bm, off, 64);
-                const int oi = __shfl_xor(bi, off, 64);
-                if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
-            }
-            float se = 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int n = n0 + tx * 4 + j;
-                if (n < N && n != mask_id) se += expf(acc[i][j] - bm);
-            }
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) se += __shfl_xor(se, off, 64);
             const int m = m0 + ty * 4 + i;
-            if (tx == 0 && m < M) {
-                float* o = out + ((size_t)m * n_tiles + blockIdx.x) * 3;
-                o[0] = bm;
-                o[1] = __int_as_float(bi);
-                o[2] = se;
+            lm_row_partial<4>(acc[i], n0 + tx * 4, N, mask_id, tx == 0 && m < M, out + ((size_t)m * n_tiles + blockIdx.x) * 3);
+        }
+    }
+}
+
+// The same sums for launches whose 64x64 tiles would leave most of the chip idle (small models, few rows): 8 rows x
+// 16 NJ outputs per work-group of 128 threads, NJ outputs per thread.  An output is still one chain of FMAs in
+// ascending k, and an LM-head partial still covers 64 columns, four consecutive ones per thread: bit for bit the
+// results of k_gemm_plain, so a row does not depend on which of the two computes it.  Bound: the latency of
+// the K walk, so the K chunks are 64 wide, one barrier each, and a chunk's 16-byte loads are in flight while the one
+// before it is multiplied.  Operands must be 16-byte aligned (K is a multiple of 8).
+// Measured, fp32, 32 rows (K x N, us, k_gemm_plain / this): 256 x 768 27 / 5.4, 768 x 256 55 / 8.4, gate/up 256 x 768
+// 53 / 6.4, LM head 256 x 1024 29 / 8.9.
+#define SBM 8
+#define SBK 64
+__device__ __forceinline__ float4 ld4_f(const float* p) {
+    const float4 v = *(const float4*)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 ld4_f(const bf16_t* p) {
+    const uint2 v = *(const uint2*)p;
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
+
+template <typename T, int EPI, int NJ>
+__global__ __launch_bounds__(128) void k_gemm_plain_small(const T* __restrict__ X, const T* __restrict__ W,
+                                                          void* __restrict__ outv, int M, int N, int K, int up_off,
+                                                          int mask_id, int n_tiles) {
+    constexpr int TN = 16 * NJ, NL = TN / 8, NU = EPI == EPI_SWIGLU ? NL : 1;
+    __shared__ __attribute__((aligned(16))) float Xs[2][SBM][SBK + 4];
+    __shared__ __attribute__((aligned(16))) float Ws[2][TN][SBK + 4];      // column n of the tile in row (n % NJ) * 16 + n / NJ
+    __shared__ __attribute__((aligned(16))) float Us[EPI == EPI_SWIGLU ? 2 : 1][EPI == EPI_SWIGLU ? TN : 1][SBK + 4];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, lk = tx * 4;
+    const int m0 = blockIdx.y * SBM, n0 = blockIdx.x * TN;
+    float4 xv, wv[NL], uv[NU];
+    auto get = [&](const T* base, size_t off, bool ok) {
+        const float4 v = ld4_f(base + (ok ? off : 0));
+        return make_float4(ok ? v.x : 0.f, ok ? v.y : 0.f, ok ? v.z : 0.f, ok ? v.w : 0.f);
+    };
+    auto issue = [&](int k0) {                               // rows, columns and k past the end count as zeros
+        const int kk = k0 + lk;
+        const bool kin = kk < K;
+        xv = get(X, (size_t)(m0 + ty) * K + kk, kin && m0 + ty < M);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int n = n0 + ty + 8 * i;
+            wv[i] = get(W, (size_t)n * K + kk, kin && n < N);
+            if (EPI == EPI_SWIGLU) uv[i % NU] = get(W, (size_t)(up_off + n) * K + kk, kin && n < N);
+        }
+    };
+    auto stage = [&](int buf) {
+        *(float4*)&Xs[buf][ty][lk] = xv;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int n = ty + 8 * i, r = (n % NJ) * 16 + n / NJ;
+            *(float4*)&Ws[buf][r][lk] = wv[i];
+            if constexpr (EPI == EPI_SWIGLU) *(float4*)&Us[buf][r][lk] = uv[i % NU];
+        }
+    };
+    float acc[NJ] = {}, accu[NJ] = {};
+    issue(0);
+    stage(0);
+    if (SBK < K) issue(SBK);
+    __syncthreads();
+    for (int k0 = 0, buf = 0; k0 < K; k0 += SBK, buf ^= 1) {
+        // the other buffer was last read before the barrier that ended the previous chunk
+        if (k0 + SBK < K) stage(buf ^ 1);
+        if (k0 + 2 * SBK < K) issue(k0 + 2 * SBK);
+#pragma unroll
+        for (int k = 0; k < SBK; k += 4) {
+            const float4 a = *(const float4*)&Xs[buf][ty][k];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const float4 b = *(const float4*)&Ws[buf][j * 16 + tx][k];
+                acc[j] += a.x * b.x; acc[j] += a.y * b.y; acc[j] += a.z * b.z; acc[j] += a.w * b.w;
+                if constexpr (EPI == EPI_SWIGLU) {
+                    const float4 u = *(const float4*)&Us[buf][j * 16 + tx][k];
+                    accu[j] += a.x * u.x; accu[j] += a.y * u.y; accu[j] += a.z * u.z; accu[j] += a.w * u.w;
+                }
             }
+        }
+        __syncthreads();
+    }
+    const int m = m0 + ty;
+    if constexpr (EPI == EPI_LMHEAD) {
+        lm_row_partial<NJ>(acc, n0 + tx * NJ, N, mask_id, tx == 0 && m < M, (float*)outv + ((size_t)m * n_tiles + blockIdx.x) * 3);
+    } else {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int n = n0 + tx * NJ + j;
+            if (m >= M || n >= N) continue;
+            if constexpr (EPI == EPI_F32) ((float*)outv)[(size_t)m * N + n] = acc[j];
+            else st_f((T*)outv + (size_t)m * N + n, acc[j] / (1.0f + expf(-acc[j])) * accu[j]);
         }
     }
 }
@@ -804,6 +901,18 @@ template <typename T>
 static void gemm_plain_t(const ssd_ctx* c, int epi, const T* X, const T* W, void* out, int M, int N, int K,
                          hipStream_t st) {
     dim3 grid((N + PBN - 1) / PBN, (M + PBM - 1) / PBM);
+    // Small tiles while the 64x64 ones fill less than a quarter of the 256 CUs (see k_gemm_plain_small); unaligned
+    // operands (kernel-level entry points take any pointer) stay with the scalar loads.
+    if (grid.x * grid.y <= 64 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0) {
+        const unsigned gy = (M + SBM - 1) / SBM;
+        if (epi == EPI_F32)
+            k_gemm_plain_small<T, EPI_F32, 1><<<dim3((N + 15) / 16, gy), 128, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
+        else if (epi == EPI_SWIGLU)
+            k_gemm_plain_small<T, EPI_SWIGLU, 1><<<dim3((N + 15) / 16, gy), 128, 0, st>>>(X, W, out, M, N, K, N, -1, 0);
+        else
+            k_gemm_plain_small<T, EPI_LMHEAD, 4><<<dim3(grid.x, gy), 128, 0, st>>>(X, W, out, M, N, K, 0, c->dm.mask_id, (int)grid.x);
+        return;
+    }
     if (epi == EPI_F32)
         k_gemm_plain<T, EPI_F32><<<grid, 256, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
     else if (epi == EPI_SWIGLU)
