@@ -11,6 +11,15 @@ typedef uint16_t bf16_t;
 
 __device__ __forceinline__ float ld_f(const float* p) { return *p; }
 __device__ __forceinline__ float ld_f(const bf16_t* p) { return __uint_as_float(((uint32_t)*p) << 16); }
+__device__ __forceinline__ float4 ld4_f(const float* p) {
+    const float4 v = *(const float4*)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 ld4_f(const bf16_t* p) {
+    const uint2 v = *(const uint2*)p;
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
 __device__ __forceinline__ uint16_t f2bf(float f) {
     uint32_t x = __float_as_uint(f);
     if ((x & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((x >> 16) | 0x40);   // NaN stays NaN
@@ -275,7 +284,9 @@ __global__ __launch_bounds__(256) void k_rope(const FwdHeader* __restrict__ fw, 
 
 // a4 (plain): one wave per (row, query head).  Keys = the sequence's cached
 // prefix [0,S), its cached suffix behind the block if it has one, then the node's own rows; online softmax in fp32 over
-// key tiles of 64 in position order.
+// key tiles of 64 in position order.  Bound by latency: keys and values are read 16 bytes per lane (a row's chain of
+// FMAs stays in channel and key order) with a tile's loads in flight together.  64 cached keys and a block of 32, head
+// size 64, 4 heads: 26 -> 8.2 us.
 template <typename T>
 __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__ fw, const int* __restrict__ row_node,
                                                    const T* __restrict__ q, const T* __restrict__ kown,
@@ -287,7 +298,7 @@ __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__
     const NodeDesc nd = fw->nodes[row_node[row]];
     const int kvh = head / (Hq / Hkv);
     const int nq = Hq * dh;
-    __shared__ float qs[128];
+    __shared__ __attribute__((aligned(16))) float qs[128];
     for (int i = lane; i < dh; i += 64) qs[i] = ld_f(q + (size_t)row * nq + head * dh + i);
     __syncthreads();
     const size_t cbase = ((((size_t)layer * max_seqs + nd.seq) * Hkv) + kvh) * (size_t)seq_stride * dh;
@@ -309,7 +320,16 @@ __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__
             const T* kp = pre ? kc : ko;
             const int p = pre ? cache_pos(j) : nd.vrow0 + j - n_cache;
             float acc = 0.f;
-            for (int i = 0; i < dh; ++i) acc += qs[i] * ld_f(kp + kfrag_off(p, i, dh));
+            for (int i0 = 0; i0 < dh; i0 += 64) {            // eight consecutive channels lie together; all 64 in flight
+                float4 kv[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) kv[i] = ld4_f(kp + kfrag_off(p, i0 + i * 4, dh));
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float4 qv = *(const float4*)&qs[i0 + i * 4];
+                    acc += qv.x * kv[i].x; acc += qv.y * kv[i].y; acc += qv.z * kv[i].z; acc += qv.w * kv[i].w;
+                }
+            }
             s = acc * scale;
         }
         const float m_new = fmaxf(m, wave_max(s));
@@ -319,14 +339,47 @@ __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__
         o0 *= corr;
         o1 *= corr;
         const int cnt = min(64, n_keys - t0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pj = __shfl(p, jj, 64);
-            const int jk = t0 + jj;
+        auto weight = [&](int jj) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), jj)); };
+        int jj = 0;
+        while (jj < cnt) {
+            const int jk = t0 + jj;                          // uniform over the wave, like everything it decides
             const bool pre = jk < n_cache;
             const T* vp = pre ? vc : vo;
             const int pp = pre ? cache_pos(jk) : nd.vrow0 + jk - n_cache;
-            o0 += pj * ld_f(vp + vfrag_off(pp, lane, dh));
-            if (dh > 64) o1 += pj * ld_f(vp + vfrag_off(pp, lane + 64, dh));
+            // keys from here on that stay in this run of consecutive positions
+            const int run = min(cnt - jj, jk < nd.S ? nd.S - jk : pre ? n_cache - jk : n_keys - jk);
+            if (run >= 32 && (pp & 3) == 0) {                // four consecutive positions of a channel lie together
+                float4 a[8], b[8];
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    a[g] = ld4_f(vp + vfrag_off(pp + 4 * g, lane, dh));
+                    if (dh > 64) b[g] = ld4_f(vp + vfrag_off(pp + 4 * g, lane + 64, dh));
+                }
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    const float w0 = weight(jj + 4 * g), w1 = weight(jj + 4 * g + 1), w2 = weight(jj + 4 * g + 2), w3 = weight(jj + 4 * g + 3);
+                    o0 += w0 * a[g].x; o0 += w1 * a[g].y; o0 += w2 * a[g].z; o0 += w3 * a[g].w;
+                    if (dh > 64) { o1 += w0 * b[g].x; o1 += w1 * b[g].y; o1 += w2 * b[g].z; o1 += w3 * b[g].w; }
+                }
+                jj += 32;
+            } else if (run >= 8) {
+                float a[8], b[8];
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    a[g] = ld_f(vp + vfrag_off(pp + g, lane, dh));
+                    if (dh > 64) b[g] = ld_f(vp + vfrag_off(pp + g, lane + 64, dh));
+                }
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    o0 += weight(jj + g) * a[g];
+                    if (dh > 64) o1 += weight(jj + g) * b[g];
+                }
+                jj += 8;
+            } else {
+                o0 += weight(jj) * ld_f(vp + vfrag_off(pp, lane, dh));
+                if (dh > 64) o1 += weight(jj) * ld_f(vp + vfrag_off(pp, lane + 64, dh));
+                ++jj;
+            }
         }
         m = m_new;
     }
@@ -460,16 +513,6 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, con
 // 53 / 6.4, LM head 256 x 1024 29 / 8.9.
 #define SBM 8
 #define SBK 64
-__device__ __forceinline__ float4 ld4_f(const float* p) {
-    const float4 v = *(const float4*)p;
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ float4 ld4_f(const bf16_t* p) {
-    const uint2 v = *(const uint2*)p;
-    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
-                       __uint_as_float(v.y & 0xffff0000u));
-}
-
 template <typename T, int EPI, int NJ>
 __global__ __launch_bounds__(128) void k_gemm_plain_small(const T* __restrict__ X, const T* __restrict__ W,
                                                           void* __restrict__ outv, int M, int N, int K, int up_off,
@@ -901,9 +944,11 @@ template <typename T>
 static void gemm_plain_t(const ssd_ctx* c, int epi, const T* X, const T* W, void* out, int M, int N, int K,
                          hipStream_t st) {
     dim3 grid((N + PBN - 1) / PBN, (M + PBM - 1) / PBM);
-    // Small tiles while the 64x64 ones fill less than a quarter of the 256 CUs (see k_gemm_plain_small); unaligned
-    // operands (kernel-level entry points take any pointer) stay with the scalar loads.
-    if (grid.x * grid.y <= 64 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0) {
+    // Small tiles while the 64x64 ones give a CU at most one work-group (see k_gemm_plain_small; fp32, us, 64x64 tiles /
+    // small ones: 12 tiles 51 / 5, 60 tiles 57 / 16, 120 tiles 105 / 35, 165 tiles 68 / 44, 240 tiles 105 / 70; the
+    // small ones read LDS three times as much per FMA).  Unaligned operands (kernel-level entry points take any
+    // pointer) stay with the scalar loads.
+    if ((size_t)grid.x * grid.y <= 256 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0) {
         const unsigned gy = (M + SBM - 1) / SBM;
         if (epi == EPI_F32)
             k_gemm_plain_small<T, EPI_F32, 1><<<dim3((N + 15) / 16, gy), 128, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
