@@ -541,6 +541,7 @@ bool gemm_f32_wn4(const GemmArgs& a);     // narrow outputs, long K (down) and e
 bool gemm_swiglu_wn3(const GemmArgs& a);
 bool gemm_swiglu_wn4(const GemmArgs& a);
 bool gemm_lmhead_wn4(const GemmArgs& a);
+void gemm_set_pass(GemmArgs& a, int wn);  // row tiles per pass and passes of the shapes above
 // the kernel for many rows (gemm_rows.h): mt row tiles of 32 rows per work-group, as gemm_rows_tile() says
 int gemm_rows_tile(int M, int N, int split);
 bool gemm_rows_f32(const GemmArgs& a, int mt);

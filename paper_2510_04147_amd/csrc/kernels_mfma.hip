@@ -76,37 +76,50 @@ int gemm_rows_tile(int M, int N, int split) {
     return best;
 }
 
+// Row tiles per pass of the few-row kernel, and the passes: 32 ... 192 rows in steps of 32; more rows (of matrices
+// too small for k_gemm_rows) re-stream the weights once per pass, in passes of 160 or 192 rows, whichever needs fewer.
+// Small matrices, whose n-blocks leave more than half of the CUs idle, take shorter passes until 128 work-groups
+// run: their weights come from L2 after the first pass, and a work-group's time is its K walk times its row tiles
+// (192 rows, K = 512, us, one pass / short passes: gate/up of 1536 channels 17 / 7.3, LM head of 2080 tokens 14.7 / 9.4,
+// attention output 10 / 4.7).
+// The rows of a pass share nothing but the weight fragments, so a row's sums do not depend on the choice.
+void gemm_set_pass(GemmArgs& a, int wn) {
+    const int tiles = (a.M + 31) / 32, blocks = (a.N / 32 + wn - 1) / wn * a.split;
+    int mt = tiles;
+    if (mt > 6) mt = (a.M + 191) / 192 < (a.M + 159) / 160 ? 6 : 5;
+    while (mt > 1 && (long long)blocks * ((tiles + mt - 1) / mt) < 128) --mt;
+    a.mt = mt;
+    a.m_chunks = (tiles + mt - 1) / mt;
+}
+
 bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, void* out, int M, int* n_split,
                       hipStream_t st) {
     if (!W.packed) return false;
     const int N = W.N, K = W.K;
     constexpr int WK = 2, KC = WK * 32;
     if (K % KC) return false;
-    // rows per pass: 32 ... 192 in steps of 32; more rows (of matrices too small for k_gemm_rows) re-stream the
-    // weights once per pass, in passes of 160 or 192 rows, whichever needs fewer.  The rows of a pass share nothing but the weight
-    // fragments, so a row's sums do not depend on the choice.
-    int mt = (M + 31) / 32;
-    if (mt > 6) mt = (M + 191) / 192 < (M + 159) / 160 ? 6 : 5;
-    const int rows = mt * 32, m_chunks = (M + rows - 1) / rows;
     const bf16_t* x = (const bf16_t*)X;
     const uint4* wp = (const uint4*)W.packed;
-    GemmArgs a{K / KC, mt, x, wp, out, M, N, K, 1, 0, -1, 0, m_chunks, st};
+    GemmArgs a{K / KC, 0, x, wp, out, M, N, K, 1, 0, -1, 0, 0, st};
     if (epi == EPI_SWIGLU) {
         // W = [2F, d] packed with gate and up rows interleaved per 16 channels: N/32 tiles of 16
         // channels each, any number of them per work-group; 96-row n-blocks give the 8B shape
         // (768 tiles) exactly one work-group per CU
         *n_split = 1;
         if (const int rt = gemm_rows_tile(M, N, 1)) return gemm_rows_swiglu(a, rt);
-        return (N / 32) % 3 == 0 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);
+        const int wn = (N / 32) % 3 == 0 ? 3 : 4;
+        gemm_set_pass(a, wn);
+        return wn == 3 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);
     }
     if (epi == EPI_LMHEAD) {
         *n_split = lm_tiles_mfma(N);
         a.mask_id = c->dm.mask_id;
         a.n_tiles_out = N / 32;
         if (const int rt = gemm_rows_tile(M, N, 1)) return gemm_rows_lmhead(a, rt);
+        gemm_set_pass(a, 4);
         return gemm_lmhead_wn4(a);
     }
-    return launch_gemm_mfma_f32(c, x, wp, out, M, N, K, mt, m_chunks, n_split, st);
+    return launch_gemm_mfma_f32(c, x, wp, out, M, N, K, n_split, st);
 }
 
 // ------------------------------------------------------------------------

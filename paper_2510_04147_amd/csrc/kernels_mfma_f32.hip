@@ -2,8 +2,8 @@
 // a translation unit of their own so that they compile next to the other epilogues.
 #include "gemm_mfma.h"
 
-bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, void* out, int M, int N, int K, int mt,
-                          int m_chunks, int* n_split, hipStream_t st) {
+bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, void* out, int M, int N, int K,
+                          int* n_split, hipStream_t st) {
     constexpr int WK = 2, KC = WK * 32;
     const size_t stride = (size_t)c->dm.max_rows * (size_t)c->part_cols;
     // Work-group shape and split along K: functions of the weight shape alone, chosen so that the
@@ -26,7 +26,8 @@ bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, vo
     const int split = pick_split(K, KC, want);
     *n_split = split;
     const int nch = K / split / KC;
-    GemmArgs a{nch, mt, x, wp, out, M, N, K, split, stride, -1, 0, m_chunks, st};
+    GemmArgs a{nch, 0, x, wp, out, M, N, K, split, stride, -1, 0, 0, st};
     if (const int rt = gemm_rows_tile(M, N, split)) return gemm_rows_f32(a, rt);
+    gemm_set_pass(a, wn);
     return wn == 3 ? gemm_f32_wn3(a) : wn == 2 ? gemm_f32_wn2(a) : gemm_f32_wn4(a);
 }
