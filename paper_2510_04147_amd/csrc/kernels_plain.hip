@@ -122,13 +122,14 @@ template <typename T, int NP>
 __device__ __forceinline__ void norm_row(float* hr, const float* pr, size_t part_stride, const float* gain, T* xr,
                                          int d, float eps) {
     const int n4 = d >> 2;
-    float4 v[NORM_J];
+    float4 v[NORM_J], g[NORM_J];
     float ss = 0.f;
 #pragma unroll
     for (int j = 0; j < NORM_J; ++j) {
         const int i4 = threadIdx.x + j * NORM_T;
         if (i4 < n4) {
             v[j] = ((const float4*)hr)[i4];
+            g[j] = ((const float4*)gain)[i4];                // not behind the reduction's barrier (1000 rows 20.1 -> 19.2 us)
             float4 pv[NP > 0 ? NP : 1];
 #pragma unroll
             for (int s = 0; s < NP; ++s) pv[s] = ((const float4*)(pr + s * part_stride))[i4];
@@ -152,8 +153,7 @@ __device__ __forceinline__ void norm_row(float* hr, const float* pr, size_t part
     for (int j = 0; j < NORM_J; ++j) {
         const int i4 = threadIdx.x + j * NORM_T;
         if (i4 < n4) {
-            const float4 g = ((const float4*)gain)[i4];
-            st4(xr + 4 * i4, v[j].x * r * g.x, v[j].y * r * g.y, v[j].z * r * g.z, v[j].w * r * g.w);
+            st4(xr + 4 * i4, v[j].x * r * g[j].x, v[j].y * r * g[j].y, v[j].z * r * g[j].z, v[j].w * r * g[j].w);
         }
     }
 }
