@@ -5,8 +5,8 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "gemm_rules.h"
 #include "ssd_internal.h"
-
 
 typedef uint16_t bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -91,12 +91,12 @@ __device__ __forceinline__ int gemm_k_start(int row, int bz, int nchunks) {
 // Every work-group starts its K walk at a different chunk and wraps, which
 // spreads the grid's weight streams over the HBM channels; the order depends
 // on the n-tile only, so a row's summation order is the same in every forward.
+// CACHED: weight loads with the default cache policy (GemmPass).
 // DBG is for measurement builds only (bit 0: no MFMA, bit 1: no activation
 // loads, bit 2: no epilogue, bit 3: every chunk reads chunk 0's activations, bit 4: no weight
-// loads, bit 5: weight loads with the default cache policy); the library
-// instantiates DBG = 0.
+// loads); the library instantiates DBG = 0.
 // ------------------------------------------------------------------------
-template <int WN, int WK, int R, int MT, int EPI, int NCH, int DBG = 0, int DW = 4, int PX = 4, int KSTEPS = 2>
+template <int WN, int WK, int R, int MT, int EPI, int NCH, bool CACHED, int DBG = 0, int DW = 4, int PX = 4, int KSTEPS = 2>
 __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, const uint4* Wp, void* outv, int M, int N,
                                                            int K, int ldx, int k_len, size_t split_stride,
                                                            int mask_id, int n_tiles_out, int n_blocks, int n_split,
@@ -193,10 +193,10 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
             for (int ks = 0; ks < KSTEPS; ++ks) {
                 if (DBG & 16)
                     dst[r * KSTEPS + ks] = make_uint4((unsigned)off, (unsigned)ks, 0u, 0u);
-                else if (DBG & 32)
+                else if (CACHED)
                     dst[r * KSTEPS + ks] = wbase[r][off + ks * 64];
                 else {
-                    // weights are read once per launch: a non-temporal load keeps them from evicting the
+                    // weights that are read once per launch: a non-temporal load keeps them from evicting the
                     // activations, which every work-group of the XCD re-reads, from L2
                     const u32x4 v = __builtin_nontemporal_load((const u32x4*)&wbase[r][off + ks * 64]);
                     dst[r * KSTEPS + ks] = make_uint4(v.x, v.y, v.z, v.w);
@@ -476,9 +476,21 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
 // launcher
 // ------------------------------------------------------------------------
 
-template <int WN, int WK, int R, int MT, int EPI, int NCH>
-static bool launch_one(const bf16_t* X, const uint4* Wp, void* out, int M, int N, int K, int split, size_t split_stride,
-                       int mask_id, int n_tiles_out, int m_chunks, hipStream_t st) {
+// the launchers of the work-group shapes, one translation unit each (they compile in parallel)
+struct GemmArgs {
+    int nch;
+    const bf16_t* X;
+    const uint4* Wp;
+    void* out;
+    int M, N, K, split;
+    size_t split_stride;
+    int mask_id, n_tiles_out;
+    GemmPass pass;                        // the few-row kernel's
+    hipStream_t st;
+};
+
+template <int WN, int WK, int R, int MT, int EPI, int NCH, bool CACHED>
+static bool launch_one(const GemmArgs& a) {
     constexpr int KC = WK * 32, ROWS = MT * 32, LDW = KC + 8;
     constexpr size_t xbytes = (size_t)3 * ROWS * LDW * 2 + (size_t)WN * WK * 64 * 16;   // three stages + spare slots
     // epilogue exchange areas: see the kernel's epilogues
@@ -487,74 +499,53 @@ static bool launch_one(const bf16_t* X, const uint4* Wp, void* out, int M, int N
                                        : (size_t)(WN / 2 + 1) * MT * 16 * 64 * 4;
     constexpr size_t smem = xbytes > rbytes ? xbytes : rbytes;
     static_assert(smem <= 160 * 1024, "LDS budget");
-    auto kern = k_gemm_mfma<WN, WK, R, MT, EPI, NCH>;
+    auto kern = k_gemm_mfma<WN, WK, R, MT, EPI, NCH, CACHED>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
             return false;
         attr_done = true;
     }
-    const int tiles = N / 32, per_wg = WN * R;
+    const int tiles = a.N / 32, per_wg = WN * R;
     const int n_blocks = (tiles + per_wg - 1) / per_wg;
-    dim3 grid(n_blocks * m_chunks * split);
-    hipLaunchKernelGGL(kern, grid, dim3(WN * WK * 64), smem, st, X, Wp, out, M, N, K, K, K / split, split_stride,
-                       mask_id, n_tiles_out, n_blocks, split, m_chunks);
+    dim3 grid(n_blocks * a.pass.passes * a.split);
+    hipLaunchKernelGGL(kern, grid, dim3(WN * WK * 64), smem, a.st, a.X, a.Wp, a.out, a.M, a.N, a.K, a.K, a.K / a.split,
+                       a.split_stride, a.mask_id, a.n_tiles_out, n_blocks, a.split, a.pass.passes);
     return true;
 }
 
 // Row tiles of 32 rows per pass: 1 (a stepwise forward of one block) to 6; other row counts round up
 // (padding rows are zero and never stored).  The rows of a pass share nothing but the weight fragments,
 // so a row's sums do not depend on the tile it is computed in.
-template <int WN, int WK, int R, int EPI, int NCH>
-static bool launch_mt(int mt, const bf16_t* X, const uint4* Wp, void* out, int M, int N, int K, int split,
-                      size_t split_stride, int mask_id, int n_tiles_out, int m_chunks,
-                      hipStream_t st) {
-#define SSD_MT_CASE(v)                                                                                          \
-    case v:                                                                                                     \
-        return launch_one<WN, WK, R, v, EPI, NCH>(X, Wp, out, M, N, K, split, split_stride, mask_id,  \
-                                               n_tiles_out, m_chunks, st);
-    switch (mt) {
-        SSD_MT_CASE(1)
-        SSD_MT_CASE(2)
-        SSD_MT_CASE(3)
-        SSD_MT_CASE(4)
-        SSD_MT_CASE(5)
-        SSD_MT_CASE(6)
+template <int WN, int WK, int R, int EPI, int NCH, bool CACHED>
+static bool launch_mt(const GemmArgs& a) {
+    switch (a.pass.mt) {
+        case 1: return launch_one<WN, WK, R, 1, EPI, NCH, CACHED>(a);
+        case 2: return launch_one<WN, WK, R, 2, EPI, NCH, CACHED>(a);
+        case 3: return launch_one<WN, WK, R, 3, EPI, NCH, CACHED>(a);
+        case 4: return launch_one<WN, WK, R, 4, EPI, NCH, CACHED>(a);
+        case 5: return launch_one<WN, WK, R, 5, EPI, NCH, CACHED>(a);
+        case 6: return launch_one<WN, WK, R, 6, EPI, NCH, CACHED>(a);
     }
-#undef SSD_MT_CASE
     return false;
 }
 
 // One chunk count per work-group shape runs as straight-line code (NCH = the 8B-class shape's chunk
 // count for that projection); every other chunk count takes the looped kernel (NCH = 0).
 template <int WN, int WK, int EPI, int NCH>
-static bool launch_shape(int nch, int mt, const bf16_t* X, const uint4* Wp, void* out, int M, int N, int K, int split,
-                         size_t split_stride, int mask_id, int n_tiles_out, int m_chunks, hipStream_t st) {
-    if (NCH > 0 && nch == NCH)
-        return launch_mt<WN, WK, 1, EPI, NCH>(mt, X, Wp, out, M, N, K, split, split_stride, mask_id, n_tiles_out, m_chunks, st);
-    return launch_mt<WN, WK, 1, EPI, 0>(mt, X, Wp, out, M, N, K, split, split_stride, mask_id, n_tiles_out, m_chunks, st);
+static bool launch_shape(const GemmArgs& a) {
+    if (NCH > 0 && a.nch == NCH)
+        return a.pass.cached ? launch_mt<WN, WK, 1, EPI, NCH, true>(a) : launch_mt<WN, WK, 1, EPI, NCH, false>(a);
+    return a.pass.cached ? launch_mt<WN, WK, 1, EPI, 0, true>(a) : launch_mt<WN, WK, 1, EPI, 0, false>(a);
 }
 
-// the launchers of the work-group shapes, one translation unit each (they compile in parallel)
-struct GemmArgs {
-    int nch, mt;
-    const bf16_t* X;
-    const uint4* Wp;
-    void* out;
-    int M, N, K, split;
-    size_t split_stride;
-    int mask_id, n_tiles_out, m_chunks;
-    hipStream_t st;
-};
 bool gemm_f32_wn3(const GemmArgs& a);     // wide outputs (QKV): 96-row n-blocks
 bool gemm_f32_wn2(const GemmArgs& a);     // narrow outputs, short K (attention output): 64-row n-blocks
 bool gemm_f32_wn4(const GemmArgs& a);     // narrow outputs, long K (down) and everything else: 128-row n-blocks
 bool gemm_swiglu_wn3(const GemmArgs& a);
 bool gemm_swiglu_wn4(const GemmArgs& a);
 bool gemm_lmhead_wn4(const GemmArgs& a);
-void gemm_set_pass(GemmArgs& a, int wn);  // row tiles per pass and passes of the shapes above
 // the kernel for many rows (gemm_rows.h): mt row tiles of 32 rows per work-group, as gemm_rows_tile() says
-int gemm_rows_tile(int M, int N, int split);
 bool gemm_rows_f32(const GemmArgs& a, int mt);
 bool gemm_rows_swiglu(const GemmArgs& a, int mt);
 bool gemm_rows_lmhead(const GemmArgs& a, int mt);

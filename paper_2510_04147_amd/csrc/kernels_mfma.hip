@@ -8,9 +8,9 @@
 //     is one contiguous 1 KiB block laid out lane by lane, so a wave's load
 //     instruction reads 1 KiB of consecutive bytes and a wave streams a
 //     contiguous region straight into registers (no LDS round trip), with
-//     non-temporal loads, so that the stream does not evict the activations
-//     from L2; the gate/up matrix interleaves gate and up rows per 16 channels,
-//     which makes SwiGLU lane-local;
+//     non-temporal loads where one pass takes all rows, so that the stream does
+//     not evict the activations from L2; the gate/up matrix interleaves gate and
+//     up rows per 16 channels, which makes SwiGLU lane-local;
 //   * the weight fragment is the A operand of v_mfma_f32_32x32x16_bf16, the
 //     activations are the B operand, so each lane ends up with 4 consecutive
 //     output columns of one row: vector stores, lane-local SwiGLU and LM-head
@@ -57,41 +57,6 @@ void launch_pack_weights(const void* src, void* dst, int N, int K, int gate_rows
 
 int lm_tiles_mfma(int V) { return V / 32; }
 
-// Row tiles (of 32 rows) per work-group of k_gemm_rows, or 0: the few-row kernel takes the call.
-// Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of them;
-// beyond that it re-streams them per pass (gate/up of the 8B shape, us, few-row against k_gemm_rows: 200 rows 83 / 60,
-// 576 rows 150 / 114, 1000 rows 283 / 178).  Fewer than 128 work-groups leave half of the chip idle: then the
-// few-row kernel's narrower n-blocks spread better.  Among the tiles the fewest rounds over the 256 CUs win, a
-// round of 96, 128 or 160 rows costing 0.78 : 1 : 1.3 (measured at 640 and 1000 rows: 47, 59 and 78 us a
-// round; the 160-row tile has registers for one weight chunk in flight only, the others for three).
-int gemm_rows_tile(int M, int N, int split) {
-    if (M <= 192) return 0;
-    const int n_blocks = (N / 32 + 7) / 8, cost[3] = {78, 100, 130};
-    int best = 0, best_cost = 0;
-    for (int mt = 3; mt <= 5; ++mt) {
-        const long long wgs = (long long)n_blocks * split * ((M + mt * 32 - 1) / (mt * 32));
-        const long long c = (wgs + 255) / 256 * cost[mt - 3];
-        if (wgs >= 128 && (best == 0 || c < best_cost)) { best = mt; best_cost = (int)c; }
-    }
-    return best;
-}
-
-// Row tiles per pass of the few-row kernel, and the passes: 32 ... 192 rows in steps of 32; more rows (of matrices
-// too small for k_gemm_rows) re-stream the weights once per pass, in passes of 160 or 192 rows, whichever needs fewer.
-// Small matrices, whose n-blocks leave more than half of the CUs idle, take shorter passes until 128 work-groups
-// run: their weights come from L2 after the first pass, and a work-group's time is its K walk times its row tiles
-// (192 rows, K = 512, us, one pass / short passes: gate/up of 1536 channels 17 / 7.3, LM head of 2080 tokens 14.7 / 9.4,
-// attention output 10 / 4.7).
-// The rows of a pass share nothing but the weight fragments, so a row's sums do not depend on the choice.
-void gemm_set_pass(GemmArgs& a, int wn) {
-    const int tiles = (a.M + 31) / 32, blocks = (a.N / 32 + wn - 1) / wn * a.split;
-    int mt = tiles;
-    if (mt > 6) mt = (a.M + 191) / 192 < (a.M + 159) / 160 ? 6 : 5;
-    while (mt > 1 && (long long)blocks * ((tiles + mt - 1) / mt) < 128) --mt;
-    a.mt = mt;
-    a.m_chunks = (tiles + mt - 1) / mt;
-}
-
 bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, void* out, int M, int* n_split,
                       hipStream_t st) {
     if (!W.packed) return false;
@@ -100,7 +65,7 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
     if (K % KC) return false;
     const bf16_t* x = (const bf16_t*)X;
     const uint4* wp = (const uint4*)W.packed;
-    GemmArgs a{K / KC, 0, x, wp, out, M, N, K, 1, 0, -1, 0, 0, st};
+    GemmArgs a{K / KC, x, wp, out, M, N, K, 1, 0, -1, 0, {}, st};
     if (epi == EPI_SWIGLU) {
         // W = [2F, d] packed with gate and up rows interleaved per 16 channels: N/32 tiles of 16
         // channels each, any number of them per work-group; 96-row n-blocks give the 8B shape
@@ -108,7 +73,7 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
         *n_split = 1;
         if (const int rt = gemm_rows_tile(M, N, 1)) return gemm_rows_swiglu(a, rt);
         const int wn = (N / 32) % 3 == 0 ? 3 : 4;
-        gemm_set_pass(a, wn);
+        a.pass = gemm_few_row_pass(M, N, 1, wn);
         return wn == 3 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);
     }
     if (epi == EPI_LMHEAD) {
@@ -116,7 +81,7 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
         a.mask_id = c->dm.mask_id;
         a.n_tiles_out = N / 32;
         if (const int rt = gemm_rows_tile(M, N, 1)) return gemm_rows_lmhead(a, rt);
-        gemm_set_pass(a, 4);
+        a.pass = gemm_few_row_pass(M, N, 1, 4);
         return gemm_lmhead_wn4(a);
     }
     return launch_gemm_mfma_f32(c, x, wp, out, M, N, K, n_split, st);

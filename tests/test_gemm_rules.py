@@ -1,0 +1,50 @@
+"""The rules that send a GEMM call to a kernel (csrc/gemm_rules.h), compiled with the host compiler."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2510_04147_amd", "csrc")
+PROGRAM = """
+#include <cstdio>
+#include "gemm_rules.h"
+int main() {
+    int M, N, K, split, wn;
+    while (std::scanf("%d %d %d %d %d", &M, &N, &K, &split, &wn) == 5) {
+        const GemmPass p = gemm_few_row_pass(M, N, split, wn);
+        std::printf("%d %d %d %d\\n", gemm_rows_tile(M, N, split), p.mt, p.passes, (int)p.cached);
+    }
+}
+"""
+# N, K, split, 32-row weight tiles per few-row work-group
+SHAPES = [(12288, 4096, 2, 3), (4096, 4096, 4, 2), (24576, 4096, 1, 3), (4096, 12288, 8, 4), (126464, 4096, 1, 4),
+          (4608, 3584, 4, 2), (37888, 3584, 1, 4), (3584, 18944, 8, 4), (768, 512, 4, 2), (512, 512, 4, 2), (3072, 512, 1, 3),
+          (512, 1536, 4, 2), (2080, 512, 1, 4), (4800, 1600, 1, 2), (1600, 1600, 1, 2), (12800, 1600, 1, 4),
+          (1600, 6400, 5, 4), (5632, 1024, 1, 4), (1024, 2816, 4, 2), (11264, 2048, 1, 4), (32, 64, 1, 2)]
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "rules.cpp"), "-o", str(d / "rules")], check=True)
+
+    def ask(calls):
+        text = "".join("%d %d %d %d %d\n" % c for c in calls)
+        out = subprocess.run([str(d / "rules")], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(int(v) for v in line.split()) for line in out.splitlines()]
+    return ask
+
+
+def test_passes_cover_the_rows(rules):
+    calls = [(M, *s) for s in SHAPES for M in (1, 31, 32, 33, 64, 65, 96, 97, 160, 161, 192, 193, 320, 321, 384, 385, 1000, 2304, 16384)]
+    for (M, N, K, split, wn), (rows_tile, mt, passes, cached) in zip(calls, rules(calls)):
+        assert rows_tile in (0, 3, 4, 5) and 1 <= mt <= 6, (M, N)
+        assert (passes - 1) * mt * 32 < M <= passes * mt * 32, (M, N, mt, passes)
+        assert rows_tile == 0 or (M > 192 and -(-N // 256) * split * -(-M // (32 * rows_tile)) >= 128), (M, N)
+
+
+def test_weights_that_several_passes_read_are_cached(rules):
+    calls = [(M, *s) for s in SHAPES for M in (1, 32, 33, 64, 160, 192, 193, 384, 1000, 2304)]
+    for call, (_, mt, passes, cached) in zip(calls, rules(calls)):
+        assert cached == (passes > 1), call
