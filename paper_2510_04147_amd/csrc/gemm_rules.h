@@ -2,14 +2,26 @@
 // Every choice leaves a row's sums as they are; these rules decide about time alone.
 #pragma once
 
-// Row tiles (of 32 rows) per work-group of k_gemm_rows, or 0: the few-row kernel takes the call.
+// Row tiles per pass of the few-row kernel before short passes: 32 ... 192 rows in steps of 32 take one pass; more rows take
+// passes of 160 or 192 rows, whichever needs fewer.
+inline int gemm_full_pass(int M) {
+    const int tiles = (M + 31) / 32;
+    return tiles <= 6 ? tiles : (M + 191) / 192 < (M + 159) / 160 ? 6 : 5;
+}
+
+// Row tiles (of 32 rows) per work-group of k_gemm_rows, or 0: the few-row kernel takes the call, in n-blocks of wn tiles.
 // Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of them;
 // beyond that it re-streams them per pass (gate/up of the 8B shape, us, few-row against k_gemm_rows: 200 rows 83 / 60,
-// 576 rows 150 / 114, 1000 rows 283 / 178).  Fewer than 128 work-groups leave half of the chip idle: then the
+// 576 rows 149 / 114, 1000 rows 284 / 177).  Fewer than 128 work-groups leave half of the chip idle: then the
 // few-row kernel's narrower n-blocks spread better.  Among the tiles the fewest rounds over the 256 CUs win, a
 // round of 96, 128 or 160 rows costing 0.78 : 1 : 1.3 (measured at 640 and 1000 rows: 47, 59 and 78 us a
 // round; the 160-row tile has registers for one weight chunk in flight only, the others for three).
-inline int gemm_rows_tile(int M, int N, int split) {
+// The few-row kernel's 96-row n-blocks, where they fill the chip, count along: a round of 160 or 192 rows costs 0.65 or
+// 0.75 there.  That keeps it for 321 to 384 rows of the 8B shape: QKV 63.5 - 65.2 us (k_gemm_rows 65.9 - 69.4), gate/up
+// 97.6 - 103.8 (99.1 - 105.9), sixteen layers and the LM head at 352 rows 4.46 ms (4.70), at 384 rows 4.57 (4.84).
+// Its 128- and 64-row n-blocks are no faster there (down 59.7 - 62.6 / 58.8 - 62.4, attention output 34.5 - 35.8 /
+// 24.4 - 26.8).
+inline int gemm_rows_tile(int M, int N, int split, int wn) {
     if (M <= 192) return 0;
     const int n_blocks = (N / 32 + 7) / 8, cost[3] = {78, 100, 130};
     int best = 0, best_cost = 0;
@@ -17,6 +29,11 @@ inline int gemm_rows_tile(int M, int N, int split) {
         const long long wgs = (long long)n_blocks * split * ((M + mt * 32 - 1) / (mt * 32));
         const long long c = (wgs + 255) / 256 * cost[mt - 3];
         if (wgs >= 128 && (best == 0 || c < best_cost)) { best = mt; best_cost = (int)c; }
+    }
+    const long long blocks = (long long)((N / 32 + wn - 1) / wn) * split;
+    if (wn == 3 && blocks >= 256) {
+        const int mt = gemm_full_pass(M);
+        if ((blocks * ((M + mt * 32 - 1) / (mt * 32)) + 255) / 256 * (mt == 6 ? 75 : 65) < best_cost) return 0;
     }
     return best;
 }
@@ -32,16 +49,13 @@ struct GemmPass {
     bool cached;
 };
 
-// 32 ... 192 rows in steps of 32 take one pass; more rows (of matrices too small for k_gemm_rows) take passes of 160 or 192
-// rows, whichever needs fewer.
 // Small matrices, whose n-blocks leave more than half of the CUs idle, take shorter passes until 128 work-groups
 // run: a work-group's time is its K walk times its row tiles
 // (192 rows, K = 512, us, one pass / short passes: gate/up of 1536 channels 17 / 7.3, LM head of 2080 tokens 14.7 / 9.4,
 // attention output 10 / 4.7).
 inline GemmPass gemm_few_row_pass(int M, int N, int split, int wn) {
     const int tiles = (M + 31) / 32, blocks = (N / 32 + wn - 1) / wn * split;
-    int mt = tiles;
-    if (mt > 6) mt = (M + 191) / 192 < (M + 159) / 160 ? 6 : 5;
+    int mt = gemm_full_pass(M);
     while (mt > 1 && (long long)blocks * ((tiles + mt - 1) / mt) < 128) --mt;
     const int passes = (tiles + mt - 1) / mt;
     return GemmPass{mt, passes, passes > 1};

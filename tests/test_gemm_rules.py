@@ -12,7 +12,7 @@ int main() {
     int M, N, K, split, wn;
     while (std::scanf("%d %d %d %d %d", &M, &N, &K, &split, &wn) == 5) {
         const GemmPass p = gemm_few_row_pass(M, N, split, wn);
-        std::printf("%d %d %d %d\\n", gemm_rows_tile(M, N, split), p.mt, p.passes, (int)p.cached);
+        std::printf("%d %d %d %d\\n", gemm_rows_tile(M, N, split, wn), p.mt, p.passes, (int)p.cached);
     }
 }
 """
@@ -48,3 +48,13 @@ def test_weights_that_several_passes_read_are_cached(rules):
     calls = [(M, *s) for s in SHAPES for M in (1, 32, 33, 64, 160, 192, 193, 384, 1000, 2304)]
     for call, (_, mt, passes, cached) in zip(calls, rules(calls)):
         assert cached == (passes > 1), call
+
+
+def test_two_full_passes_are_kept_where_they_are_faster(rules):
+    """8B shape: two 192-row passes of QKV and gate/up beat the many-row kernel at 321 to 384 rows; down, attention
+    output and LM head, and every matrix at the rows around them, do not."""
+    qkv, o, gu, down, lm = SHAPES[:5]
+    for M in (321, 352, 384):
+        assert [r[0] == 0 for r in rules([(M, *s) for s in (qkv, o, gu, down, lm)])] == [True, False, True, False, False], M
+    for M in (193, 256, 257, 320, 385, 448, 576, 640, 705, 768, 1000, 2304):
+        assert all(r[0] > 0 for r in rules([(M, *s) for s in (qkv, o, gu, down, lm)])), M
