@@ -22,6 +22,7 @@ extern "C" {
 
 /* One linear step of layer `layer` (ignored for SSD_LIN_LM) with the kernel path the context
  * currently selects: x and out are device pointers, x in cfg.dtype, row-major, M <= max_rows.
+ * x may start anywhere that suits its type; from a 16-byte boundary it takes the fastest kernels, with the same results.
  * Split-K partial sums are added in split order, as the forward's consumers do.
  * Asynchronous on the context's stream.  Errors: SSD_EINVAL, SSD_ERANGE. */
 int ssd_k_linear(ssd_ctx* ctx, int which, int layer, const void* x, int M, void* out);

@@ -1,6 +1,7 @@
 // Which MFMA GEMM kernel takes a call and in what passes: plain C++ without HIP, so that a host compiler can check it.
 // Every choice leaves a row's sums as they are; these rules decide about time alone.
 #pragma once
+#include <stdint.h>
 
 // Row tiles per pass of the few-row kernel before short passes: 32 ... 192 rows in steps of 32 take one pass; more rows take
 // passes of 160 or 192 rows, whichever needs fewer.
@@ -21,8 +22,10 @@ inline int gemm_full_pass(int M) {
 // 97.6 - 103.8 (99.1 - 105.9), sixteen layers and the LM head at 352 rows 4.46 ms (4.70), at 384 rows 4.57 (4.84).
 // Its 128- and 64-row n-blocks are no faster there (down 59.7 - 62.6 / 58.8 - 62.4, attention output 34.5 - 35.8 /
 // 24.4 - 26.8).
-inline int gemm_rows_tile(int M, int N, int split, int wn) {
-    if (M <= 192) return 0;
+// X, the activations, must start on 16 bytes (their rows then do: K is a multiple of 64): k_gemm_rows copies them to LDS in
+// 16-byte pieces.  The kernel-level entry points take any pointer; the few-row kernel reads others as it always did.
+inline int gemm_rows_tile(const void* X, int M, int N, int split, int wn) {
+    if (M <= 192 || ((uintptr_t)X & 15)) return 0;
     const int n_blocks = (N / 32 + 7) / 8, cost[3] = {78, 100, 130};
     int best = 0, best_cost = 0;
     for (int mt = 3; mt <= 5; ++mt) {

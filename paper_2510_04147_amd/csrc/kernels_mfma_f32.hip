@@ -27,7 +27,7 @@ bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, vo
     *n_split = split;
     const int nch = K / split / KC;
     GemmArgs a{nch, x, wp, out, M, N, K, split, stride, -1, 0, {}, st};
-    if (const int rt = gemm_rows_tile(M, N, split, wn)) return gemm_rows_f32(a, rt);
+    if (const int rt = gemm_rows_tile(x, M, N, split, wn)) return gemm_rows_f32(a, rt);
     a.pass = gemm_few_row_pass(M, N, split, wn);
     return wn == 3 ? gemm_f32_wn3(a) : wn == 2 ? gemm_f32_wn2(a) : gemm_f32_wn4(a);
 }

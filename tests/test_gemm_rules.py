@@ -12,7 +12,9 @@ int main() {
     int M, N, K, split, wn;
     while (std::scanf("%d %d %d %d %d", &M, &N, &K, &split, &wn) == 5) {
         const GemmPass p = gemm_few_row_pass(M, N, split, wn);
-        std::printf("%d %d %d %d\\n", gemm_rows_tile(M, N, split, wn), p.mt, p.passes, (int)p.cached);
+        std::printf("%d %d %d %d", gemm_rows_tile((const void*)4096, M, N, split, wn), p.mt, p.passes, (int)p.cached);
+        for (uintptr_t x = 4098; x <= 4112; x += 2) std::printf(" %d", gemm_rows_tile((const void*)x, M, N, split, wn));
+        std::printf("\\n");
     }
 }
 """
@@ -38,7 +40,7 @@ def rules(tmp_path_factory):
 
 def test_passes_cover_the_rows(rules):
     calls = [(M, *s) for s in SHAPES for M in (1, 31, 32, 33, 64, 65, 96, 97, 160, 161, 192, 193, 320, 321, 384, 385, 1000, 2304, 16384)]
-    for (M, N, K, split, wn), (rows_tile, mt, passes, cached) in zip(calls, rules(calls)):
+    for (M, N, K, split, wn), (rows_tile, mt, passes, cached) in zip(calls, (r[:4] for r in rules(calls))):
         assert rows_tile in (0, 3, 4, 5) and 1 <= mt <= 6, (M, N)
         assert (passes - 1) * mt * 32 < M <= passes * mt * 32, (M, N, mt, passes)
         assert rows_tile == 0 or (M > 192 and -(-N // 256) * split * -(-M // (32 * rows_tile)) >= 128), (M, N)
@@ -46,7 +48,7 @@ def test_passes_cover_the_rows(rules):
 
 def test_weights_that_several_passes_read_are_cached(rules):
     calls = [(M, *s) for s in SHAPES for M in (1, 32, 33, 64, 160, 192, 193, 384, 1000, 2304)]
-    for call, (_, mt, passes, cached) in zip(calls, rules(calls)):
+    for call, (_, mt, passes, cached) in zip(calls, (r[:4] for r in rules(calls))):
         assert cached == (passes > 1), call
 
 
@@ -58,3 +60,9 @@ def test_two_full_passes_are_kept_where_they_are_faster(rules):
         assert [r[0] == 0 for r in rules([(M, *s) for s in (qkv, o, gu, down, lm)])] == [True, False, True, False, False], M
     for M in (193, 256, 257, 320, 385, 448, 576, 640, 705, 768, 1000, 2304):
         assert all(r[0] > 0 for r in rules([(M, *s) for s in (qkv, o, gu, down, lm)])), M
+
+
+def test_unaligned_rows_stay_with_the_few_row_kernel(rules):
+    """The many-row kernel copies 16 bytes at a time: x at byte offsets 2, 4 ... 14 never goes there, at 16 as at 0."""
+    for r in rules([(M, *s) for s in SHAPES for M in (160, 193, 256, 640, 1000, 2304)]):
+        assert r[4:] == (0,) * 7 + (r[0],)

@@ -39,3 +39,26 @@ def test_passes_equal_single_tiles(shape):
                 assert torch.equal(call(x), ref), (shape, M, which)
     finally:
         eng.close()
+
+
+def test_unaligned_rows_equal_aligned_ones():
+    """Row counts of the many-row kernel with x off a 16-byte boundary: the few-row kernel takes the call, same rows."""
+    from paper_2510_04147_amd import binding
+    cfg = synth.model_config("8b", n_layers=1, d_model=896, d_ffn=9232, vocab=21152)
+    w = synth.gen_weights(cfg, 5, device="cuda")
+    eng = binding.SSD(cfg, w, max_seqs=1, max_seq_len=64, block=32, max_draft=4, max_rows=700)
+    d, F, nqkv = cfg["d_model"], cfg["d_ffn"], (cfg["n_q_heads"] + 2 * cfg["n_kv_heads"]) * cfg["head_dim"]
+    try:
+        for M in (193, 641):
+            x = (torch.randn(M, d, device="cuda") * 0.5).bfloat16()
+            for which, cols in ((0, nqkv), (2, F), (4, 3)):
+                outs = []
+                for off in (0, 2, 4):                    # elements: byte offsets 0, 4, 8
+                    y = torch.empty(x.numel() + 8, device="cuda", dtype=x.dtype)[off:off + x.numel()].view_as(x).copy_(x)
+                    assert y.data_ptr() % 16 == 2 * off
+                    out = torch.full((M * cols,), float("nan"), device="cuda", dtype=torch.bfloat16 if which == 2 else torch.float32)
+                    eng.k_linear(which, 0, y, out)
+                    outs.append(out)
+                assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (M, which)
+    finally:
+        eng.close()
