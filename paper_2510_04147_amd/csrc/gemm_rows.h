@@ -83,7 +83,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(const bf16_t* X, const uint4*
     auto issue_x1 = [&](int j, int slot, int c) {                            // load j of the wave
         const char* src = xrow0 + (size_t)chunk_at(c) * (KC * 2);
         const unsigned dst = lds0 + slot * SB + (wave + 8 * j) * 1024;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(xoff[j]), "s"(src) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(xoff[j]), "s"(src) : "memory", "m0");
     };
     uint4 w0[WF], w1[WF], w2[WF], w3[WF];
 #define SSD_WSLOT(i) ((i) % DW == 0 ? w0 : (i) % DW == 1 ? w1 : (i) % DW == 2 ? w2 : w3)
