@@ -74,6 +74,14 @@ __device__ __forceinline__ int gemm_k_start(int row, int bz, int nchunks) {
     return (int)(((unsigned)(row / 768) * 5u + (unsigned)bz * 3u) % (unsigned)nchunks);
 }
 
+// Between accesses to LDS by different lanes of one wave.  No instruction: a wave's LDS accesses complete in order, but the
+// compiler orders them by address within a lane only.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------------------
 // GEMM.  Work-group = WN x WK waves.  Wave (wn, wk) owns one n-tile of 32
 // weight rows and, of every K chunk of WK*32 columns, the 32 columns
@@ -342,9 +350,10 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
                         v[gq] = make_float4(acc[0][mt][g * 4] + o.x, acc[0][mt][g * 4 + 1] + o.y,
                                             acc[0][mt][g * 4 + 2] + o.z, acc[0][mt][g * 4 + 3] + o.w);
                     }
+                    wave_lds_order();                        // every lane has read what is overwritten next
 #pragma unroll
                     for (int gq = 0; gq < 2; ++gq) t[lm * 4 + ((gq * 2 + lh) ^ ((lm >> 1) & 3))] = v[gq];
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes of this wave wrote what is read next
+                    wave_lds_order();                        // other lanes wrote what is read next
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int r = h * 16 + (lane >> 2), m = m0 + mt * 32 + r;

@@ -212,10 +212,11 @@ __global__ __launch_bounds__(512) void k_gemm_rows(const bf16_t* X, const uint4*
             // 79.5 -> 77.2, attention output 31.1 -> 29.7); the area is the one the partner's sums came in, which only this wave reads, and
             // piece s of row r lies in slot s ^ (r % 8)
             float4* t = b + (wave ^ 4) * 256;
+            wave_lds_order();                                            // every lane has read what is overwritten next
 #pragma unroll
             for (int g = 0; g < 4; ++g)
                 t[lm * 8 + ((g * 2 + lh) ^ (lm & 7))] = make_float4(v[g * 4], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes of this wave wrote what is read next
+            wave_lds_order();                                            // other lanes wrote what is read next
             float* out = (float*)outv + (size_t)bz * split_stride + my_nt * 32 + (lane & 7) * 4;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {

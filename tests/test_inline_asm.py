@@ -1,4 +1,5 @@
-"""Inline assembly in the kernel sources tells the compiler every register it changes."""
+"""What the kernel sources have to tell the compiler beyond the language: registers that inline assembly changes, and the
+order of LDS accesses that different lanes of a wave make to the same place."""
 import glob
 import os
 import re
@@ -14,3 +15,12 @@ def test_statements_that_write_m0_declare_it():
                 seen += 1
                 assert re.search(r':[^:]*"m0"[^:]*\)\s*$', rest), (os.path.basename(path), text)
     assert seen == 1
+
+
+def test_areas_exchanged_within_a_wave_are_ordered_on_both_sides():
+    """Both fp32 epilogues read the partner's sums, write the finished tile over them and read it in row order."""
+    for name in ("gemm_mfma.h", "gemm_rows.h"):
+        text = open(os.path.join(CSRC, name)).read()
+        at = text.index("float4* t = ")
+        write, read = re.search(r"\bt\[lm \* \d", text[at:]).start(), re.search(r"= t\[r \* \d", text[at:]).start()
+        assert "wave_lds_order();" in text[at:at + write] and "wave_lds_order();" in text[at + write:at + read], name
