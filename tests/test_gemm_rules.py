@@ -66,3 +66,31 @@ def test_unaligned_rows_stay_with_the_few_row_kernel(rules):
     """The many-row kernel copies 16 bytes at a time: x at byte offsets 2, 4 ... 14 never goes there, at 16 as at 0."""
     for r in rules([(M, *s) for s in SHAPES for M in (160, 193, 256, 640, 1000, 2304)]):
         assert r[4:] == (0,) * 7 + (r[0],)
+
+
+def test_gpu_test_reaches_every_tile(rules):
+    """Row counts and shapes of test_gpu_many_rows.py: every tile height with every epilogue, the fp32 one with K whole and
+    in 2, 4 and 8 slices, and every tile height among the row counts compared with fp64."""
+    from paper_2510_04147_amd import synth
+    from test_gpu_many_rows import ROWS, ROWS64, SHAPES as MODELS
+    seen, seen64 = set(), set()
+    for m in MODELS:
+        cfg = synth.model_config("8b", **m)
+        d, F, nq = cfg["d_model"], cfg["d_ffn"], cfg["n_q_heads"] * cfg["head_dim"]
+        for epi, N, K in (("f32", nq + 2 * cfg["n_kv_heads"] * cfg["head_dim"], d), ("f32", d, nq), ("f32", d, F),
+                          ("swiglu", 2 * F, d), ("lm", cfg["vocab"], d)):
+            if K % 64 or N % 32:
+                continue                                     # the plain kernel's
+            wn, split = (3 if N // 32 % 3 == 0 else 4) if epi == "swiglu" else 4, 1
+            if epi == "f32":                                 # as launch_gemm_mfma_f32 chooses
+                wn, split = (3 if N // 32 % 3 == 0 else 4, 2) if N > 8192 else (2, 4) if K <= 4096 else (4, 8)
+                while K % (split * 64):
+                    split -= 1
+            for M, r in zip(ROWS, rules([(M, N, K, split, wn) for M in ROWS])):
+                if r[0]:
+                    seen.add((epi, split, r[0]))
+                    if M in ROWS64 and epi != "swiglu":
+                        seen64.add((epi, r[0]))
+    assert {(e, t) for e, _, t in seen} == {(e, t) for e in ("f32", "swiglu", "lm") for t in (3, 4, 5)}
+    assert {(s, t) for e, s, t in seen if e == "f32"} >= {(s, t) for s in (1, 2, 4, 8) for t in (3, 4, 5)}, sorted(seen)
+    assert seen64 == {(e, t) for e in ("f32", "lm") for t in (3, 4, 5)}, sorted(seen64)
