@@ -1,4 +1,4 @@
-// Which MFMA GEMM kernel takes a call and in what passes: plain C++ without HIP, so that a host compiler can check it.
+// Which GEMM kernel takes a call and in what passes: plain C++ without HIP, so that a host compiler can check it.
 // Every choice leaves a row's sums as they are; these rules decide about time alone.
 #pragma once
 #include <stdint.h>
@@ -62,4 +62,15 @@ inline GemmPass gemm_few_row_pass(int M, int N, int split, int wn) {
     while (mt > 1 && (long long)blocks * ((tiles + mt - 1) / mt) < 128) --mt;
     const int passes = (tiles + mt - 1) / mt;
     return GemmPass{mt, passes, passes > 1};
+}
+
+// Plain GEMM: k_gemm_plain_small takes the call while k_gemm_plain's 64x64 tiles would give a CU at most one work-group
+// (fp32, us, 64x64 tiles / small ones: 12 tiles 51 / 5, 60 tiles 57 / 16, 120 tiles 105 / 35, 165 tiles 68 / 44, 240 tiles
+// 105 / 70; bf16, N = 4096, K = 12288: 64 tiles 1271 / 236, 192 tiles 1300 / 639, 256 tiles 1322 / 978; the small ones
+// read LDS three times as much per FMA).
+// Unaligned operands (kernel-level entry points take any pointer) stay with the scalar loads.
+#define GEMM_PLAIN_TILE 64
+inline bool gemm_plain_small_tiles(const void* X, const void* W, int M, int N) {
+    const long long tiles = (long long)((N + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE) * ((M + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE);
+    return tiles <= 256 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0;
 }

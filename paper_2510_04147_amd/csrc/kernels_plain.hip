@@ -7,6 +7,7 @@
 // reproduce stepwise decoding exactly.
 #include <type_traits>
 
+#include "gemm_rules.h"
 #include "ssd_internal.h"
 
 typedef uint16_t bf16_t;
@@ -418,8 +419,8 @@ __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__
 // Plain tiled GEMM  out[M,N] = X[M,K] * W[N,K]^T, fp32 accumulation in
 // ascending k.  64x64 tile per work-group, 4x4 outputs per thread.
 // ------------------------------------------------------------------------
-#define PBM 64
-#define PBN 64
+#define PBM GEMM_PLAIN_TILE
+#define PBN GEMM_PLAIN_TILE
 #define PBK 16
 
 // Fused LM-head reduction over 16 adjacent lanes that hold NJ consecutive logits each, from vocabulary row n0 of this
@@ -970,11 +971,7 @@ template <typename T>
 static void gemm_plain_t(const ssd_ctx* c, int epi, const T* X, const T* W, void* out, int M, int N, int K,
                          hipStream_t st) {
     dim3 grid((N + PBN - 1) / PBN, (M + PBM - 1) / PBM);
-    // Small tiles while the 64x64 ones give a CU at most one work-group (see k_gemm_plain_small; fp32, us, 64x64 tiles /
-    // small ones: 12 tiles 51 / 5, 60 tiles 57 / 16, 120 tiles 105 / 35, 165 tiles 68 / 44, 240 tiles 105 / 70; the
-    // small ones read LDS three times as much per FMA).  Unaligned operands (kernel-level entry points take any
-    // pointer) stay with the scalar loads.
-    if ((size_t)grid.x * grid.y <= 256 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0) {
+    if (gemm_plain_small_tiles(X, W, M, N)) {
         const unsigned gy = (M + SBM - 1) / SBM;
         if (epi == EPI_F32)
             k_gemm_plain_small<T, EPI_F32, 1><<<dim3((N + 15) / 16, gy), 128, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);

@@ -94,3 +94,27 @@ def test_gpu_test_reaches_every_tile(rules):
     assert {(e, t) for e, _, t in seen} == {(e, t) for e in ("f32", "swiglu", "lm") for t in (3, 4, 5)}
     assert {(s, t) for e, s, t in seen if e == "f32"} >= {(s, t) for s in (1, 2, 4, 8) for t in (3, 4, 5)}, sorted(seen)
     assert seen64 == {(e, t) for e in ("f32", "lm") for t in (3, 4, 5)}, sorted(seen64)
+
+
+def test_plain_gemm_gpu_test_crosses_the_switch(tmp_path):
+    """Shapes and row counts of test_gpu_small_tiles.py: every epilogue with at most 256 tiles of 64x64 and with more, close to
+    the limit on either side; unaligned operands never take the small tiles."""
+    from paper_2510_04147_amd import synth
+    from test_gpu_small_tiles import SHAPES as MODELS, rows_of
+    (tmp_path / "p.cpp").write_text(
+        '#include <cstdio>\n#include "gemm_rules.h"\nint main() { int M, N; while (std::scanf("%d %d", &M, &N) == 2) { '
+        'auto f = [&](uintptr_t x, uintptr_t w) { return (int)gemm_plain_small_tiles((const void*)x, (const void*)w, M, N); }; '
+        'std::printf("%d %d %d\\n", f(4096, 8192), f(4100, 8192), f(4096, 8194)); } }')
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "p.cpp"), "-o", str(tmp_path / "p")], check=True)
+    calls = []
+    for m in MODELS:
+        cfg = synth.model_config("tiny", **m)
+        for epi, N in (("f32", (cfg["n_q_heads"] + 2 * cfg["n_kv_heads"]) * cfg["head_dim"]), ("f32", cfg["d_model"]),
+                       ("swiglu", cfg["d_ffn"]), ("lm", cfg["vocab"])):
+            calls += [(epi, M, N, -(-N // 64) * -(-M // 64)) for M in rows_of(m)]
+    out = subprocess.run([str(tmp_path / "p")], input="".join("%d %d\n" % c[1:3] for c in calls), capture_output=True, text=True, check=True)
+    small = [tuple(int(v) for v in line.split()) for line in out.stdout.splitlines()]
+    assert small == [(int(c[3] <= 256), 0, 0) for c in calls]
+    for epi in ("f32", "swiglu", "lm"):
+        tiles = [c[3] for c in calls if c[0] == epi]
+        assert any(246 < t <= 256 for t in tiles) and any(256 < t < 280 for t in tiles), (epi, sorted(tiles)[-6:])
