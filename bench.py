@@ -35,7 +35,7 @@ def kernel_source_stamp():
     stamp of the build it was taken with, and is only quoted while the sources still hash to it."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gemm_mfma.h", "kernels_mfma.hip", "kernels_mfma_f32.hip"):
+    for f in ("gemm_rules.h", "gemm_mfma.h", "kernels_mfma.hip", "kernels_mfma_f32.hip"):
         h.update(open(os.path.join(ROOT, "paper_2510_04147_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -351,14 +351,15 @@ def main():
     traffic, traffic_note = read_measured_traffic(args.workload)
     # the bound is whichever of the two rooflines takes longer for this kernel's bytes and flops
     hbm_bound = gu_bytes / (HBM_PEAK_GBS * 1e9) >= gu_flops / (MFMA_BF16_PEAK_TFLOPS * 1e12)
+    gu_kernel = ("k_gemm_plain" if cfg["dtype"] == "fp32" else "k_gemm_mfma" if M <= 192 else "k_gemm_rows") + "<SwiGLU> (gate/up projection)"
     if hbm_bound:
-        roof = {"kernel": "k_gemm_mfma<SwiGLU> (gate/up projection)", "bound": "hbm", "achieved": gu_gbs,
+        roof = {"kernel": gu_kernel, "bound": "hbm", "achieved": gu_gbs,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gu_gbs / HBM_PEAK_GBS, "traffic": traffic,
                 "bytes_per_launch": gu_bytes, "us_per_launch": gu_us, "us_per_launch_with_event_pairs": gu_us_raw,
                 "event_pair_overhead_us": event_pair_us, "launches_timed": gu["launches"],
                 "us_per_launch_back_to_back_alone": gu_iso_us}
     else:
-        roof = {"kernel": "k_gemm_mfma<SwiGLU> (gate/up projection)", "bound": "mfma", "achieved": gu_tflops,
+        roof = {"kernel": gu_kernel, "bound": "mfma", "achieved": gu_tflops,
                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": gu_tflops / MFMA_BF16_PEAK_TFLOPS,
                 "traffic": traffic, "flops_per_launch": gu_flops, "achieved_GBs": gu_gbs, "us_per_launch": gu_us,
                 "us_per_launch_with_event_pairs": gu_us_raw,

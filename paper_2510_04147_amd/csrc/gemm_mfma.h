@@ -1,6 +1,6 @@
 // The MFMA GEMM kernel template and its launchers, shared by the translation units that instantiate it
-// (kernels_mfma.hip: SwiGLU and LM-head epilogues; kernels_mfma_f32.hip: fp32 partial sums), so that they
-// compile in parallel.  See kernels_mfma.hip for the design.
+// (gemm_f32_*, gemm_swiglu_*, gemm_lmhead_*: one per epilogue and work-group shape), so that they compile in parallel.
+// See kernels_mfma.hip for the design.
 #pragma once
 #include <cstdlib>
 #include <type_traits>
@@ -67,9 +67,10 @@ __device__ __forceinline__ void lm_tile_partial(const floatx16& v, int nt, int l
     p[2] = se + __shfl_xor(se, 32, 64);
 }
 
-// First chunk of a work-group's K walk: the work-groups start at different chunks, which spreads the grid's weight
-// streams over the HBM channels.  One start per 768 weight rows (a multiple of every n-block width) and
-// k-slice, so that the kernels for few and for many rows sum in the same order.
+// First chunk of a work-group's K walk: groups of work-groups start at different chunks, which spreads the grid's weight
+// streams over the HBM channels.  One start per 768 weight rows (a multiple of every n-block width: three to twelve
+// neighbouring n-blocks; a matrix of at most 768 rows has one) and k-slice, so that the kernels for few and for many
+// rows sum in the same order.
 __device__ __forceinline__ int gemm_k_start(int row, int bz, int nchunks) {
     return (int)(((unsigned)(row / 768) * 5u + (unsigned)bz * 3u) % (unsigned)nchunks);
 }
@@ -96,9 +97,10 @@ __device__ __forceinline__ void wave_lds_order() {
 // With the chunk count known at compile time (NCH > 0) the loop is straight-line
 // code, so the compiler's wait counts are exact; NCH = 0 is the same pipeline as
 // a loop unrolled by DW with loads past the end clamped (in bounds, unused).
-// Every work-group starts its K walk at a different chunk and wraps, which
-// spreads the grid's weight streams over the HBM channels; the order depends
-// on the n-tile only, so a row's summation order is the same in every forward.
+// The K walk starts at a chunk that depends on the k-slice and on the group of
+// 768 weight rows (gemm_k_start) and wraps, which spreads the grid's weight
+// streams over the HBM channels; the order depends on the n-tile only, so a
+// row's summation order is the same in every forward.
 // CACHED: weight loads with the default cache policy (GemmPass).
 // DBG is for measurement builds only (bit 0: no MFMA, bit 1: no activation
 // loads, bit 2: no epilogue, bit 3: every chunk reads chunk 0's activations, bit 4: no weight

@@ -18,9 +18,10 @@
 // One barrier per chunk c: it tells that chunk c + 1 is in LDS and that chunk c - 1 has been read by everyone.
 // Fragments are read from LDS one 16-column step ahead of the MFMAs that use them.
 //
-// Bound: at 640 rows of the 8B gate/up shape 120 us (1.07 PFLOP/s; few-row kernel 168 us), 1000 rows 178 us (283 us).
-// With its MFMAs and LDS reads alone the kernel runs at 1.5 PFLOP/s, what a large library product reaches on this
-// chip; the 32 KB of weights a work-group pulls through its L1 per chunk, next to 16 KB of activations, take the rest.
+// Bound: at 640 rows of the 8B gate/up shape 121 us (1.07 PFLOP/s; few-row kernel 168 us), 1000 rows 183 us (283 us).
+// Without its loads (MFMAs, LDS reads and barriers on whatever LDS and registers hold) the kernel takes 76 and 108 us: the
+// 32 KB of weights a work-group pulls through its L1 per chunk, next to 16 KB of activations, take the rest.  A large
+// library product reaches 1.4 to 1.6 PFLOP/s on random operands and 2.1 on zeros on this chip.
 // The two chains per output cap the tile: 256 x 128 outputs fill half of the register file.  Deeper rings (5 weight
 // chunks, 5 or 6 activation stages), non-temporal weights, a raised wave priority around the MFMAs and a common
 // start of all K walks made no difference, nor did gathering the SwiGLU outputs of a row tile in LDS for 256-byte

@@ -13,7 +13,7 @@ inline int gemm_full_pass(int M) {
 // Row tiles (of 32 rows) per work-group of k_gemm_rows, or 0: the few-row kernel takes the call, in n-blocks of wn tiles.
 // Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of them;
 // beyond that it re-streams them per pass (gate/up of the 8B shape, us, few-row against k_gemm_rows: 200 rows 83 / 60,
-// 576 rows 149 / 114, 1000 rows 284 / 177).  Fewer than 128 work-groups leave half of the chip idle: then the
+// 576 rows 150 / 117, 1000 rows 283 / 183).  Fewer than 128 work-groups leave half of the chip idle: then the
 // few-row kernel's narrower n-blocks spread better.  Among the tiles the fewest rounds over the 256 CUs win, a
 // round of 96, 128 or 160 rows costing 0.78 : 1 : 1.3 (measured at 640 and 1000 rows: 47, 59 and 78 us a
 // round; the 160-row tile has registers for one weight chunk in flight only, the others for three).

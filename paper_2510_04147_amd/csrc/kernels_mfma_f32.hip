@@ -1,5 +1,5 @@
-// The fp32-partial-sum instantiations of the MFMA GEMM (QKV, attention output and down projections):
-// a translation unit of their own so that they compile next to the other epilogues.
+// The fp32-partial-sum MFMA GEMMs (QKV, attention output and down projections): work-group shape, split along K and
+// kernel.  The instantiations are in gemm_f32_*.hip and gemm_rows_f32.hip.
 #include "gemm_mfma.h"
 
 bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, void* out, int M, int N, int K,

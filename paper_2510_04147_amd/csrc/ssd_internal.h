@@ -264,8 +264,7 @@ void launch_gemm_plain(const ssd_ctx* c, int epi, const void* X, const void* W, 
 bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, void* out, int M, int* n_split,
                       hipStream_t st);
 int lm_tiles_mfma(int V);
-// the fp32-partial-sum GEMMs (QKV, attention output, down), instantiated in a translation unit of their own;
-// mt row tiles of 32 rows per pass, m_chunks passes
+// the fp32-partial-sum GEMMs (QKV, attention output, down); *n_split = the number of partial sums
 bool launch_gemm_mfma_f32(const ssd_ctx* c, const uint16_t* x, const uint4* wp, void* out, int M, int N, int K,
                           int* n_split, hipStream_t st);
 // n_part >= 0: the kernel also sums the QKV projection's n_part partial sums and applies the rotary
