@@ -1,5 +1,5 @@
-// fp32 partial sums, 64-row n-blocks (the attention output projection): 16 chunks per k-slice at 4096
+// fp32 partial sums, 64-row n-blocks (the attention output projection)
 // (one instantiation unit of the MFMA GEMM template; see kernels_mfma.hip for the design)
 #include "gemm_mfma.h"
 
-bool gemm_f32_wn2(const GemmArgs& a) { return launch_shape<2, 2, EPI_F32, 16>(a); }
+bool gemm_f32_wn2(const GemmArgs& a) { return launch_shape<2, EPI_F32>(a); }

@@ -1,5 +1,5 @@
-// fp32 partial sums, 96-row n-blocks (the QKV projection): 32 chunks per k-slice at d_model 4096
+// fp32 partial sums, 96-row n-blocks (the QKV projection)
 // (one instantiation unit of the MFMA GEMM template; see kernels_mfma.hip for the design)
 #include "gemm_mfma.h"
 
-bool gemm_f32_wn3(const GemmArgs& a) { return launch_shape<3, 2, EPI_F32, 32>(a); }
+bool gemm_f32_wn3(const GemmArgs& a) { return launch_shape<3, EPI_F32>(a); }

@@ -13,6 +13,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// for lambdas, whose captures have to stay in registers
+#define SSD_INLINE __attribute__((always_inline))
+
 // Compile-time loop: f(integral_constant<int, C>) for C in [BEGIN, END).  The ring slots of the
 // GEMM pipeline are selected by these constants, so no register array is ever indexed by a
 // run-time value (which would push it to scratch memory).
@@ -29,42 +32,50 @@ __device__ __forceinline__ void static_for(F&& f) {
 // arithmetic it follows; the results are rounded to bf16 or summed over a vocabulary afterwards.
 __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 
-__device__ __forceinline__ uint16_t f2bf_m(float f) {
-    uint32_t x = __float_as_uint(f);
-    if ((x & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((x >> 16) | 0x40);
-    x += 0x7fffu + ((x >> 16) & 1u);
-    return (uint16_t)(x >> 16);
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// two values to bf16, to nearest even (one instruction)
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
 }
+__device__ __forceinline__ uint16_t f2bf_m(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
-// silu(gate) * up, rounded to bf16
-__device__ __forceinline__ uint16_t swiglu_bf16(float g, float u) {
-    return f2bf_m(g * __builtin_amdgcn_rcpf(1.0f + fast_exp(-g)) * u);
+// silu(gate) * up
+__device__ __forceinline__ float swiglu(float g, float u) { return g * __builtin_amdgcn_rcpf(1.0f + fast_exp(-g)) * u; }
+
+// The other half's value: lane l gets lane l ^ 32's (no trip through LDS, unlike a shuffle).
+__device__ __forceinline__ unsigned other_half(unsigned v, int lh) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);     // [0]: the lower lanes' in both halves, [1]: the upper lanes'
+    return lh ? r[0] : r[1];
 }
+__device__ __forceinline__ float other_half(float v, int lh) { return __uint_as_float(other_half(__float_as_uint(v), lh)); }
 
 // LM head: (max, arg-max as float bits, sum of exp) of one row over the 32 vocabulary rows of tile nt; lane (lm, lh)
-// holds n = 8*(i/4) + 4*lh + i%4 of row lm.  The mask token takes no part.
-__device__ __forceinline__ void lm_tile_partial(const floatx16& v, int nt, int lh, int mask_id, float* p) {
-    float bm = -INFINITY;
+// holds n = 8*(i/4) + 4*lh + i%4 of row lm.  The mask token takes no part.  Bound by instructions: the maximum first, its
+// lowest position from the equal ones (384 rows, us, with a compare and two selects per value and shuffles through LDS /
+// this: 32000 tokens, K = 1600 55.2 / 46.5, K = 2048 65.9 / 56.8).
+__device__ __forceinline__ void lm_tile_partial(const floatx16& acc, int nt, int lh, int mask_id, float* p) {
+    floatx16 v = acc;
+    if (nt == mask_id >> 5) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (nt * 32 + (i >> 2) * 8 + lh * 4 + (i & 3) == mask_id) v[i] = -INFINITY;
+    }
+    float bm = -INFINITY;                                    // a NaN is never the maximum
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bm = fmaxf(bm, v[i]);
+    bm = fmaxf(bm, other_half(bm, lh));
     int bi = 0x7fffffff;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int n = nt * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
-        if (n != mask_id && v[i] > bm) { bm = v[i]; bi = n; }
-    }
-    {
-        const float om = __shfl_xor(bm, 32, 64);
-        const int oi = __shfl_xor(bi, 32, 64);
-        if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
-    }
+    for (int i = 15; i >= 0; --i) bi = v[i] == bm ? (i >> 2) * 8 + (i & 3) : bi;
+    bi = bi == 0x7fffffff || bm == -INFINITY ? 0x7fffffff : nt * 32 + lh * 4 + bi;
+    bi = min(bi, (int)other_half((unsigned)bi, lh));
     float se = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int n = nt * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
-        if (n != mask_id) se += fast_exp(v[i] - bm);
-    }
+    for (int i = 0; i < 16; ++i) se += fast_exp(v[i] - bm);
     p[0] = bm;
     p[1] = __int_as_float(bi);
-    p[2] = se + __shfl_xor(se, 32, 64);
+    p[2] = se + other_half(se, lh);
 }
 
 // First chunk of a work-group's K walk: groups of work-groups start at different chunks, which spreads the grid's weight
@@ -83,46 +94,55 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// 16 bytes per lane from src + off (per lane) to LDS address dst + 16 lane, without passing through registers.  The compiler
+// does not count these loads: whoever reads what they bring writes the wait out.  NT: non-temporal.
+template <bool NT>
+__device__ __forceinline__ void load_to_lds(unsigned dst, unsigned off, const void* src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t.if %3\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\t.else\n\tglobal_load_lds_dwordx4 %1, %2\n\t.endif"
+                 ::"s"(dst), "v"(off), "s"(src), "n"(NT ? 1 : 0) : "memory", "m0");
+}
+// At most N of this wave's loads outstanding and none of its LDS accesses, then the barrier of the work-group.
+template <int N>
+__device__ __forceinline__ void wait_and_meet() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // ------------------------------------------------------------------------
-// GEMM.  Work-group = WN x WK waves.  Wave (wn, wk) owns one n-tile of 32
-// weight rows and, of every K chunk of WK*32 columns, the 32 columns
-// [32wk, 32wk+32) (two k16 steps).
+// GEMM for few rows.  Work-group = WN x WM waves.  Wave (wn, wm) owns one n-tile of 32 weight rows, the row tiles wm,
+// wm + WM, ... of MT and, of the work-group's k-slice, every column: one chain of MFMAs per output, in chunks of KC = 64
+// columns.  k_gemm_rows builds the same chains, so a row's sums are bit for bit the same in both.
 //
-// Software pipeline, all statically indexed:
-//   weights      a ring of DW chunks in registers per wave: the fragment loads
-//                of chunk c+DW-1 are issued while chunk c is multiplied;
-//   activations  loads of chunk c+PX are issued into a register ring, chunk c+2
-//                is written to the free stage of a three-stage LDS ring while
-//                chunk c is multiplied, one barrier per chunk.
-// With the chunk count known at compile time (NCH > 0) the loop is straight-line
-// code, so the compiler's wait counts are exact; NCH = 0 is the same pipeline as
-// a loop unrolled by DW with loads past the end clamped (in bounds, unused).
+// Weights and activations go global -> LDS without passing through registers into a ring of NST stages.  From the barrier in
+// front of chunk c on, whose stage has landed and with which everyone has read chunk c - 1, chunk c - 1 + NST is loaded into
+// the stage of chunk c - 1, a fourth of its loads in front of each of four steps of 16 columns; fragments are
+// read from LDS one step ahead of the MFMAs that use them.
 // The K walk starts at a chunk that depends on the k-slice and on the group of
 // 768 weight rows (gemm_k_start) and wraps, which spreads the grid's weight
 // streams over the HBM channels; the order depends on the n-tile only, so a
 // row's summation order is the same in every forward.
 // CACHED: weight loads with the default cache policy (GemmPass).
-// DBG is for measurement builds only (bit 0: no MFMA, bit 1: no activation
-// loads, bit 2: no epilogue, bit 3: every chunk reads chunk 0's activations, bit 4: no weight
-// loads); the library instantiates DBG = 0.
+//
+// Bound by the line requests a CU keeps in flight: the weight stream and the activations, which every work-group reads whole
+// from L2, queue for them.  160 rows of the 8B shape, inside the forward, us (with two chains per output in two waves,
+// weights in register rings and activations staged through registers / this): gate/up 48.2 / 46.6, QKV 28.1 / 27.6,
+// down 27.4 / 26.3, attention output 15.5 / 14.9; 40 rows 32.4 / 32.8, 18.8 / 18.9, 19.0 / 18.8, 9.6 / 9.0.  Four stages:
+// five take 51.0 for gate/up at 160 rows, three 47.8 there but 27.4 for down; all of a chunk's loads
+// behind the barrier in one go 52.0, one wave per n-tile for all rows (WM = 1) 52.3.
 // ------------------------------------------------------------------------
-template <int WN, int WK, int R, int MT, int EPI, int NCH, bool CACHED, int DBG = 0, int DW = 4, int PX = 4, int KSTEPS = 2>
-__global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, const uint4* Wp, void* outv, int M, int N,
-                                                           int K, int ldx, int k_len, size_t split_stride,
-                                                           int mask_id, int n_tiles_out, int n_blocks, int n_split,
-                                                           int m_chunks_total) {
-    constexpr int T = WN * WK * 64, KW = 16 * KSTEPS, KC = WK * KW, ROWS = MT * 32, LDW = KC + 8;
-    constexpr int NST = 3;                              // LDS stages
-    static_assert(DW >= 2 && DW <= 6 && PX >= 3 && PX <= 4, "ring depths");
-    static_assert(EPI != EPI_SWIGLU || (WK == 2 && R == 1), "the SwiGLU epilogue is written for two k-slice waves");
-    constexpr int XSEG = ROWS * (KC / 8);               // 16-byte segments per X chunk
-    constexpr int XPT = (XSEG + T - 1) / T;             // per thread
-    constexpr int SPARE = NST * ROWS * LDW;             // LDS element offset of the per-thread spare slots
+template <int WN, int WM, int MT, int EPI, bool CACHED, int NST>
+__global__ __launch_bounds__(WN* WM * 64) void k_gemm_mfma(const bf16_t* X, const uint4* Wp, void* outv, int M, int N,
+                                                           int K, int k_len, size_t split_stride, int mask_id,
+                                                           int n_tiles_out, int n_blocks, int n_split, int m_chunks_total) {
+    constexpr int NW = WN * WM, KC = 64, KSTEPS = KC / 16, ROWS = MT * 32, TW = (MT + WM - 1) / WM;
+    constexpr int WB = WN * KSTEPS * 1024, SB = WB + ROWS * KC * 2;             // bytes of a stage: weights, activations
+    constexpr int PIECES = SB / 1024, PMIN = PIECES / NW, PMORE = PIECES % NW;  // loads of a stage; per wave
+    static_assert(NST >= 2 && PMIN * (NST - 1) < 64, "ring depth");
     extern __shared__ uint4 smem_u4[];
-    bf16_t* xs = (bf16_t*)smem_u4;                      // [NST][ROWS][LDW] + spare
+    char* const smem = (char*)smem_u4;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wn = wave % WN, wk = wave / WN;
-    const int lm = lane & 31, lh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN, wm = wave / WN, lm = lane & 31, lh = lane >> 5;
     // The grid is one-dimensional; work-groups go to the 8 XCDs round-robin by their linear id, and every
     // XCD has an L2 of its own.  The id is decoded so that with split-K all work-groups of an XCD take the
     // same k-slice, i.e. read the same slice of the activations and find it in that XCD's L2, and so that
@@ -144,340 +164,175 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
         }
     }
     const int m0 = by * ROWS;
-    const int kbeg = bz * k_len, nchunks = NCH > 0 ? NCH : k_len / KC;
+    const int kbeg = bz * k_len, nchunks = k_len / KC;
     const int KS = K >> 4, NT = N >> 5;
+    const int nt = bx * WN + wn;                         // this wave's n-tile (past the end: never stored)
+    const bool nt_ok = nt < NT;
 
-    // n-tiles of this wave (tiles past the end are clamped and never stored)
-    int nt[R];
-    bool nt_ok[R];
+    const int rot = gemm_k_start(bx * (WN * 32), bz, nchunks);
+    // Load i of this wave is piece wave + NW i of a stage: 1 KB each, first the n-tiles' fragments, then eight rows of the
+    // activations per piece, the 16-byte piece s of row r in slot s ^ (r / 2 % 8) of its line, so that the 32 rows of a
+    // fragment spread over all LDS banks.  n-tiles and rows past the end read the last one (never stored).
+    const char* xrow0 = (const char*)(X + (size_t)m0 * K + kbeg);
+    unsigned xoff[PMIN + 1];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        nt[r] = (bx * WN + wn) * R + r;
-        nt_ok[r] = nt[r] < NT;
-        if (!nt_ok[r]) nt[r] = NT - 1;
+    for (int i = 0; i <= PMIN; ++i) {
+        const int p = wave + NW * i - WN * KSTEPS;
+        const int r = p * 8 + (lane >> 3), s = (lane & 7) ^ ((r >> 1) & 7);
+        xoff[i] = p < 0 ? lane * 16 : (unsigned)(m0 + r < M ? r : M - 1 - m0) * (unsigned)(K * 2) + s * 16;
     }
-    const uint4* wbase[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) wbase[r] = Wp + ((size_t)nt[r] * KS + (kbeg >> 4) + wk * KSTEPS) * 64 + lane;
-
-    floatx16 acc[R][MT];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[r][mt][i] = 0.f;
-
-    const int rot = gemm_k_start(bx * (WN * R * 32), bz, nchunks);
-    auto chunk_at = [&](int c) {
-        c = c < nchunks - 1 ? c : nchunks - 1;
-        c += rot;
-        return c >= nchunks ? c - nchunks : c;
+    auto issue1 = [&](int i, int slot, int at) SSD_INLINE {         // at: the chunk, rotated
+        const int p = wave + NW * i;
+        const unsigned dst = lds0 + slot * SB + p * 1024;
+        const int t = p / KSTEPS;
+        if (NW * i + NW <= WN * KSTEPS || (NW * i < WN * KSTEPS && p < WN * KSTEPS)) {
+            const int n = bx * WN + t < NT ? bx * WN + t : NT - 1;
+            load_to_lds<!CACHED>(dst, xoff[i], Wp + ((size_t)n * KS + (kbeg >> 4) + at * KSTEPS + p % KSTEPS) * 64);
+        } else
+            load_to_lds<false>(dst, xoff[i], xrow0 + (size_t)at * (KC * 2));
     };
-
-    // per-thread activation segments (the same for every chunk); segments past the tile or
-    // past row M load row 0 / write a spare slot or zeros, so nothing branches
-    const bf16_t* xsrc[XPT];
-    int xdst[XPT];
-    bool xok[XPT];
+    int at = rot;                                        // the next chunk to load, rotated
+    floatx16 acc[TW];
 #pragma unroll
-    for (int i = 0; i < XPT; ++i) {
-        const int seg = tid + i * T;
-        const int m = seg / (KC / 8), sg = seg - m * (KC / 8);
-        xok[i] = seg < XSEG && m0 + m < M;
-        xsrc[i] = X + (size_t)(xok[i] ? m0 + m : 0) * ldx + kbeg + sg * 8;
-        xdst[i] = seg < XSEG ? m * LDW + sg * 8 : SPARE + tid * 8;
-    }
-
-    // the rings are separate arrays selected by compile-time constants only
-    constexpr int WF = R * KSTEPS;                      // weight fragments per chunk per wave
-    uint4 w0[WF], w1[WF], w2[WF], w3[WF], w4[WF], w5[WF];
-    uint4 x0[XPT], x1[XPT], x2[XPT], x3[XPT];
-#define SSD_WSLOT(i) ((i) % DW == 0 ? w0 : (i) % DW == 1 ? w1 : (i) % DW == 2 ? w2 : (i) % DW == 3 ? w3 : (i) % DW == 4 ? w4 : w5)
-#define SSD_XSLOT(i) ((i) % PX == 0 ? x0 : (i) % PX == 1 ? x1 : (i) % PX == 2 ? x2 : x3)
-    auto issue_w = [&](uint4* dst, int c) {
-        const size_t off = (size_t)chunk_at(c) * (KC / 16) * 64;
+    for (int t = 0; t < TW; ++t)
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+    const bool full = MT % WM == 0 || wm < MT % WM;      // this wave has TW row tiles, else TW - 1
+    const int sw = (lm >> 1) & 7;
+    struct Frags { bf16x8 w, x[TW]; } fa, fb;
+    auto read = [&](Frags& f, int slot, int ks) SSD_INLINE {
+        const char* s = smem + slot * SB;
+        f.w = *(const bf16x8*)(s + (wn * KSTEPS + ks) * 1024 + lane * 16);
 #pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) {
-                if (DBG & 16)
-                    dst[r * KSTEPS + ks] = make_uint4((unsigned)off, (unsigned)ks, 0u, 0u);
-                else if (CACHED)
-                    dst[r * KSTEPS + ks] = wbase[r][off + ks * 64];
-                else {
-                    // weights that are read once per launch: a non-temporal load keeps them from evicting the
-                    // activations, which every work-group of the XCD re-reads, from L2
-                    const u32x4 v = __builtin_nontemporal_load((const u32x4*)&wbase[r][off + ks * 64]);
-                    dst[r * KSTEPS + ks] = make_uint4(v.x, v.y, v.z, v.w);
-                }
-            }
+        for (int t = 0; t < TW; ++t)
+            if (t < TW - 1 || full)
+                f.x[t] = *(const bf16x8*)(s + WB + (wm + WM * t) * 4096 + lm * 128 + (((ks * 2 + lh) ^ sw) << 4));
     };
-    auto issue_x = [&](uint4* dst, int c) {
-        const size_t off = (DBG & 8) ? (size_t)0 : (size_t)chunk_at(c) * KC;
+    auto multiply = [&](const Frags& f) SSD_INLINE {
 #pragma unroll
-        for (int i = 0; i < XPT; ++i) {
-            if (DBG & 2)
-                dst[i] = make_uint4(c, c, c, c);
-            else
-                dst[i] = *(const uint4*)(xsrc[i] + off);
-        }
+        for (int t = 0; t < TW; ++t)
+            if (t < TW - 1 || full) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w, f.x[t], acc[t], 0, 0, 0);
     };
-    auto stage_x = [&](const uint4* src, int buf) {
-#pragma unroll
-        for (int i = 0; i < XPT; ++i) {
-            uint4 v = src[i];
-            if (!xok[i]) v = make_uint4(0, 0, 0, 0);
-            const int off = xdst[i] < SPARE ? buf * ROWS * LDW + xdst[i] : xdst[i];
-            *(uint4*)(xs + off) = v;
-        }
+    auto issue = [&](int i, int slot) SSD_INLINE {       // i up to PMIN; some waves have one load more than others
+        if (i < PMIN || wave < PMORE) issue1(i, slot, at);
     };
-    // all activation fragments of the chunk are read from LDS first, then the MFMAs run back
-    // to back: one exposed LDS latency per chunk instead of one per MFMA; a fragment serves
-    // the wave's R weight tiles
-    auto multiply = [&](const uint4* w, int buf) {
-        const bf16_t* xb = xs + (size_t)buf * ROWS * LDW + wk * KW + lh * 8;
-        bf16x8 xf[KSTEPS][MT];
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) xf[ks][mt] = *(const bf16x8*)(xb + (size_t)(mt * 32 + lm) * LDW + ks * 16);
+    auto after = [&](int at) SSD_INLINE { return at + 1 == nchunks ? 0 : at + 1; };
+    constexpr int PER = PMIN + (PMORE ? 1 : 0);
+    // step q behind the barrier: its share of the loads, then its MFMAs
+    auto step = [&](auto qc, const Frags& f, int slot, bool load) SSD_INLINE {
+        constexpr int q = decltype(qc)::value;
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks)
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const uint4 wv = w[r * KSTEPS + ks];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    if (DBG & 1)
-                        acc[r][mt][0] += __uint_as_float(wv.x ^ wv.w) + __uint_as_float(((const uint4*)&xf[ks][mt])->x);
-                    else
-                        acc[r][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)&wv, xf[ks][mt], acc[r][mt], 0, 0, 0);
-                }
-            }
+        if (load)
+            static_for<q * PER / 4, (q + 1) * PER / 4>([&](auto ic) SSD_INLINE { issue(decltype(ic)::value, slot); });
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f);
+        __builtin_amdgcn_sched_barrier(0);
     };
-
-    // Chunk c is multiplied in iteration c from LDS stage c % 3.  Its activations were written
-    // to LDS in iteration c-2, before that iteration's MFMAs, so the write -> barrier -> read
-    // chain of a chunk overlaps the arithmetic of the two chunks before it instead of sitting
-    // between them.  A stage is rewritten in the iteration after its last read; the barrier
-    // that ends every iteration separates the two.
-    static_for<0, PX>([&](auto ic) { constexpr int u = decltype(ic)::value; issue_x(SSD_XSLOT(u), u); });
-    static_for<0, DW - 1>([&](auto ic) { constexpr int u = decltype(ic)::value; issue_w(SSD_WSLOT(u), u); });
-    stage_x(x0, 0);
-    stage_x(x1, 1);
-    __syncthreads();
-    if constexpr (NCH > 0) {
-        static_for<0, NCH>([&](auto ic) {
-            constexpr int c = decltype(ic)::value;
-            if constexpr (c + 2 < NCH) stage_x(SSD_XSLOT(c + 2), (c + 2) % NST);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (c + PX < NCH) issue_x(SSD_XSLOT(c + PX), c + PX);
-            if constexpr (c + DW - 1 < NCH) issue_w(SSD_WSLOT(c + DW - 1), c + DW - 1);
-            multiply(SSD_WSLOT(c), c % NST);
-            __syncthreads();
-        });
-    } else {
-        constexpr int UN = 12;                          // ring and stage slots repeat with this period
-        static_assert(UN % DW == 0 && UN % PX == 0 && UN % NST == 0, "unroll period");
-        for (int c0 = 0; c0 < nchunks; c0 += UN) {
-            static_for<0, UN>([&](auto ic) {
-                constexpr int u = decltype(ic)::value;
-                const int c = c0 + u;
-                if (c < nchunks) {
-                    stage_x(SSD_XSLOT(u + 2), (u + 2) % NST);
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue_x(SSD_XSLOT(u + PX), c + PX);
-                    issue_w(SSD_WSLOT(u + DW - 1), c + DW - 1);
-                    multiply(SSD_WSLOT(u), u % NST);
-                    __syncthreads();
-                }
-            });
+    int slot = 0;
+    // three steps of a chunk, whose first fragments are on their way
+    auto three_steps = [&](int prev, bool load) SSD_INLINE {
+        read(fb, slot, 1);
+        step(std::integral_constant<int, 1>{}, fa, prev, load);
+        read(fa, slot, 2);
+        step(std::integral_constant<int, 2>{}, fb, prev, load);
+        read(fb, slot, 3);
+        step(std::integral_constant<int, 3>{}, fa, prev, load);
+    };
+    // from the barrier in front of a chunk on: the last step of the chunk before, whose stage is free, and three of its own
+    auto period = [&](bool load) SSD_INLINE {
+        const int prev = slot;
+        slot = slot + 1 == NST ? 0 : slot + 1;
+        read(fa, slot, 0);
+        step(std::integral_constant<int, 0>{}, fb, prev, load);
+        three_steps(prev, load);
+        at = after(at);
+    };
+#pragma unroll
+    for (int u = 0; u < NST; ++u)
+        if (u < nchunks) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) issue(i, u);
+            at = after(at);
         }
+    // the oldest chunk on its way has landed, B behind it may be outstanding
+    auto landed = [&](auto bc) SSD_INLINE {
+        constexpr int B = decltype(bc)::value;
+        if (PMORE && wave < PMORE) wait_and_meet<(PMIN + 1) * B>();
+        else wait_and_meet<PMIN * B>();
+    };
+    if (nchunks >= NST) landed(std::integral_constant<int, NST - 1>{});
+    else landed(std::integral_constant<int, 0>{});
+    read(fa, 0, 0);
+    three_steps(0, false);
+    int c = 1;
+    for (; c - 1 + NST < nchunks; ++c) {
+        landed(std::integral_constant<int, NST - 2>{});
+        period(true);
     }
-#undef SSD_WSLOT
-#undef SSD_XSLOT
-    if (DBG & 4) {
-        float sum = 0.f;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum += acc[r][mt][i];
-        if (sum == 1.2345f) *(float*)outv = sum;
-        return;
+    for (; c < nchunks; ++c) {
+        landed(std::integral_constant<int, 0>{});
+        period(false);
     }
+    step(std::integral_constant<int, 0>{}, fb, 0, false);
+    __syncthreads();                                     // the epilogue reuses the ring
 
     // ---- epilogues.  Lane (lm, lh) holds, per tile, rows n = 8*(i/4) + 4*lh + i%4 of column m = lm;
     // g = i/4 selects a group of four consecutive n.
-    if constexpr (WK == 2 && R == 1 && EPI == EPI_F32) {
-        // The two k-slice waves of an n-tile share the output: wave wk keeps groups 2wk, 2wk+1 and
-        // hands the other two to its partner through LDS, so both waves add and store (k-slice 0
-        // plus k-slice 1, the order of the sequential reduction).
-        float4* ex = (float4*)smem_u4;                  // [WN][sender wk][MT][2][64]
-        static_for<0, 2>([&](auto iw) {
-            constexpr int w = decltype(iw)::value;
-            if (wk == w) {
+    if constexpr (EPI == EPI_F32) {
+        // through LDS into row order (every wave has read its last fragments: an area of 4 KB per wave and parity of the
+        // row tile), so that a store covers whole 128-byte lines of 8 rows; piece s of row r lies in slot s ^ (r % 8)
+        float* out = (float*)outv + (size_t)bz * split_stride + (size_t)nt * 32 + (lane & 7) * 4;
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+        for (int i = 0; i < TW; ++i) {
+            if (i == TW - 1 && !full) continue;
+            const int mt = wm + WM * i;
+            float4* t = (float4*)smem_u4 + (wave * 2 + (i & 1)) * 256;
+            wave_lds_order();                            // every lane has read what is overwritten next
 #pragma unroll
-                    for (int gq = 0; gq < 2; ++gq) {
-                        constexpr int gbase = (1 - w) * 2;
-                        const int g = gbase + gq;
-                        ex[(((wn * 2 + w) * MT + mt) * 2 + gq) * 64 + lane] =
-                            make_float4(acc[0][mt][g * 4], acc[0][mt][g * 4 + 1], acc[0][mt][g * 4 + 2], acc[0][mt][g * 4 + 3]);
-                    }
+            for (int g = 0; g < 4; ++g)
+                t[lm * 8 + ((g * 2 + lh) ^ (lm & 7))] = make_float4(acc[i][g * 4], acc[i][g * 4 + 1], acc[i][g * 4 + 2], acc[i][g * 4 + 3]);
+            wave_lds_order();                            // other lanes wrote what is read next
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int r = g * 8 + (lane >> 3), m = m0 + mt * 32 + r;
+                const float4 o = t[r * 8 + ((lane & 7) ^ (r & 7))];
+                if (nt_ok && m < M) *(float4*)(out + (size_t)m * N) = o;
             }
-        });
-        __syncthreads();
-        float* out = (float*)outv + (size_t)bz * split_stride;
-        static_for<0, 2>([&](auto iw) {
-            constexpr int w = decltype(iw)::value;
-            if (wk == w && nt_ok[0]) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    // the partner's sums of this row tile, then the finished ones on their way into row order (this wave
-                    // alone reads the area by now): a store covers 64 bytes of 16 rows instead of 32 bytes of 32, which
-                    // halves the L2's write requests (160 rows of the 8B shape: QKV 29.4 -> 28.5 us, down 28.5 -> 27.5);
-                    // piece s of row r lies in slot s ^ (r / 2 % 4)
-                    float4* t = ex + ((wn * 2 + (1 - w)) * MT + mt) * 128;
-                    float4 v[2];
-#pragma unroll
-                    for (int gq = 0; gq < 2; ++gq) {
-                        constexpr int gbase = w * 2;
-                        const int g = gbase + gq;
-                        const float4 o = t[gq * 64 + lane];
-                        v[gq] = make_float4(acc[0][mt][g * 4] + o.x, acc[0][mt][g * 4 + 1] + o.y,
-                                            acc[0][mt][g * 4 + 2] + o.z, acc[0][mt][g * 4 + 3] + o.w);
-                    }
-                    wave_lds_order();                        // every lane has read what is overwritten next
-#pragma unroll
-                    for (int gq = 0; gq < 2; ++gq) t[lm * 4 + ((gq * 2 + lh) ^ ((lm >> 1) & 3))] = v[gq];
-                    wave_lds_order();                        // other lanes wrote what is read next
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int r = h * 16 + (lane >> 2), m = m0 + mt * 32 + r;
-                        const float4 o = t[r * 4 + ((lane & 3) ^ ((r >> 1) & 3))];
-                        if (m < M) *(float4*)(out + (size_t)m * N + nt[0] * 32 + w * 16 + (lane & 3) * 4) = o;
-                    }
-                }
-            }
-        });
-        return;
-    }
-    if constexpr (WK == 2 && R == 1 && EPI == EPI_SWIGLU) {
+        }
+    } else if constexpr (EPI == EPI_SWIGLU) {
         // A tile holds 16 channels: rows 0..15 gate, rows 16..31 up, so groups g and g + 2 of a lane are
-        // gate and up of the same four channels.  Wave wk finishes g = wk and receives the other
-        // k-slice's values of groups wk and wk + 2 through LDS (k-slice 0 plus k-slice 1).
-        float4* ex = (float4*)smem_u4;                  // [WN][sender wk][MT][gate, up][64]
-        static_for<0, 2>([&](auto iw) {
-            constexpr int w = decltype(iw)::value;
-            if (wk == w) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        constexpr int gother = 1 - w;
-                        const int g = gother + 2 * h;
-                        ex[(((wn * 2 + w) * MT + mt) * 2 + h) * 64 + lane] =
-                            make_float4(acc[0][mt][g * 4], acc[0][mt][g * 4 + 1], acc[0][mt][g * 4 + 2], acc[0][mt][g * 4 + 3]);
-                    }
-            }
-        });
-        __syncthreads();
+        // gate and up of the same four channels.
         bf16_t* out = (bf16_t*)outv;
-        const int F = N >> 1;                           // output channels = row stride of the output
-        static_for<0, 2>([&](auto iw) {
-            constexpr int w = decltype(iw)::value;
-            if (wk == w && nt_ok[0]) {
+        const int F = N >> 1;                            // output channels = row stride of the output
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const float4 og = ex[(((wn * 2 + (1 - w)) * MT + mt) * 2 + 0) * 64 + lane];
-                    const float4 ou = ex[(((wn * 2 + (1 - w)) * MT + mt) * 2 + 1) * 64 + lane];
-                    const float gv[4] = {acc[0][mt][w * 4] + og.x, acc[0][mt][w * 4 + 1] + og.y,
-                                         acc[0][mt][w * 4 + 2] + og.z, acc[0][mt][w * 4 + 3] + og.w};
-                    const float uv[4] = {acc[0][mt][(w + 2) * 4] + ou.x, acc[0][mt][(w + 2) * 4 + 1] + ou.y,
-                                         acc[0][mt][(w + 2) * 4 + 2] + ou.z, acc[0][mt][(w + 2) * 4 + 3] + ou.w};
-                    uint16_t o[4];
+        for (int i = 0; i < TW; ++i) {
+            if (i == TW - 1 && !full) continue;
+            const int mt = wm + WM * i;
+            const int m = m0 + mt * 32 + lm;
+            if (!nt_ok || m >= M) continue;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) o[j] = swiglu_bf16(gv[j], uv[j]);
-                    const int m = m0 + mt * 32 + lm;
-                    const int f = nt[0] * 16 + w * 8 + lh * 4;
-                    if (m < M)
-                        *(uint2*)(out + (size_t)m * F + f) =
-                            make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
-                }
-            }
-        });
-        return;
-    }
-
-    // ---- reduce the WK k-slices of the work-group through LDS, in order wk = 1, 2, ...
-    const bool lead = wk == 0;
-    if (WK > 1) {
-        float* red = (float*)smem_u4;                   // [(WK-1)][WN][R*MT*16][64]
-        constexpr int VALS = R * MT * 16;
-        if (!lead) {
-            float* dst = red + ((size_t)((wk - 1) * WN + wn) * VALS) * 64 + lane;
+            for (int g = 0; g < 2; ++g) {
+                float o[4];
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) dst[((r * MT + mt) * 16 + i) * 64] = acc[r][mt][i];
-        }
-        __syncthreads();
-        if (lead) {
-#pragma unroll
-            for (int w2 = 1; w2 < WK; ++w2) {
-                const float* src = red + ((size_t)((w2 - 1) * WN + wn) * VALS) * 64 + lane;
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) acc[r][mt][i] += src[((r * MT + mt) * 16 + i) * 64];
+                for (int j = 0; j < 4; ++j) o[j] = swiglu(acc[i][g * 4 + j], acc[i][(g + 2) * 4 + j]);
+                *(uint2*)(out + (size_t)m * F + nt * 16 + g * 8 + lh * 4) = make_uint2(bf16_pair(o[0], o[1]), bf16_pair(o[2], o[3]));
             }
         }
-    }
-
-    // ---- epilogues.  Lane (lm, lh) holds, per tile, rows n = 8*(i/4) + 4*lh + i%4 of column m = lm.
-    if (EPI == EPI_F32) {
-        float* out = (float*)outv + (size_t)bz * split_stride;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!lead || !nt_ok[r]) continue;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int m = m0 + mt * 32 + lm;
-                if (m >= M) continue;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int n = nt[r] * 32 + g * 8 + lh * 4;
-                    *(float4*)(out + (size_t)m * N + n) =
-                        make_float4(acc[r][mt][g * 4], acc[r][mt][g * 4 + 1], acc[r][mt][g * 4 + 2], acc[r][mt][g * 4 + 3]);
-                }
-            }
-        }
-    } else if (lead) {
+    } else {
         // LM head: per (row, n-tile) partial over the tile's 32 vocabulary rows
         float* out = (float*)outv;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int tile_out = (bx * WN + wn) * R + r;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                float p[3];
-                lm_tile_partial(acc[r][mt], nt[r], lh, mask_id, p);
-                const int m = m0 + mt * 32 + lm;
-                if (lh == 0 && m < M && tile_out < n_tiles_out && nt_ok[r]) {
-                    float* o = out + ((size_t)m * n_tiles_out + tile_out) * 3;
-                    o[0] = p[0];
-                    o[1] = p[1];
-                    o[2] = p[2];
-                }
+        for (int i = 0; i < TW; ++i) {
+            if (i == TW - 1 && !full) continue;
+            const int mt = wm + WM * i;
+            float p[3];
+            lm_tile_partial(acc[i], nt, lh, mask_id, p);
+            const int m = m0 + mt * 32 + lm;
+            if (lh == 0 && m < M && nt_ok) {
+                float* o = out + ((size_t)m * n_tiles_out + nt) * 3;
+                o[0] = p[0];
+                o[1] = p[1];
+                o[2] = p[2];
             }
         }
     }
@@ -489,7 +344,6 @@ __global__ __launch_bounds__(WN* WK * 64) void k_gemm_mfma(const bf16_t* X, cons
 
 // the launchers of the work-group shapes, one translation unit each (they compile in parallel)
 struct GemmArgs {
-    int nch;
     const bf16_t* X;
     const uint4* Wp;
     void* out;
@@ -500,27 +354,28 @@ struct GemmArgs {
     hipStream_t st;
 };
 
-template <int WN, int WK, int R, int MT, int EPI, int NCH, bool CACHED>
+template <int WN, int MT, int EPI, bool CACHED, int NST = 4>
 static bool launch_one(const GemmArgs& a) {
-    constexpr int KC = WK * 32, ROWS = MT * 32, LDW = KC + 8;
-    constexpr size_t xbytes = (size_t)3 * ROWS * LDW * 2 + (size_t)WN * WK * 64 * 16;   // three stages + spare slots
-    // epilogue exchange areas: see the kernel's epilogues
-    constexpr size_t rbytes = (WK == 2 && R == 1 && EPI != EPI_LMHEAD) ? (size_t)WN * 2 * MT * 2 * 1024
-                              : WK > 1 ? (size_t)(WK - 1) * WN * R * MT * 16 * 64 * 4
-                                       : (size_t)(WN / 2 + 1) * MT * 16 * 64 * 4;
-    constexpr size_t smem = xbytes > rbytes ? xbytes : rbytes;
+    constexpr int WM = MT > 1 ? 2 : 1;
+    constexpr size_t stage = (size_t)(WN + MT) * 4096;
+    // four stages; a grid of several rounds over the chip (the LM head) takes as many as leave room for a second work-group on
+    // the CU (8B, 160 rows 213.5 -> 211.2 us, 40 rows 162 -> 160; 250 work-groups, 1600 wide, 96 rows: 24.5 with four, 27.3 so)
+    constexpr int fit = (int)(80 * 1024 / stage), PAIR = fit > 4 ? 4 : fit < 2 ? 2 : fit;
+    if constexpr (EPI == EPI_LMHEAD && NST == 4 && PAIR < 4)
+        if ((a.N / 32 + WN - 1) / WN * a.pass.passes * a.split > 256) return launch_one<WN, MT, EPI, CACHED, PAIR>(a);
+    constexpr size_t rbytes = EPI == EPI_F32 ? (size_t)WN * WM * 2 * 4096 : 0;          // the epilogue's row-order areas
+    constexpr size_t smem = NST * stage > rbytes ? NST * stage : rbytes;
     static_assert(smem <= 160 * 1024, "LDS budget");
-    auto kern = k_gemm_mfma<WN, WK, R, MT, EPI, NCH, CACHED>;
+    auto kern = k_gemm_mfma<WN, WM, MT, EPI, CACHED, NST>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
             return false;
         attr_done = true;
     }
-    const int tiles = a.N / 32, per_wg = WN * R;
-    const int n_blocks = (tiles + per_wg - 1) / per_wg;
+    const int n_blocks = (a.N / 32 + WN - 1) / WN;
     dim3 grid(n_blocks * a.pass.passes * a.split);
-    hipLaunchKernelGGL(kern, grid, dim3(WN * WK * 64), smem, a.st, a.X, a.Wp, a.out, a.M, a.N, a.K, a.K, a.K / a.split,
+    hipLaunchKernelGGL(kern, grid, dim3(WN * WM * 64), smem, a.st, a.X, a.Wp, a.out, a.M, a.N, a.K, a.K / a.split,
                        a.split_stride, a.mask_id, a.n_tiles_out, n_blocks, a.split, a.pass.passes);
     return true;
 }
@@ -528,26 +383,22 @@ static bool launch_one(const GemmArgs& a) {
 // Row tiles of 32 rows per pass: 1 (a stepwise forward of one block) to 6; other row counts round up
 // (padding rows are zero and never stored).  The rows of a pass share nothing but the weight fragments,
 // so a row's sums do not depend on the tile it is computed in.
-template <int WN, int WK, int R, int EPI, int NCH, bool CACHED>
+template <int WN, int EPI, bool CACHED>
 static bool launch_mt(const GemmArgs& a) {
     switch (a.pass.mt) {
-        case 1: return launch_one<WN, WK, R, 1, EPI, NCH, CACHED>(a);
-        case 2: return launch_one<WN, WK, R, 2, EPI, NCH, CACHED>(a);
-        case 3: return launch_one<WN, WK, R, 3, EPI, NCH, CACHED>(a);
-        case 4: return launch_one<WN, WK, R, 4, EPI, NCH, CACHED>(a);
-        case 5: return launch_one<WN, WK, R, 5, EPI, NCH, CACHED>(a);
-        case 6: return launch_one<WN, WK, R, 6, EPI, NCH, CACHED>(a);
+        case 1: return launch_one<WN, 1, EPI, CACHED>(a);
+        case 2: return launch_one<WN, 2, EPI, CACHED>(a);
+        case 3: return launch_one<WN, 3, EPI, CACHED>(a);
+        case 4: return launch_one<WN, 4, EPI, CACHED>(a);
+        case 5: return launch_one<WN, 5, EPI, CACHED>(a);
+        case 6: return launch_one<WN, 6, EPI, CACHED>(a);
     }
     return false;
 }
 
-// One chunk count per work-group shape runs as straight-line code (NCH = the 8B-class shape's chunk
-// count for that projection); every other chunk count takes the looped kernel (NCH = 0).
-template <int WN, int WK, int EPI, int NCH>
+template <int WN, int EPI>
 static bool launch_shape(const GemmArgs& a) {
-    if (NCH > 0 && a.nch == NCH)
-        return a.pass.cached ? launch_mt<WN, WK, 1, EPI, NCH, true>(a) : launch_mt<WN, WK, 1, EPI, NCH, false>(a);
-    return a.pass.cached ? launch_mt<WN, WK, 1, EPI, 0, true>(a) : launch_mt<WN, WK, 1, EPI, 0, false>(a);
+    return a.pass.cached ? launch_mt<WN, EPI, true>(a) : launch_mt<WN, EPI, false>(a);
 }
 
 bool gemm_f32_wn3(const GemmArgs& a);     // wide outputs (QKV): 96-row n-blocks
@@ -556,10 +407,10 @@ bool gemm_f32_wn4(const GemmArgs& a);     // narrow outputs, long K (down) and e
 bool gemm_swiglu_wn3(const GemmArgs& a);
 bool gemm_swiglu_wn4(const GemmArgs& a);
 bool gemm_lmhead_wn4(const GemmArgs& a);
-// the kernel for many rows (gemm_rows.h): mt row tiles of 32 rows per work-group, as gemm_rows_tile() says
-bool gemm_rows_f32(const GemmArgs& a, int mt);
-bool gemm_rows_swiglu(const GemmArgs& a, int mt);
-bool gemm_rows_lmhead(const GemmArgs& a, int mt);
+// the kernel for many rows (gemm_rows.h) with the tile that gemm_wide_tile() or gemm_rows_tile() says
+bool gemm_rows_f32(const GemmArgs& a, int tile);
+bool gemm_rows_swiglu(const GemmArgs& a, int tile);
+bool gemm_rows_lmhead(const GemmArgs& a, int tile);
 
 // Split along K across work-groups: a function of the weight shape only.
 static int pick_split(int K, int kc, int want) {

@@ -10,23 +10,52 @@ inline int gemm_full_pass(int M) {
     return tiles <= 6 ? tiles : (M + 191) / 192 < (M + 159) / 160 ? 6 : 5;
 }
 
-// Row tiles (of 32 rows) per work-group of k_gemm_rows, or 0: the few-row kernel takes the call, in n-blocks of wn tiles.
+// The large tiles of k_gemm_rows, weight rows x activation rows.  The small ones, 256 x 96, 128 and 160, are named by their
+// 3, 4 or 5 row tiles of 32.
+enum GemmWideTile { GEMM_256x256 = 256256, GEMM_192x320 = 192320, GEMM_192x256 = 192256 };
+
+// One of the large tiles where it is the fastest way for M rows, or 0: gemm_rows_tile() and gemm_few_row_pass() choose.
+// nch: chunks of 64 columns in a k-slice; wn: as below.
+// Time of a launch = rounds over the 256 CUs x (fixed + chunks x a) + share of the chip's work-group slots x chunks x b, since
+// a round that fills the chip only partly draws less power and clocks higher.  Fitted, ns, to gate/up of the 8B shape at 193
+// to 2304 rows (64 chunks; one round of half the chip / of the whole chip, two rounds of it, us: 192 x 256 68 / 86, 171;
+// 192 x 320 77 / 100, 195; 256 x 256 at 192 work-groups 89, at 512 and 768 - / - , 184 / 318).  Over the four matrices of the 8B and
+// the 7B class and the LM head, 193 to 2304 rows, the choice was within 4 % of the fastest tile but for 8 % at down, 256 rows.
+// At least 128 work-groups: fewer leave half of the chip idle, and the few-row kernel's narrower n-blocks spread better.
+inline int gemm_wide_tile(int M, int N, int nch, int split, int wn) {
+    if (M <= 192) return 0;
+    struct Kind { int code, nt, mt, a, b; };
+    static const Kind kinds[6] = {{GEMM_256x256, 8, 8, 840, 620}, {GEMM_192x320, 6, 10, 656, 750}, {GEMM_192x256, 6, 8, 625, 560},
+                                  {0, 8, 4, 560, 250}, {0, 8, 5, 690, 230}, {0, 8, 3, 470, 190}};
+    const long long fixed = 10000;
+    int best = 0;
+    long long best_time = -1;
+    for (const Kind& k : kinds) {
+        const long long wgs = (long long)((N / 32 + k.nt - 1) / k.nt) * split * ((M + k.mt * 32 - 1) / (k.mt * 32));
+        const long long t = (wgs + 255) / 256 * (fixed + (long long)nch * k.a) + wgs * nch * k.b / 256;
+        if (wgs >= 128 && (best_time < 0 || t < best_time)) { best = k.code; best_time = t; }
+    }
+    // the few-row kernel's passes of 160 or 192 rows
+    const int mt = gemm_full_pass(M);
+    const long long wgs = (long long)((N / 32 + wn - 1) / wn) * split * ((M + mt * 32 - 1) / (mt * 32));
+    if (wgs >= 256 && (wgs + 255) / 256 * (4000 + (long long)nch * (mt == 6 ? 630 : 560)) * wn / 3 < best_time) return 0;
+    return best;
+}
+
+// Row tiles (of 32 rows) per work-group of k_gemm_rows with 256 weight rows, or 0: the few-row kernel takes the call, in
+// n-blocks of wn tiles.  Asked where no large tile is the fastest.
 // Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of them;
-// beyond that it re-streams them per pass (gate/up of the 8B shape, us, few-row against k_gemm_rows: 200 rows 83 / 60,
-// 576 rows 150 / 117, 1000 rows 283 / 183).  Fewer than 128 work-groups leave half of the chip idle: then the
+// beyond that it re-streams them per pass (8B shape, 193 rows, us, few-row / 128 rows: gate/up 80 / 57, QKV 46 / 33, down 40 /
+// 33).  Fewer than 128 work-groups leave half of the chip idle: then the
 // few-row kernel's narrower n-blocks spread better.  Among the tiles the fewest rounds over the 256 CUs win, a
-// round of 96, 128 or 160 rows costing 0.78 : 1 : 1.3 (measured at 640 and 1000 rows: 47, 59 and 78 us a
-// round; the 160-row tile has registers for one weight chunk in flight only, the others for three).
+// round of 96, 128 or 160 rows costing 0.84 : 1 : 1.11 (gate/up at 256 to 640 rows: 48, 57 and 65 us a round).
 // The few-row kernel's 96-row n-blocks, where they fill the chip, count along: a round of 160 or 192 rows costs 0.65 or
-// 0.75 there.  That keeps it for 321 to 384 rows of the 8B shape: QKV 63.5 - 65.2 us (k_gemm_rows 65.9 - 69.4), gate/up
-// 97.6 - 103.8 (99.1 - 105.9), sixteen layers and the LM head at 352 rows 4.46 ms (4.70), at 384 rows 4.57 (4.84).
-// Its 128- and 64-row n-blocks are no faster there (down 59.7 - 62.6 / 58.8 - 62.4, attention output 34.5 - 35.8 /
-// 24.4 - 26.8).
-// X, the activations, must start on 16 bytes (their rows then do: K is a multiple of 64): k_gemm_rows copies them to LDS in
-// 16-byte pieces.  The kernel-level entry points take any pointer; the few-row kernel reads others as it always did.
+// 0.75 there (320 and 384 rows in two passes: 82 and 89 us).
+// X, the activations, must start on 16 bytes (their rows then do: K is a multiple of 64): the kernels copy them to LDS in
+// 16-byte pieces (launch_gemm_mfma sees to it that they do).
 inline int gemm_rows_tile(const void* X, int M, int N, int split, int wn) {
     if (M <= 192 || ((uintptr_t)X & 15)) return 0;
-    const int n_blocks = (N / 32 + 7) / 8, cost[3] = {78, 100, 130};
+    const int n_blocks = (N / 32 + 7) / 8, cost[3] = {84, 100, 111};
     int best = 0, best_cost = 0;
     for (int mt = 3; mt <= 5; ++mt) {
         const long long wgs = (long long)n_blocks * split * ((M + mt * 32 - 1) / (mt * 32));

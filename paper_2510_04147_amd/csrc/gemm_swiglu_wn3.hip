@@ -1,5 +1,5 @@
-// gate/up projection with the SwiGLU epilogue, 96-row n-blocks: 64 chunks at d_model 4096
+// gate/up projection with the SwiGLU epilogue, 96-row n-blocks
 // (one instantiation unit of the MFMA GEMM template; see kernels_mfma.hip for the design)
 #include "gemm_mfma.h"
 
-bool gemm_swiglu_wn3(const GemmArgs& a) { return launch_shape<3, 2, EPI_SWIGLU, 64>(a); }
+bool gemm_swiglu_wn3(const GemmArgs& a) { return launch_shape<3, EPI_SWIGLU>(a); }

@@ -2,4 +2,4 @@
 // (one instantiation unit of the MFMA GEMM template; see kernels_mfma.hip for the design)
 #include "gemm_mfma.h"
 
-bool gemm_swiglu_wn4(const GemmArgs& a) { return launch_shape<4, 2, EPI_SWIGLU, 0>(a); }
+bool gemm_swiglu_wn4(const GemmArgs& a) { return launch_shape<4, EPI_SWIGLU>(a); }

@@ -6,8 +6,7 @@
 //   * weights are repacked once, at context creation, into MFMA fragment
 //     order: fragment (nt, ks) = rows [32nt, 32nt+32) x columns [16ks, 16ks+16)
 //     is one contiguous 1 KiB block laid out lane by lane, so a wave's load
-//     instruction reads 1 KiB of consecutive bytes and a wave streams a
-//     contiguous region straight into registers (no LDS round trip), with
+//     instruction copies 1 KiB of consecutive bytes to LDS as they are, with
 //     non-temporal loads where one pass takes all rows, so that the stream does
 //     not evict the activations from L2; the gate/up matrix interleaves gate and
 //     up rows per 16 channels, which makes SwiGLU lane-local;
@@ -15,13 +14,12 @@
 //     activations are the B operand, so each lane ends up with 4 consecutive
 //     output columns of one row: vector stores, lane-local SwiGLU and LM-head
 //     reductions;
-//   * activations are staged through LDS in K chunks (a three-stage ring),
-//     shared by all waves of the work-group;
+//   * weights and activations go to LDS in K chunks without passing through registers,
+//     into a ring of four stages shared by all waves of the work-group;
 //   * grids aim at one work-group per CU (256) and are XCD-aware: with split-K
 //     the work-groups of one XCD read the same k-slice of the activations;
-//   * K can be split inside a work-group (waves reduce through LDS) and across
-//     work-groups (partial sums to a workspace, summed in a fixed order by the
-//     consumer).  Both splits depend on the weight shape only, never on M, and
+//   * K can be split across work-groups (partial sums to a workspace, summed in a fixed order by the
+//     consumer), which depends on the weight shape only, never on M, and
 //     a row's arithmetic never involves another row: a row is bit-identical in
 //     a 1-node and an (N+1)-node forward.
 // Forwards with more rows take k_gemm_rows (gemm_rows.h), which computes the same sums in the same order.
@@ -61,17 +59,25 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
                       hipStream_t st) {
     if (!W.packed) return false;
     const int N = W.N, K = W.K;
-    constexpr int WK = 2, KC = WK * 32;
+    constexpr int KC = 64;
     if (K % KC) return false;
+    if ((uintptr_t)X & 15) {
+        // the kernels copy rows to LDS in 16-byte pieces; only the kernel-level entry points see other pointers
+        const Dims& d = c->dm;
+        void* to = K <= d.d ? c->b.xn : K <= d.nq() ? c->b.attn : c->b.act;
+        if (hipMemcpyAsync(to, X, (size_t)M * K * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return false;
+        X = to;
+    }
     const bf16_t* x = (const bf16_t*)X;
     const uint4* wp = (const uint4*)W.packed;
-    GemmArgs a{K / KC, x, wp, out, M, N, K, 1, 0, -1, 0, {}, st};
+    GemmArgs a{x, wp, out, M, N, K, 1, 0, -1, 0, {}, st};
     if (epi == EPI_SWIGLU) {
         // W = [2F, d] packed with gate and up rows interleaved per 16 channels: N/32 tiles of 16
         // channels each, any number of them per work-group; 96-row n-blocks give the 8B shape
         // (768 tiles) exactly one work-group per CU
         *n_split = 1;
         const int wn = (N / 32) % 3 == 0 ? 3 : 4;
+        if (const int t = gemm_wide_tile(M, N, K / KC, 1, wn)) return gemm_rows_swiglu(a, t);
         if (const int rt = gemm_rows_tile(X, M, N, 1, wn)) return gemm_rows_swiglu(a, rt);
         a.pass = gemm_few_row_pass(M, N, 1, wn);
         return wn == 3 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);
@@ -80,6 +86,7 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
         *n_split = lm_tiles_mfma(N);
         a.mask_id = c->dm.mask_id;
         a.n_tiles_out = N / 32;
+        if (const int t = gemm_wide_tile(M, N, K / KC, 1, 4)) return gemm_rows_lmhead(a, t);
         if (const int rt = gemm_rows_tile(X, M, N, 1, 4)) return gemm_rows_lmhead(a, rt);
         a.pass = gemm_few_row_pass(M, N, 1, 4);
         return gemm_lmhead_wn4(a);

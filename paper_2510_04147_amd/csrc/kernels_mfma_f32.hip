@@ -4,7 +4,7 @@
 
 bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, void* out, int M, int N, int K,
                           int* n_split, hipStream_t st) {
-    constexpr int WK = 2, KC = WK * 32;
+    constexpr int KC = 64;
     const size_t stride = (size_t)c->dm.max_rows * (size_t)c->part_cols;
     // Work-group shape and split along K: functions of the weight shape alone, chosen so that the
     // grid comes close to one work-group per CU (256) with at least 16 K chunks each where the
@@ -25,8 +25,8 @@ bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, vo
     if (want > SSD_MAX_SPLIT) want = SSD_MAX_SPLIT;
     const int split = pick_split(K, KC, want);
     *n_split = split;
-    const int nch = K / split / KC;
-    GemmArgs a{nch, x, wp, out, M, N, K, split, stride, -1, 0, {}, st};
+    GemmArgs a{x, wp, out, M, N, K, split, stride, -1, 0, {}, st};
+    if (const int t = gemm_wide_tile(M, N, K / split / KC, split, wn)) return gemm_rows_f32(a, t);
     if (const int rt = gemm_rows_tile(x, M, N, split, wn)) return gemm_rows_f32(a, rt);
     a.pass = gemm_few_row_pass(M, N, split, wn);
     return wn == 3 ? gemm_f32_wn3(a) : wn == 2 ? gemm_f32_wn2(a) : gemm_f32_wn4(a);
