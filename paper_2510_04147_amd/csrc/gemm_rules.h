@@ -93,13 +93,18 @@ inline GemmPass gemm_few_row_pass(int M, int N, int split, int wn) {
     return GemmPass{mt, passes, passes > 1};
 }
 
-// Plain GEMM: k_gemm_plain_small takes the call while k_gemm_plain's 64x64 tiles would give a CU at most one work-group
-// (fp32, us, 64x64 tiles / small ones: 12 tiles 51 / 5, 60 tiles 57 / 16, 120 tiles 105 / 35, 165 tiles 68 / 44, 240 tiles
-// 105 / 70; bf16, N = 4096, K = 12288: 64 tiles 1271 / 236, 192 tiles 1300 / 639, 256 tiles 1322 / 978; the small ones
-// read LDS three times as much per FMA).
+// Plain GEMM: k_gemm_plain_small may take the call while k_gemm_plain's 64x64 tiles would give a CU at most one work-group.
 // Unaligned operands (kernel-level entry points take any pointer) stay with the scalar loads.
 #define GEMM_PLAIN_TILE 64
 inline bool gemm_plain_small_tiles(const void* X, const void* W, int M, int N) {
     const long long tiles = (long long)((N + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE) * ((M + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE);
     return tiles <= 256 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0;
+}
+
+// It does for up to 64 rows, and for more rows up to 160 tiles: its 16 rows share nothing, so every 16 rows read the weights
+// again (us, 64x64 tiles / small ones; up to 64 rows: 60 tiles 12.7 / 6.4, 125 tiles 43 / 30, 192 tiles 4096 wide 172 / 106 and 257 /
+// 220; more rows: 120 tiles 13.2 / 11.7, 144 tiles 36 / 32, 160 tiles 54 / 45, 176 tiles 40 / 43, 192 tiles 20 / 25, 256
+// tiles 40 / 60).
+inline bool gemm_plain_small_wins(int M, int N) {
+    return M <= 64 || (long long)((N + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE) * ((M + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE) <= 160;
 }

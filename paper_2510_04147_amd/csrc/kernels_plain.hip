@@ -416,12 +416,31 @@ __global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__
 }
 
 // ------------------------------------------------------------------------
-// Plain tiled GEMM  out[M,N] = X[M,K] * W[N,K]^T, fp32 accumulation in
-// ascending k.  64x64 tile per work-group, 4x4 outputs per thread.
+// Plain GEMM  out[M,N] = X[M,K] * W[N,K]^T  in fp32 (bf16 operands widened), on the fp32 matrix cores.
+// The order of an output's sum, the same in both kernels: the columns in steps of 16, the steps in eight chains of ceil(steps
+// / 8) consecutive ones, a step as four 16x16x4 MFMAs, MFMA i over its columns 4q + i, q = 0 ... 3; the chains are
+// added in order.  A lane's operands of a step's four MFMAs are four consecutive columns of one row: one 16-byte load,
+// straight from memory into the registers that the matrix core reads.  Columns past K (a multiple of 8) count as zeros.
 // ------------------------------------------------------------------------
 #define PBM GEMM_PLAIN_TILE
 #define PBN GEMM_PLAIN_TILE
-#define PBK 16
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// Four consecutive values, or zeros.  VEC: the address is a multiple of four elements.
+template <bool VEC, typename T>
+__device__ __forceinline__ float4 get4(const T* p, bool ok = true) {
+    if (!ok) return make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (VEC) return ld4_f(p);
+    else return make_float4(ld_f(p), ld_f(p + 1), ld_f(p + 2), ld_f(p + 3));
+}
+// One step of one chain: lane (q, j) = (lane / 16, lane % 16) holds columns 4q ... 4q + 3 of weight row j and of row j of X;
+// it ends up with weight rows 4q ... 4q + 3 of row j.
+__device__ __forceinline__ floatx4 mfma_step(const float4& w, const float4& x, floatx4 acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, x.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, x.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, x.z, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, x.w, acc, 0, 0, 0);
+}
 
 // Fused LM-head reduction over 16 adjacent lanes that hold NJ consecutive logits each, from vocabulary row n0 of this
 // lane on: max logit, its lowest index, sum of exp(logit - max).  The mask token takes no part.
@@ -455,160 +474,166 @@ __device__ __forceinline__ void lm_row_partial(const float (&v)[NJ], int n0, int
     }
 }
 
-template <typename T, int EPI>
+// 64x64 tile per work-group, 2x2 waves of 32x32: 2x2 MFMA tiles.  A step's operands are loaded while the step before it is
+// multiplied.  Bound: the caches; every operand is requested by the two waves that need it.  160 rows, K = 12288,
+// N = 4096, us, FMAs through LDS / this: 697 / 462.
+template <typename T, int EPI, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, const T* __restrict__ W,
                                                     void* __restrict__ outv, int M, int N, int K, int up_off,
                                                     int mask_id, int n_tiles) {
-    __shared__ float Xs[PBK][PBM + 4];
-    __shared__ float Ws[PBK][PBN + 4];
-    __shared__ float Us[EPI == EPI_SWIGLU ? PBK : 1][PBN + 4];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * PBM, n0 = blockIdx.x * PBN;
-    const int lr = tid >> 2, lk = (tid & 3) * 4;
-    float acc[4][4] = {}, accu[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += PBK) {
+    constexpr int NU = EPI == EPI_SWIGLU ? 2 : 1;         // gate rows and up rows
+    __shared__ float lg[EPI == EPI_LMHEAD ? PBM : 1][EPI == EPI_LMHEAD ? PBN + 4 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, j = lane & 15;
+    const int m0 = blockIdx.y * PBM + (wave >> 1) * 32, n0 = blockIdx.x * PBN + (wave & 1) * 32;
+    floatx4 acc[NU][2][2], tot[NU][2][2];                 // [gate, up][n-tile][m-tile]: a chain, the chains before it
+    float4 w[2][NU][2], x[2][2];
+    const T *xr[2], *wr[NU][2];                           // rows past the end read the last one (never stored)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int kk = k0 + lk + i;
-            const bool kin = kk < K;
-            Xs[lk + i][lr] = (kin && m0 + lr < M) ? ld_f(X + (size_t)(m0 + lr) * K + kk) : 0.f;
-            Ws[lk + i][lr] = (kin && n0 + lr < N) ? ld_f(W + (size_t)(n0 + lr) * K + kk) : 0.f;
-            if (EPI == EPI_SWIGLU)
-                Us[lk + i][lr] = (kin && n0 + lr < N) ? ld_f(W + (size_t)(up_off + n0 + lr) * K + kk) : 0.f;
-        }
-        __syncthreads();
+    for (int t = 0; t < 2; ++t) {
+        xr[t] = X + (size_t)min(m0 + t * 16 + j, M - 1) * K;
 #pragma unroll
-        for (int kk = 0; kk < PBK; ++kk) {
-            float a[4], b[4], u[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = Xs[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Ws[kk][tx * 4 + j];
-            if (EPI == EPI_SWIGLU) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) u[j] = Us[kk][tx * 4 + j];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc[i][j] += a[i] * b[j];
-                    if (EPI == EPI_SWIGLU) accu[i][j] += a[i] * u[j];
-                }
-        }
-        __syncthreads();
+        for (int u = 0; u < NU; ++u) wr[u][t] = W + (size_t)(u * up_off + min(n0 + t * 16 + j, N - 1)) * K;
     }
-    if (EPI == EPI_F32) {
-        float* out = (float*)outv;
+    auto load = [&](int buf, int s) __attribute__((always_inline)) {
+        const int k = s * 16 + q * 4;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int t = 0; t < 2; ++t) {
+            x[buf][t] = get4<VEC>(xr[t] + k, k < K);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-                if (m < M && n < N) out[(size_t)m * N + n] = acc[i][j];
-            }
-    } else if (EPI == EPI_SWIGLU) {
-        T* out = (T*)outv;
+            for (int u = 0; u < NU; ++u) w[buf][u][t] = get4<VEC>(wr[u][t] + k, k < K);
+        }
+    };
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    const int steps = (K + 15) >> 4, len = (steps + 7) >> 3;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+    for (int u = 0; u < NU; ++u)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-                if (m < M && n < N) {
-                    const float g = acc[i][j];
-                    st_f(out + (size_t)m * N + n, g / (1.0f + expf(-g)) * accu[i][j]);
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[u][a][b] = tot[u][a][b] = zero;
+    auto close = [&]() __attribute__((always_inline)) {   // the end of a chain
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) { tot[u][a][b] += acc[u][a][b]; acc[u][a][b] = zero; }
+    };
+    load(0, 0);
+    int left = len;
+    for (int s0 = 0; s0 < steps; s0 += 2)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (s0 + c >= steps) break;
+            load(c ^ 1, s0 + c + 1);                      // past the end: zeros, unused
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) acc[u][a][b] = mfma_step(w[c][u][a], x[c][b], acc[u][a][b]);
+            if (--left == 0) { close(); left = len; }
+        }
+    close();
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            floatx4 v[NU];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) v[u] = tot[u][a][b];
+            const int m = m0 + b * 16 + j, n = n0 + a * 16 + q * 4;
+            if constexpr (EPI == EPI_LMHEAD) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) lg[(wave >> 1) * 32 + b * 16 + j][(wave & 1) * 32 + a * 16 + q * 4 + i] = v[0][i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (m >= M || n + i >= N) continue;
+                    if constexpr (EPI == EPI_F32) ((float*)outv)[(size_t)m * N + n + i] = v[0][i];
+                    else st_f((T*)outv + (size_t)m * N + n + i, v[0][i] / (1.0f + expf(-v[0][i])) * v[NU - 1][i]);
                 }
             }
-    } else {
+        }
+    if constexpr (EPI == EPI_LMHEAD) {
         // per row, over this tile's 64 vocabulary columns; the 16 threads of a row are 16 adjacent lanes
+        __syncthreads();
         float* out = (float*)outv;
+        const int tx = tid & 15;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int m = m0 + ty * 4 + i;
-            lm_row_partial<4>(acc[i], n0 + tx * 4, N, mask_id, tx == 0 && m < M, out + ((size_t)m * n_tiles + blockIdx.x) * 3);
+            const int r = (tid >> 4) * 4 + i, m = blockIdx.y * PBM + r;
+            const float v[4] = {lg[r][tx * 4], lg[r][tx * 4 + 1], lg[r][tx * 4 + 2], lg[r][tx * 4 + 3]};
+            lm_row_partial<4>(v, blockIdx.x * PBN + tx * 4, N, mask_id, tx == 0 && m < M, out + ((size_t)m * n_tiles + blockIdx.x) * 3);
         }
     }
 }
 
-// The same sums for launches whose 64x64 tiles would leave most of the chip idle (small models, few rows): 8 rows x
-// 16 NJ outputs per work-group of 128 threads, NJ outputs per thread.  An output is still one chain of FMAs in
-// ascending k, and an LM-head partial still covers 64 columns, four consecutive ones per thread: bit for bit the
-// results of k_gemm_plain, so a row does not depend on which of the two computes it.  Bound: the latency of
-// the K walk, so the K chunks are 64 wide, one barrier each, and a chunk's 16-byte loads are in flight while the one
-// before it is multiplied.  Operands must be 16-byte aligned (K is a multiple of 8).
-// Measured, fp32, 32 rows (K x N, us, k_gemm_plain / this): 256 x 768 27 / 5.4, 768 x 256 55 / 8.4, gate/up 256 x 768
-// 53 / 6.4, LM head 256 x 1024 29 / 8.9.
-#define SBM 8
-#define SBK 64
-template <typename T, int EPI, int NJ>
-__global__ __launch_bounds__(128) void k_gemm_plain_small(const T* __restrict__ X, const T* __restrict__ W,
-                                                          void* __restrict__ outv, int M, int N, int K, int up_off,
-                                                          int mask_id, int n_tiles) {
-    constexpr int TN = 16 * NJ, NL = TN / 8, NU = EPI == EPI_SWIGLU ? NL : 1;
-    __shared__ __attribute__((aligned(16))) float Xs[2][SBM][SBK + 4];
-    __shared__ __attribute__((aligned(16))) float Ws[2][TN][SBK + 4];      // column n of the tile in row (n % NJ) * 16 + n / NJ
-    __shared__ __attribute__((aligned(16))) float Us[EPI == EPI_SWIGLU ? 2 : 1][EPI == EPI_SWIGLU ? TN : 1][SBK + 4];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, lk = tx * 4;
-    const int m0 = blockIdx.y * SBM, n0 = blockIdx.x * TN;
-    float4 xv, wv[NL], uv[NU];
-    auto get = [&](const T* base, size_t off, bool ok) {
-        const float4 v = ld4_f(base + (ok ? off : 0));
-        return make_float4(ok ? v.x : 0.f, ok ? v.y : 0.f, ok ? v.z : 0.f, ok ? v.w : 0.f);
-    };
-    auto issue = [&](int k0) {                               // rows, columns and k past the end count as zeros
-        const int kk = k0 + lk;
-        const bool kin = kk < K;
-        xv = get(X, (size_t)(m0 + ty) * K + kk, kin && m0 + ty < M);
+// The same sums for launches whose 64x64 tiles would leave most of the chip idle (small models, few rows): 16 rows x 16
+// outputs per work-group (LM head: 16 x 64, the width of a partial), one wave per chain; gate and up rows, and two halves of the
+// LM head's columns, have waves of their own.  Bound: launch, one trip to memory, a chain's MFMAs; four steps' loads are in
+// flight together (K up to 512 in one trip).  Operands must be 16-byte aligned.
+// Measured, fp32, 32 rows (K x N, us, FMAs of 8x16 tiles through LDS / this): 256 x 768 5.5 / 3.6, 256 and 768 x 256 8.7 / 4.5,
+// gate/up 256 x 768 6.7 / 4.6, LM head 256 x 1024 9.0 / 6.2; four chains instead of eight, twice the steps each: 4.6, 6.1, 6.6, 10.5.
+template <typename T, int EPI>
+__global__ __launch_bounds__(EPI == EPI_F32 ? 512 : 1024) void k_gemm_plain_small(
+    const T* __restrict__ X, const T* __restrict__ W, void* __restrict__ outv, int M, int N, int K, int up_off, int mask_id,
+    int n_tiles) {
+    constexpr int NG = EPI == EPI_F32 ? 1 : EPI == EPI_SWIGLU ? 2 : 4;       // groups of 16 weight rows
+    constexpr int GW = EPI == EPI_LMHEAD ? 2 : 1, TN = EPI == EPI_LMHEAD ? 64 : 16, BATCH = 4;     // groups per wave
+    __shared__ __attribute__((aligned(16))) float part[NG][8][16][20];       // [group][chain][row][16 outputs, padded]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chain = wave & 7, h = wave >> 3, q = lane >> 4, j = lane & 15;
+    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * TN;
+    const int steps = (K + 15) >> 4, len = (steps + 7) >> 3, s0 = chain * len, cnt = min(len, steps - s0);
+    const T* xr = X + (size_t)min(m0 + j, M - 1) * K + s0 * 16 + q * 4;      // rows past the end: the last one, never stored
+    const T* wr[GW];
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int n = n0 + ty + 8 * i;
-            wv[i] = get(W, (size_t)n * K + kk, kin && n < N);
-            if (EPI == EPI_SWIGLU) uv[i % NU] = get(W, (size_t)(up_off + n) * K + kk, kin && n < N);
-        }
-    };
-    auto stage = [&](int buf) {
-        *(float4*)&Xs[buf][ty][lk] = xv;
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int n = ty + 8 * i, r = (n % NJ) * 16 + n / NJ;
-            *(float4*)&Ws[buf][r][lk] = wv[i];
-            if constexpr (EPI == EPI_SWIGLU) *(float4*)&Us[buf][r][lk] = uv[i % NU];
-        }
-    };
-    float acc[NJ] = {}, accu[NJ] = {};
-    issue(0);
-    stage(0);
-    if (SBK < K) issue(SBK);
-    __syncthreads();
-    for (int k0 = 0, buf = 0; k0 < K; k0 += SBK, buf ^= 1) {
-        // the other buffer was last read before the barrier that ended the previous chunk
-        if (k0 + SBK < K) stage(buf ^ 1);
-        if (k0 + 2 * SBK < K) issue(k0 + 2 * SBK);
-#pragma unroll
-        for (int k = 0; k < SBK; k += 4) {
-            const float4 a = *(const float4*)&Xs[buf][ty][k];
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const float4 b = *(const float4*)&Ws[buf][j * 16 + tx][k];
-                acc[j] += a.x * b.x; acc[j] += a.y * b.y; acc[j] += a.z * b.z; acc[j] += a.w * b.w;
-                if constexpr (EPI == EPI_SWIGLU) {
-                    const float4 u = *(const float4*)&Us[buf][j * 16 + tx][k];
-                    accu[j] += a.x * u.x; accu[j] += a.y * u.y; accu[j] += a.z * u.z; accu[j] += a.w * u.w;
-                }
-            }
-        }
-        __syncthreads();
+    for (int g = 0; g < GW; ++g) {
+        const int n = EPI == EPI_SWIGLU ? h * up_off + min(n0 + j, N - 1) : min(n0 + (h * GW + g) * 16 + j, N - 1);
+        wr[g] = W + (size_t)n * K + s0 * 16 + q * 4;
     }
-    const int m = m0 + ty;
-    if constexpr (EPI == EPI_LMHEAD) {
-        lm_row_partial<NJ>(acc, n0 + tx * NJ, N, mask_id, tx == 0 && m < M, (float*)outv + ((size_t)m * n_tiles + blockIdx.x) * 3);
-    } else {
+    const int kleft = K - s0 * 16 - q * 4;                                   // this lane's columns are below K while > 0
+    floatx4 acc[GW];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int n = n0 + tx * NJ + j;
-            if (m >= M || n >= N) continue;
-            if constexpr (EPI == EPI_F32) ((float*)outv)[(size_t)m * N + n] = acc[j];
-            else st_f((T*)outv + (size_t)m * N + n, acc[j] / (1.0f + expf(-acc[j])) * accu[j]);
+    for (int g = 0; g < GW; ++g) acc[g] = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < cnt; s += BATCH) {
+        float4 w[GW][BATCH], x[BATCH];
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i)
+            if (s + i < cnt) {
+                const bool ok = (s + i) * 16 < kleft;
+                x[i] = get4<true>(xr + (s + i) * 16, ok);
+#pragma unroll
+                for (int g = 0; g < GW; ++g) w[g][i] = get4<true>(wr[g] + (s + i) * 16, ok);
+            }
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i)
+            if (s + i < cnt)
+#pragma unroll
+                for (int g = 0; g < GW; ++g) acc[g] = mfma_step(w[g][i], x[i], acc[g]);
+    }
+#pragma unroll
+    for (int g = 0; g < GW; ++g) *(floatx4*)&part[h * GW + g][chain][j][q * 4] = acc[g];
+    __syncthreads();
+    if (tid >= 256) return;
+    const int r = tid >> 4, c = tid & 15, m = m0 + r;
+    auto sum = [&](int g, int col) {
+        float v = 0.f;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) v += part[g][p][r][col];
+        return v;
+    };
+    if constexpr (EPI == EPI_LMHEAD) {
+        const int g = c >> 2, col = (c & 3) * 4;
+        const float v[4] = {sum(g, col), sum(g, col + 1), sum(g, col + 2), sum(g, col + 3)};
+        lm_row_partial<4>(v, n0 + c * 4, N, mask_id, c == 0 && m < M, (float*)outv + ((size_t)m * n_tiles + blockIdx.x) * 3);
+    } else {
+        const int n = n0 + c;
+        if (m >= M || n >= N) return;
+        if constexpr (EPI == EPI_F32) ((float*)outv)[(size_t)m * N + n] = sum(0, c);
+        else {
+            const float g = sum(0, c);
+            st_f((T*)outv + (size_t)m * N + n, g / (1.0f + expf(-g)) * sum(NG - 1, c));
         }
     }
 }
@@ -970,23 +995,26 @@ void launch_attn_plain(const ssd_ctx* c, int M, int layer, hipStream_t st) {
 template <typename T>
 static void gemm_plain_t(const ssd_ctx* c, int epi, const T* X, const T* W, void* out, int M, int N, int K,
                          hipStream_t st) {
-    dim3 grid((N + PBN - 1) / PBN, (M + PBM - 1) / PBM);
-    if (gemm_plain_small_tiles(X, W, M, N)) {
-        const unsigned gy = (M + SBM - 1) / SBM;
-        if (epi == EPI_F32)
-            k_gemm_plain_small<T, EPI_F32, 1><<<dim3((N + 15) / 16, gy), 128, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
-        else if (epi == EPI_SWIGLU)
-            k_gemm_plain_small<T, EPI_SWIGLU, 1><<<dim3((N + 15) / 16, gy), 128, 0, st>>>(X, W, out, M, N, K, N, -1, 0);
-        else
-            k_gemm_plain_small<T, EPI_LMHEAD, 4><<<dim3(grid.x, gy), 128, 0, st>>>(X, W, out, M, N, K, 0, c->dm.mask_id, (int)grid.x);
+    const unsigned tiles = (N + PBN - 1) / PBN;
+    const int mask = c->dm.mask_id;
+    if (gemm_plain_small_tiles(X, W, M, N) && gemm_plain_small_wins(M, N)) {
+        const unsigned gy = (M + 15) / 16;
+        const dim3 grid((N + 15) / 16, gy);
+        if (epi == EPI_F32) k_gemm_plain_small<T, EPI_F32><<<grid, 512, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
+        else if (epi == EPI_SWIGLU) k_gemm_plain_small<T, EPI_SWIGLU><<<grid, 1024, 0, st>>>(X, W, out, M, N, K, N, -1, 0);
+        else k_gemm_plain_small<T, EPI_LMHEAD><<<dim3(tiles, gy), 1024, 0, st>>>(X, W, out, M, N, K, 0, mask, (int)tiles);
         return;
     }
-    if (epi == EPI_F32)
-        k_gemm_plain<T, EPI_F32><<<grid, 256, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
-    else if (epi == EPI_SWIGLU)
-        k_gemm_plain<T, EPI_SWIGLU><<<grid, 256, 0, st>>>(X, W, out, M, N, K, N, -1, 0);
-    else
-        k_gemm_plain<T, EPI_LMHEAD><<<grid, 256, 0, st>>>(X, W, out, M, N, K, 0, c->dm.mask_id, (int)grid.x);
+    const dim3 grid(tiles, (M + PBM - 1) / PBM);
+    auto run = [&](auto vec) {
+        constexpr bool VEC = decltype(vec)::value;
+        if (epi == EPI_F32) k_gemm_plain<T, EPI_F32, VEC><<<grid, 256, 0, st>>>(X, W, out, M, N, K, 0, -1, 0);
+        else if (epi == EPI_SWIGLU) k_gemm_plain<T, EPI_SWIGLU, VEC><<<grid, 256, 0, st>>>(X, W, out, M, N, K, N, -1, 0);
+        else k_gemm_plain<T, EPI_LMHEAD, VEC><<<grid, 256, 0, st>>>(X, W, out, M, N, K, 0, mask, (int)tiles);
+    };
+    // four elements of a row, which starts at a multiple of eight elements, as one load where the matrices are aligned
+    if ((((uintptr_t)X | (uintptr_t)W) & 15) == 0) run(std::true_type{});
+    else run(std::false_type{});
 }
 
 void launch_gemm_plain(const ssd_ctx* c, int epi, const void* X, const void* W, void* out, int M, int N, int K,
