@@ -32,15 +32,39 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 __device__ __forceinline__ void st_f(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st_f(bf16_t* p, float v) { *p = f2bf(v); }
 
+// Reductions over the wave's 64 lanes, the result in every lane, without the LDS (a shuffle costs a trip through it): within
+// rows of 16 lanes by DPP (pairs, pairs of pairs, mirrored halves), across rows by the swaps of 16 and 32 lanes.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+template <class F>
+__device__ __forceinline__ int wave_reduce(int v, F&& f) {
+    v = f(v, dpp<0xB1>(v));                              // lanes 1 0 3 2
+    v = f(v, dpp<0x4E>(v));                              // lanes 2 3 0 1
+    v = f(v, dpp<0x141>(v));                             // the other four of eight
+    v = f(v, dpp<0x140>(v));                             // the other eight of sixteen
+    const auto r16 = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    v = f((int)r16[0], (int)r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return f((int)r32[0], (int)r32[1]);
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    return __int_as_float(wave_reduce(__float_as_int(v), [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }));
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
+    return __int_as_float(wave_reduce(__float_as_int(v), [](int a, int b) { return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b))); }));
+}
+__device__ __forceinline__ int wave_min(int v) { return wave_reduce(v, [](int a, int b) { return a < b ? a : b; }); }
+__device__ __forceinline__ float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+// How many of the lanes in `set` are ahead of this one: higher value, or equal and lower lane.
+__device__ __forceinline__ int rank_among(float c, unsigned long long set, int lane) {
+    int rank = 0;
+    while (set) {                                        // uniform over the wave
+        const int l = __ffsll(set) - 1;
+        set &= set - 1;
+        const float o = lane_value(c, l);
+        rank += o > c || (o == c && l < lane);
+    }
+    return rank;
 }
 
 // ------------------------------------------------------------------------
@@ -65,12 +89,7 @@ __global__ void k_build_rows(const FwdHeader* __restrict__ fw, SeqState* __restr
         const int lane = threadIdx.x;
         const size_t base = (size_t)nd.seq * max_seq_len + nd.S;
         const float c = lane < nd.blen ? ref_conf[base + lane] : -1.f;
-        int rank = 0;
-        for (int qd = 0; qd < 64; ++qd) {
-            const float cq = __shfl(c, qd, 64);
-            if (qd < nd.blen && (cq > c || (cq == c && qd < lane))) ++rank;
-        }
-        ref_rank = rank;
+        ref_rank = rank_among(c, nd.blen >= 64 ? ~0ull : (1ull << nd.blen) - 1ull, lane);
         if (lane < nd.blen) ref_tok = ref_arg[base + lane];
     }
     for (int p = threadIdx.x; p < nd.blen; p += blockDim.x) {
@@ -638,51 +657,39 @@ __global__ __launch_bounds__(EPI == EPI_F32 ? 512 : 1024) void k_gemm_plain_smal
     }
 }
 
-// Merge the per-tile (max, arg, sumexp) triples of a row in a fixed order:
-// each thread folds tiles tid, tid+256, ... in ascending order, then the 64
-// lanes of a wave are folded by a butterfly and the four waves in order.
-// Ties keep the lowest token id.
-__device__ __forceinline__ void lm_fold(float& m, int& a, float& s, float om, int oa, float os) {
-    if (os == 0.f) return;                 // empty partner
-    if (s == 0.f) { m = om; a = oa; s = os; return; }
-    const float nm = fmaxf(m, om);
-    s = s * expf(m - nm) + os * expf(om - nm);
-    if (om > m || (om == m && oa < a)) a = oa;
-    m = nm;
-}
-
+// Merge the per-tile (max, arg, sumexp) triples of a row: the maximum first, then every tile's sum scaled to it, added in an
+// order that depends on the tile count alone (tile t by thread t mod 256, ascending; the lanes of a wave; the four waves).
+// Ties keep the lowest token id.  Bound by latency: folding pairs of triples lane by lane through LDS took two exponentials
+// and three shuffles a step (us before / now: 1024 tokens, 32 rows 3.9 / 2.5; 2080 tokens, 192 rows 5.0 / 2.6).
 __global__ __launch_bounds__(256) void k_lm_merge(const float* __restrict__ part, int n_tiles,
                                                   float* __restrict__ row_max, int* __restrict__ row_arg,
                                                   float* __restrict__ row_conf, int V, int mask_id) {
-    // One work-group per row.  The fold order (tile t goes to thread t mod 256, then a butterfly
-    // inside each wave, then waves 0..3 in order) depends on the tile count alone.
     __shared__ float sm[4], ss[4];
     __shared__ int sa[4];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float m = -INFINITY, s = 0.f;
+    const float* p = part + (size_t)row * n_tiles * 3;
+    float m = -INFINITY;
+    for (int t = tid; t < n_tiles; t += 256) m = fmaxf(m, p[3 * t]);
+    m = wave_max(m);
+    if (lane == 0) sm[wave] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+    float s = 0.f;
     int a = 0x7fffffff;
     for (int t = tid; t < n_tiles; t += 256) {
-        const float* p = part + ((size_t)row * n_tiles + t) * 3;
-        lm_fold(m, a, s, p[0], __float_as_int(p[1]), p[2]);
+        const float tm = p[3 * t];
+        const int ta = __float_as_int(p[3 * t + 1]);
+        const float ts = p[3 * t + 2];
+        if (tm == m && ta < a) a = ta;
+        if (ts != 0.f) s += ts * expf(tm - m);           // 0: a tile without tokens
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float om = __shfl_xor(m, off, 64), os = __shfl_xor(s, off, 64);
-        const int oa = __shfl_xor(a, off, 64);
-        // fold (lower lane, higher lane) in the same order on both sides
-        if (lane & off) {
-            float tm = om, ts = os;
-            int ta = oa;
-            lm_fold(tm, ta, ts, m, a, s);
-            m = tm; a = ta; s = ts;
-        } else {
-            lm_fold(m, a, s, om, oa, os);
-        }
-    }
-    if (lane == 0) { sm[wave] = m; sa[wave] = a; ss[wave] = s; }
+    s = wave_sum(s);
+    a = wave_min(a);
+    if (lane == 0) { ss[wave] = s; sa[wave] = a; }
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < 4; ++w) lm_fold(m, a, s, sm[w], sa[w], ss[w]);
+        s = ((ss[0] + ss[1]) + ss[2]) + ss[3];
+        a = min(min(sa[0], sa[1]), min(sa[2], sa[3]));
         // Non-finite logits (NaN weights) leave no arg-max: fall back to the lowest valid id and
         // confidence 0 so that every later step stays well defined and in bounds.
         if ((unsigned)a >= (unsigned)V) a = mask_id == 0 ? 1 : 0;
@@ -703,7 +710,11 @@ __global__ __launch_bounds__(256) void k_lm_merge(const float* __restrict__ part
 // masked positions by confidence for the next drafts; commits to the state.
 // With mix-order nodes in the group (Section 5.2) a mismatch whose choice is
 // draft m+2 accepts that draft and ends at the node holding drafts 1..m, m+2.
+// Bound by latency: the confidences and tokens of all nodes come in one trip and wait in LDS, a choice is a reduction without
+// LDS, ranks count over the open positions alone (us, a trip and shuffles per node and 64 shuffles per ranking / this: one
+// node of 32 positions 6.9 / 3.9, two sequences of four nodes 11.1 / 5.2).
 // ------------------------------------------------------------------------
+#define ACCEPT_NODES (2 * SSD_MAX_DRAFT + 1)              // a chain and its mix-order nodes
 __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw, SeqState* __restrict__ state,
                                                const float* __restrict__ row_conf, const int* __restrict__ row_arg,
                                                const float* __restrict__ row_max, StepResult* __restrict__ result,
@@ -731,11 +742,7 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
     auto drafts_from_refresh = [&](int S_blk, int blen_blk, int& dpos, int& dtok) {
         const size_t base = (size_t)g.seq * max_seq_len + S_blk;
         const float cr = lane < blen_blk ? ref_conf[base + lane] : -1.f;
-        int rank = 0;
-        for (int qd = 0; qd < 64; ++qd) {
-            const float cq = __shfl(cr, qd, 64);
-            if (qd < blen_blk && (cq > cr || (cq == cr && qd < lane))) ++rank;
-        }
+        const int rank = rank_among(cr, blen_blk >= 64 ? ~0ull : (1ull << blen_blk) - 1ull, lane);
         __syncthreads();
         if (lane < blen_blk) { sh_pos[rank] = lane; sh_tok[rank] = ref_arg[base + lane]; }
         __syncthreads();
@@ -751,41 +758,61 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
     unsigned long long cur = g.fresh ? (blen >= 64 ? ~0ull : ((1ull << blen) - 1ull)) : s->masked;
     __syncthreads();
 
+    __shared__ float node_conf[ACCEPT_NODES][64];
+    __shared__ int node_arg[ACCEPT_NODES][64];
     if (lane < blen) {
-        for (int j = 0; j < g.n_chain && j <= maxDraft; ++j) {
-            const int row = g.row0 + j * blen + lane;
-            const size_t o = ((size_t)gi * (maxDraft + 1) + j) * blockB + lane;
-            if (out.row_maxlogit) out.row_maxlogit[o] = row_max[row];
-            if (out.row_argmax) out.row_argmax[o] = row_arg[row];
-            if (out.row_conf) out.row_conf[o] = row_conf[row];
+        const int n_nodes = min(g.n_nodes, ACCEPT_NODES);
+        for (int j0 = 0; j0 < n_nodes; j0 += 8) {
+            float cf[8], mx[8];
+            int ar[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = g.row0 + min(j0 + i, n_nodes - 1) * blen + lane;
+                cf[i] = row_conf[row];
+                ar[i] = row_arg[row];
+                mx[i] = row_max[row];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = j0 + i;
+                if (j >= n_nodes) break;
+                node_conf[j][lane] = cf[i];
+                node_arg[j][lane] = ar[i];
+                if (j >= g.n_chain || j > maxDraft) continue;
+                const size_t o = ((size_t)gi * (maxDraft + 1) + j) * blockB + lane;
+                if (out.row_maxlogit) out.row_maxlogit[o] = mx[i];
+                if (out.row_argmax) out.row_argmax[o] = ar[i];
+                if (out.row_conf) out.row_conf[o] = cf[i];
+            }
         }
     }
+    __syncthreads();
 
-    // stepwise choice of a node (rows row0 + lane of a block of bl positions) over the positions still masked in
-    // `cur`: highest confidence, ties to the lowest position; leaves this lane's confidence in c
+    // stepwise choice of a node over the positions still masked in `cur`: highest confidence (not a number counts as 0), ties
+    // to the lowest position; leaves this lane's confidence in c.  conf: of position `lane`
     int pstar = 0, tstar = 0;
     float c = -1.f;
-    auto choose_at = [&](int row0, int bl) {
+    auto choose_from = [&](float conf, int bl) {
         const bool valid = lane < bl && ((cur >> lane) & 1ull);
-        c = valid ? row_conf[row0 + lane] : -1.f;
-        float bc = c;
-        int bp = lane;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const float oc = __shfl_xor(bc, off, 64);
-            const int op = __shfl_xor(bp, off, 64);
-            if (oc > bc || (oc == bc && op < bp)) { bc = oc; bp = op; }
-        }
-        pstar = bp;
-        tstar = row_arg[row0 + pstar];
+        c = valid ? (conf == conf ? conf : 0.f) : -INFINITY;
+        const float top = wave_max(c);
+        const unsigned long long best = __ballot(valid && c == top);
+        pstar = best ? __ffsll(best) - 1 : 0;
     };
-    auto choose = [&](int node) { choose_at(g.row0 + node * blen, blen); };
+    auto choose_at = [&](int row0, int bl) {              // rows row0 + lane
+        choose_from(lane < bl ? row_conf[row0 + lane] : 0.f, bl);
+        tstar = __builtin_amdgcn_readfirstlane(row_arg[row0 + pstar]);
+    };
+    auto choose = [&](int node) {
+        choose_from(lane < blen ? node_conf[node][lane] : 0.f, blen);
+        tstar = __builtin_amdgcn_readfirstlane(node_arg[node][pstar]);
+    };
     int m = 0;
     bool complete = false;
     while (true) {
         if (cur == 0ull) { complete = true; break; }     // the drafts covered every masked position
         choose(m);
-        const int dp = __shfl(my_dpos, m, 64), dt = __shfl(my_dtok, m, 64);
+        const int dp = __builtin_amdgcn_readlane(my_dpos, m), dt = __builtin_amdgcn_readlane(my_dtok, m);
         if (m < nd && pstar == dp && tstar == dt) {
             cur &= ~(1ull << pstar);
             ++m;
@@ -824,7 +851,7 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
             int k = 0;
             while (true) {
                 choose_at(g2.row0 + k * blen2, blen2);
-                const int dp = __shfl(dpos2, k, 64), dt = __shfl(dtok2, k, 64);
+                const int dp = __builtin_amdgcn_readlane(dpos2, k), dt = __builtin_amdgcn_readlane(dtok2, k);
                 if (k < nd2 && pstar == dp && tstar == dt) {
                     cur &= ~(1ull << pstar);
                     ++k;
@@ -836,11 +863,7 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
             const int n_rem = __popcll(rem);
             n_next = min(g2.n_draft_next, g2.allow_full ? n_rem : max(n_rem - 1, 0));
             const bool mine = (rem >> lane) & 1ull;
-            int rank = 0;
-            for (int qd = 0; qd < 64; ++qd) {
-                const float cq = __shfl(c, qd, 64);
-                if (((rem >> qd) & 1ull) && (cq > c || (cq == c && qd < lane))) ++rank;
-            }
+            const int rank = n_next > 0 ? rank_among(c, rem, lane) : 0;
             const int my_tok = row_arg[g2.row0 + k * blen2 + (lane < blen2 ? lane : 0)];
             if (mine && rank < n_next) {
                 r->next_pos[rank] = lane;
@@ -880,7 +903,7 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
     // one more token from the node that holds drafts 1..m and m+2; that node has no children
     int last = m, res_pos = -1, res_tok = -1;
     if (g.n_nodes > g.n_chain && m + 1 < nd) {
-        const int dp2 = __shfl(my_dpos, m + 1, 64), dt2 = __shfl(my_dtok, m + 1, 64);
+        const int dp2 = __builtin_amdgcn_readlane(my_dpos, m + 1), dt2 = __builtin_amdgcn_readlane(my_dtok, m + 1);
         if (pstar == dp2 && tstar == dt2) {
             res_pos = pstar;
             res_tok = tstar;
@@ -895,12 +918,8 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
     // the leaf keeps one masked position to predict, unless a next block exists for it to reach into
     const int n_next = min(g.n_draft_next, g.allow_full ? n_rem : max(n_rem - 1, 0));
     const bool mine = (rem >> lane) & 1ull;
-    int rank = 0;
-    for (int qd = 0; qd < 64; ++qd) {
-        const float cq = __shfl(c, qd, 64);
-        if (((rem >> qd) & 1ull) && (cq > c || (cq == c && qd < lane))) ++rank;
-    }
-    const int my_tok = row_arg[g.row0 + last * blen + (lane < blen ? lane : 0)];
+    const int rank = n_next > 0 ? rank_among(c, rem, lane) : 0;
+    const int my_tok = node_arg[last][lane < blen ? lane : 0];
     if (mine && rank < n_next) {
         r->next_pos[rank] = lane;
         r->next_tok[rank] = my_tok;
