@@ -67,68 +67,6 @@ __device__ __forceinline__ int rank_among(float c, unsigned long long set, int l
     return rank;
 }
 
-// ------------------------------------------------------------------------
-// a0: tree build.  One work-group per node: node j of a decode group is the
-// block state with drafts 1..j written in (Section 3.2.3).
-// ------------------------------------------------------------------------
-__global__ void k_build_rows(const FwdHeader* __restrict__ fw, SeqState* __restrict__ state,
-                             const int* __restrict__ raw_tok, int* __restrict__ row_tok,
-                             int* __restrict__ row_pos, int* __restrict__ row_node,
-                             int* __restrict__ out_tok, int mask_id, int max_seq_len,
-                             const float* __restrict__ ref_conf, const int* __restrict__ ref_arg) {
-    const int ni = blockIdx.x;
-    if (ni >= fw->n_nodes) return;
-    const NodeDesc nd = fw->nodes[ni];
-    const GroupDesc g = fw->groups[nd.group];
-    SeqState* s = &state[nd.seq];
-    // A block nobody has predicted yet, with drafts read off the last refresh (Section 3.2.2 with the cache of
-    // Section 4.1): node j holds the j positions the refresh was most confident of.  One wave per node, one lane
-    // per position.
-    int ref_rank = 0x7fffffff, ref_tok = mask_id;
-    if (g.mode == GM_DECODE && g.from_refresh) {             // uniform over the wave
-        const int lane = threadIdx.x;
-        const size_t base = (size_t)nd.seq * max_seq_len + nd.S;
-        const float c = lane < nd.blen ? ref_conf[base + lane] : -1.f;
-        ref_rank = rank_among(c, nd.blen >= 64 ? ~0ull : (1ull << nd.blen) - 1ull, lane);
-        if (lane < nd.blen) ref_tok = ref_arg[base + lane];
-    }
-    for (int p = threadIdx.x; p < nd.blen; p += blockDim.x) {
-        int tok;
-        if (g.mode == GM_RAW) {
-            tok = raw_tok[g.raw_off + p];
-        } else if (g.mode == GM_APPEND) {
-            tok = s->tok[p];
-            if (g.out_off >= 0) out_tok[(size_t)nd.seq * max_seq_len + g.out_off + p] = tok;
-        } else if (g.from_refresh) {
-            tok = ref_rank < nd.j ? ref_tok : mask_id;       // a decode block has at most 64 positions: p is this lane
-        } else if (g.fresh) {
-            tok = mask_id;
-        } else {
-            tok = s->tok[p];
-            for (int j = 0; j < nd.j; ++j)
-                if (s->draft_pos[j] == p) tok = s->draft_tok[j];
-            // a mix-order node skips draft j and holds draft j + 1 instead (Section 5.2)
-            if (nd.extra >= 0 && s->draft_pos[nd.extra] == p) tok = s->draft_tok[nd.extra];
-        }
-        const int row = nd.row0 + p;
-        row_tok[row] = tok;
-        row_pos[row] = nd.S + p;
-        row_node[row] = ni;
-    }
-}
-
-// a1: embedding gather into the fp32 residual stream.
-template <typename T>
-__global__ void k_embed(const T* __restrict__ embed, const int* __restrict__ row_tok, float* __restrict__ h, int d,
-                        int V) {
-    const int row = blockIdx.x;
-    // ids are validated on the host or produced by the arg-max; the clamp keeps the gather in
-    // bounds whatever a corrupted state holds
-    const int tok = min(max(row_tok[row], 0), V - 1);
-    const T* e = embed + (size_t)tok * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) h[(size_t)row * d + i] = ld_f(e + i);
-}
-
 // a2/a6/a9: h += sum of split-K partial sums (fixed order s = 0, 1, ...), then RMSNorm.
 // One work-group of NORM_T threads per row; every thread owns up to NORM_J float4 groups of the
 // row and issues all partial-sum loads of a group before the first add, so a 4096-wide row has
@@ -140,9 +78,10 @@ __device__ __forceinline__ void st4(bf16_t* p, float a, float b, float c, float 
     *(uint2*)p = make_uint2((uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16), (uint32_t)f2bf(c) | ((uint32_t)f2bf(d) << 16));
 }
 
+// NP < 0: the row is the embedding e.
 template <typename T, int NP>
 __device__ __forceinline__ void norm_row(float* hr, const float* pr, size_t part_stride, const float* gain, T* xr,
-                                         int d, float eps) {
+                                         int d, float eps, const T* e = nullptr) {
     const int n4 = d >> 2;
     float4 v[NORM_J], g[NORM_J];
     float ss = 0.f;
@@ -150,7 +89,7 @@ __device__ __forceinline__ void norm_row(float* hr, const float* pr, size_t part
     for (int j = 0; j < NORM_J; ++j) {
         const int i4 = threadIdx.x + j * NORM_T;
         if (i4 < n4) {
-            v[j] = ((const float4*)hr)[i4];
+            v[j] = NP < 0 ? (((uintptr_t)e & 15) == 0 ? ld4_f(e + 4 * i4) : make_float4(ld_f(e + 4 * i4), ld_f(e + 4 * i4 + 1), ld_f(e + 4 * i4 + 2), ld_f(e + 4 * i4 + 3))) : ((const float4*)hr)[i4];
             g[j] = ((const float4*)gain)[i4];                // not behind the reduction's barrier (1000 rows 20.1 -> 19.2 us)
             float4 pv[NP > 0 ? NP : 1];
 #pragma unroll
@@ -159,7 +98,7 @@ __device__ __forceinline__ void norm_row(float* hr, const float* pr, size_t part
             for (int s = 0; s < NP; ++s) {
                 v[j].x += pv[s].x; v[j].y += pv[s].y; v[j].z += pv[s].z; v[j].w += pv[s].w;
             }
-            if (NP > 0) ((float4*)hr)[i4] = v[j];
+            if (NP != 0) ((float4*)hr)[i4] = v[j];
             ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
         }
     }
@@ -204,6 +143,90 @@ __global__ __launch_bounds__(NORM_T) void k_norm(float* __restrict__ h, const fl
             __syncthreads();
             norm_row<T, 0>(hr, pr, part_stride, gain, xr, d, eps);
         }
+    }
+}
+
+// ------------------------------------------------------------------------
+// The forward's descriptor, raw tokens and block states from pinned host memory: what is used of them, in one trip by one
+// work-group.  A copy of the header, 25 KB, goes through the copy engine, and the kernels wait for it on both sides; every block
+// state is a copy of its own (a forward of the fp32 parity model, 32 rows, 101 us; with this and the fused kernel below 82; of
+// the small bf16 model, two sequences of four nodes, 140 / 118).
+// ------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void k_stage(const int* __restrict__ src, StageLayout lay, int* __restrict__ fwd,
+                                                int* __restrict__ raw_tok, int* __restrict__ state) {
+    // segment s of the source: lay.n[s] words from lay.from[s]
+    for (int i = threadIdx.x; i < lay.total; i += 1024) {
+        int j = i, s = 0;
+        while (j >= lay.n[s]) j -= lay.n[s++];
+        const int v = src[lay.from[s] + j];
+        if (s < 3) fwd[lay.from[s] + j] = v;              // the header's front, groups, nodes: same place as in the source
+        else if (s == 3) raw_tok[j] = v;
+        else {
+            constexpr int W = sizeof(SeqState) / 4;
+            state[lay.seq[j / W] * W + j % W] = v;
+        }
+    }
+}
+
+// ------------------------------------------------------------------------
+// a0 + a1 + a2 of the first layer: tree build, embedding gather into the fp32 residual stream, RMSNorm.  One work-group per
+// row.  Node j of a decode group is the block state with drafts 1..j written in (Section 3.2.3).  Bound by latency, a trip to
+// memory each for node, state and embedding (32 rows x 256, us, three kernels / this: 2.6 + 2.3 + 2.7 / 3.8).
+// EMBED = false: the tree build alone.
+// ------------------------------------------------------------------------
+template <typename T, bool EMBED>
+__global__ __launch_bounds__(EMBED ? NORM_T : 64) void k_rows(const FwdHeader* __restrict__ fw, int n_nodes, const SeqState* __restrict__ state,
+                                                             const int* __restrict__ raw_tok, int* __restrict__ row_node,
+                                                             int* __restrict__ out_tok, int mask_id, int max_seq_len,
+                                                             const float* __restrict__ ref_conf, const int* __restrict__ ref_arg,
+                                                             const T* __restrict__ embed, float* __restrict__ h,
+                                                             const float* __restrict__ gain, T* __restrict__ xn, int d, int V, float eps) {
+    __shared__ int sh_tok;
+    const int row = blockIdx.x, lane = threadIdx.x & 63;
+    if (threadIdx.x < 64) {
+        // the node that holds the row: nodes lie in row order
+        int ni = 0;
+        for (int n0 = 0; n0 < n_nodes; n0 += 64) {
+            const unsigned long long at_or_before = __ballot(n0 + lane < n_nodes && fw->nodes[min(n0 + lane, n_nodes - 1)].row0 <= row);
+            if (at_or_before) ni = n0 + 63 - __clzll(at_or_before);
+        }
+        const NodeDesc nd = fw->nodes[ni];
+        const GroupDesc g = fw->groups[nd.group];
+        const SeqState* s = &state[nd.seq];
+        const int p = row - nd.row0;
+        int tok;
+        if (g.mode == GM_RAW) {
+            tok = raw_tok[g.raw_off + p];
+        } else if (g.mode == GM_APPEND) {
+            tok = s->tok[p];
+            if (g.out_off >= 0 && lane == 0) out_tok[(size_t)nd.seq * max_seq_len + g.out_off + p] = tok;
+        } else if (g.from_refresh) {
+            // A block nobody has predicted yet, with drafts read off the last refresh (Section 3.2.2 with the cache of
+            // Section 4.1): node j holds the j positions the refresh was most confident of.  One lane per position.
+            const size_t base = (size_t)nd.seq * max_seq_len + nd.S;
+            const float c = lane < nd.blen ? ref_conf[base + lane] : -1.f;
+            const int rank = rank_among(c, nd.blen >= 64 ? ~0ull : (1ull << nd.blen) - 1ull, lane);
+            tok = __builtin_amdgcn_readlane(rank, p) < nd.j ? ref_arg[base + p] : mask_id;
+        } else if (g.fresh) {
+            tok = mask_id;
+        } else {
+            // the drafts: lane j holds draft j + 1; a mix-order node skips draft j and holds draft j + 1 instead (Section 5.2)
+            const int dpos = lane <= SSD_MAX_DRAFT ? s->draft_pos[lane] : -1, dtok = lane <= SSD_MAX_DRAFT ? s->draft_tok[lane] : 0;
+            tok = s->tok[p];
+            const unsigned long long in = __ballot((lane < nd.j || lane == nd.extra) && lane <= SSD_MAX_DRAFT && dpos == p);
+            if (in) tok = __builtin_amdgcn_readlane(dtok, 63 - __clzll(in));
+        }
+        if (threadIdx.x == 0) {
+            row_node[row] = ni;
+            sh_tok = tok;
+        }
+    }
+    if constexpr (EMBED) {
+        __syncthreads();
+        // ids are validated on the host or produced by the arg-max; the clamp keeps the gather in bounds whatever a corrupted
+        // state holds
+        const T* e = embed + (size_t)min(max(sh_tok, 0), V - 1) * d;
+        norm_row<T, -1>(h + (size_t)row * d, nullptr, 0, gain, xn + (size_t)row * d, d, eps, e);
     }
 }
 
@@ -955,17 +978,20 @@ __global__ __launch_bounds__(64) void k_accept(const FwdHeader* __restrict__ fw,
 // ------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------
-void launch_build_rows(const ssd_ctx* c, hipStream_t st, int n_nodes) {
-    k_build_rows<<<n_nodes, 64, 0, st>>>(c->b.fwd, c->b.state, c->b.raw_tok, c->b.row_tok, c->b.row_pos,
-                                         c->b.row_node, c->b.out_tok, c->dm.mask_id, c->dm.max_seq_len, c->b.ref_conf,
-                                         c->b.ref_arg);
+void launch_stage(const ssd_ctx* c, const void* pinned, const StageLayout& lay, hipStream_t st) {
+    k_stage<<<1, 1024, 0, st>>>((const int*)pinned, lay, (int*)c->b.fwd, c->b.raw_tok, (int*)c->b.state);
 }
 
-void launch_embed(const ssd_ctx* c, int M, hipStream_t st) {
-    if (c->dm.dtype == SSD_F32)
-        k_embed<float><<<M, 256, 0, st>>>((const float*)c->embed, c->b.row_tok, c->b.h, c->dm.d, c->dm.V);
-    else
-        k_embed<bf16_t><<<M, 256, 0, st>>>((const bf16_t*)c->embed, c->b.row_tok, c->b.h, c->dm.d, c->dm.V);
+template <typename T, bool EMBED>
+static void rows_t(const ssd_ctx* c, int M, int n_nodes, const float* gain, hipStream_t st) {
+    k_rows<T, EMBED><<<M, EMBED ? NORM_T : 64, 0, st>>>(c->b.fwd, n_nodes, c->b.state, c->b.raw_tok, c->b.row_node, c->b.out_tok,
+                                                       c->dm.mask_id, c->dm.max_seq_len, c->b.ref_conf, c->b.ref_arg,
+                                                       (const T*)c->embed, c->b.h, gain, (T*)c->b.xn, c->dm.d, c->dm.V, c->dm.eps);
+}
+
+void launch_rows(const ssd_ctx* c, int M, int n_nodes, const float* gain, hipStream_t st) {
+    if (c->dm.dtype == SSD_F32) gain ? rows_t<float, true>(c, M, n_nodes, gain, st) : rows_t<float, false>(c, M, n_nodes, gain, st);
+    else gain ? rows_t<bf16_t, true>(c, M, n_nodes, gain, st) : rows_t<bf16_t, false>(c, M, n_nodes, gain, st);
 }
 
 void launch_norm(const ssd_ctx* c, int M, const float* gain, int n_part, hipStream_t st) {

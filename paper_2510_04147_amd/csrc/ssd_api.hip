@@ -139,8 +139,6 @@ static size_t carve(const Dims& d, char* base, Buffers* b) {
     t.row_max = (float*)take(R * 4);
     t.row_arg = (int*)take(R * 4);
     t.row_conf = (float*)take(R * 4);
-    t.row_tok = (int*)take(R * 4);
-    t.row_pos = (int*)take(R * 4);
     t.row_node = (int*)take(R * 4);
     t.raw_tok = (int*)take(R * 4);
     const size_t cache = (size_t)d.L * d.max_seqs * d.Hkv * d.seq_stride() * d.dh * e;
@@ -252,6 +250,7 @@ extern "C" __attribute__((visibility("default"))) int ssd_create(const ssd_confi
     for (int i = 0; i < ssd_ctx::kSlots; ++i) {
         if ((e = hipHostMalloc((void**)&c->stage[i], c->stage_bytes, hipHostMallocDefault)) != hipSuccess)
             return fail(e, "hipHostMalloc(staging)");
+        if ((e = hipHostGetDevicePointer(&c->stage_dev[i], c->stage[i], 0)) != hipSuccess) return fail(e, "hipHostGetDevicePointer");
         if ((e = hipEventCreateWithFlags(&c->stage_ev[i], hipEventDisableTiming)) != hipSuccess)
             return fail(e, "hipEventCreate");
     }
@@ -447,35 +446,38 @@ static void gemm(ssd_ctx* c, int cls, int epi, const void* X, const Wt& W, void*
     launch_gemm_plain(c, epi, X, W.raw, out, M, N, W.K, c->stream);
 }
 
-// Copies a forward's descriptor, its raw tokens and the block states to upload to the device through
+// Brings a forward's descriptor, its raw tokens and the block states to upload to the device through
 // the pinned staging ring (asynchronous on the context's stream).
 static int stage_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int n_raw, const Upload* ups, int n_ups,
                          const ssd_step_out* out) {
-    const Dims& d = c->dm;
+    static_assert(offsetof(FwdHeader, groups) % 4 == 0 && offsetof(FwdHeader, nodes) % 4 == 0 && sizeof(SeqState) % 4 == 0, "staged in words");
     hipStream_t st = c->stream;
-    // ---- stage and upload the descriptor
     const int slot = c->stage_next;
     c->stage_next = (slot + 1) % ssd_ctx::kSlots;
     if (c->stage_used[slot]) HIPCHK(c, hipEventSynchronize(c->stage_ev[slot]));
     char* sp = c->stage[slot];
-    memcpy(sp, &hd, sizeof hd);
-    if (out) ((FwdHeader*)sp)->out = *out;
-    HIPCHK(c, hipMemcpyAsync(c->b.fwd, sp, sizeof hd, hipMemcpyHostToDevice, st));
-    if (n_raw > 0) {
-        int* sr = (int*)(sp + sizeof(FwdHeader));
-        memcpy(sr, raw, (size_t)n_raw * 4);
-        HIPCHK(c, hipMemcpyAsync(c->b.raw_tok, sr, (size_t)n_raw * 4, hipMemcpyHostToDevice, st));
+    FwdHeader* sh = (FwdHeader*)sp;
+    memcpy(sp, &hd, offsetof(FwdHeader, groups));
+    memcpy(sh->groups, hd.groups, sizeof(GroupDesc) * hd.n_groups);
+    memcpy(sh->nodes, hd.nodes, sizeof(NodeDesc) * hd.n_nodes);
+    if (out) sh->out = *out;
+    const size_t raw_at = sizeof(FwdHeader), state_at = raw_at + (size_t)c->dm.max_rows * 4;
+    if (n_raw > 0) memcpy(sp + raw_at, raw, (size_t)n_raw * 4);
+    StageLayout lay;
+    for (int i = 0; i < n_ups; ++i) {
+        memcpy(sp + state_at + sizeof(SeqState) * i, &ups[i].st, sizeof(SeqState));
+        lay.seq[i] = ups[i].seq;
     }
-    if (n_ups > 0) {
-        SeqState* ss = (SeqState*)(sp + sizeof(FwdHeader) + (size_t)d.max_rows * 4);
-        for (int i = 0; i < n_ups; ++i) {
-            ss[i] = ups[i].st;
-            HIPCHK(c, hipMemcpyAsync(&c->b.state[ups[i].seq], &ss[i], sizeof(SeqState), hipMemcpyHostToDevice, st));
-        }
-    }
+    for (int i = n_ups; i < SSD_MAX_SEQS; ++i) lay.seq[i] = 0;
+    const size_t from[5] = {0, offsetof(FwdHeader, groups), offsetof(FwdHeader, nodes), raw_at, state_at};
+    const size_t bytes[5] = {offsetof(FwdHeader, groups), sizeof(GroupDesc) * hd.n_groups, sizeof(NodeDesc) * hd.n_nodes,
+                             (size_t)std::max(n_raw, 0) * 4, sizeof(SeqState) * n_ups};
+    lay.total = 0;
+    for (int i = 0; i < 5; ++i) { lay.from[i] = (int)(from[i] / 4); lay.n[i] = (int)(bytes[i] / 4); lay.total += lay.n[i]; }
+    launch_stage(c, c->stage_dev[slot], lay, st);
+    HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipEventRecord(c->stage_ev[slot], st));
     c->stage_used[slot] = true;
-
     return SSD_OK;
 }
 
@@ -535,13 +537,12 @@ static int run_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int 
     auto launch_all = [&]() {
         {
             ProfScope ps(c, KC_ROWS);
-            launch_build_rows(c, st, hd.n_nodes);
-            launch_embed(c, M, st);
+            launch_rows(c, M, hd.n_nodes, c->lw[0].norm1, st);
         }
         int n_part = 0, ns = 1;
         for (int l = 0; l < d.L; ++l) {
             const LayerW& w = c->lw[l];
-            { ProfScope ps(c, KC_NORM); launch_norm(c, M, w.norm1, n_part, st); }
+            if (l > 0) { ProfScope ps(c, KC_NORM); launch_norm(c, M, w.norm1, n_part, st); }
             n_part = 0;
             gemm(c, KC_GEMM_QKV, EPI_F32, c->b.xn, w.wqkv, c->b.part, M, &ns);
             // blocks of at most 32 rows: the attention kernel sums the partial sums and applies the
@@ -1284,7 +1285,7 @@ extern "C" __attribute__((visibility("default"))) int ssd_k_attention(ssd_ctx* c
     for (int sp = 0; sp < n_part; ++sp)
         HIPCHK(c, hipMemcpyAsync(c->b.part + sp * stride, qkv + (size_t)sp * M * d.nqkv(), (size_t)M * d.nqkv() * 4,
                                  hipMemcpyDeviceToDevice, st));
-    launch_build_rows(c, st, hd.n_nodes);
+    launch_rows(c, M, hd.n_nodes, nullptr, st);
     if (!fused) launch_rope(c, hd.n_nodes, max_blen, layer, n_part, st);
     if (!(mfma && launch_attn_mfma(c, hd.n_nodes, 0, max_blen, layer, fused ? n_part : -1, any_suffix, st)))
         launch_attn_plain(c, M, layer, st);

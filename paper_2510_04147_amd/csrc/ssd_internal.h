@@ -147,8 +147,6 @@ struct Buffers {
     float* row_max;      // [max_rows]
     int* row_arg;        // [max_rows]
     float* row_conf;     // [max_rows]
-    int* row_tok;        // [max_rows]
-    int* row_pos;        // [max_rows]
     int* row_node;       // [max_rows]
     int* raw_tok;        // [max_rows]
     void* kcache;        // [L][max_seqs][Hkv][seq_stride * dh] T, keys after rotary, fragment order
@@ -214,6 +212,7 @@ struct ssd_ctx {
     // host staging ring for descriptors / small uploads
     static const int kSlots = 4;
     char* stage[kSlots];
+    void* stage_dev[kSlots];   // the same memory as the device sees it
     hipEvent_t stage_ev[kSlots];
     bool stage_used[kSlots];
     int stage_next;
@@ -231,8 +230,15 @@ struct ssd_ctx {
 
 // ---- launchers implemented in the kernel files (all asynchronous on `st`)
 // T-typed buffers are passed as void* with the dtype flag.
-void launch_build_rows(const ssd_ctx* c, hipStream_t st, int n_nodes);
-void launch_embed(const ssd_ctx* c, int M, hipStream_t st);
+// What a forward uploads from the pinned staging slot, in words: the header's front, its groups, its nodes (to the same place
+// of the device's header), the raw tokens, the block states of the sequences in seq.
+struct StageLayout {
+    int from[5], n[5], total;
+    int seq[SSD_MAX_SEQS];
+};
+void launch_stage(const ssd_ctx* c, const void* pinned, const StageLayout& lay, hipStream_t st);
+// tree build, embedding and the first layer's norm (gain = its gains) of M rows; gain == nullptr: the tree build alone
+void launch_rows(const ssd_ctx* c, int M, int n_nodes, const float* gain, hipStream_t st);
 void launch_norm(const ssd_ctx* c, int M, const float* gain, int n_part, hipStream_t st);
 // gate_rows > 0: the matrix is gate rows then up rows; interleave them per 16 channels
 void launch_pack_weights(const void* src, void* dst, int N, int K, int gate_rows, hipStream_t st);
