@@ -1082,7 +1082,7 @@ void launch_lm_merge_to(const ssd_ctx* c, int M, int n_tiles, const float* part,
 }
 
 void launch_accept(const ssd_ctx* c, int n_groups, hipStream_t st) {
-    k_accept<<<n_groups, 64, 0, st>>>(c->b.fwd, c->b.state, c->b.row_conf, c->b.row_arg, c->b.row_max, c->b.result,
+    k_accept<<<n_groups, 64, 0, st>>>(c->b.fwd, c->b.state, c->b.row_conf, c->b.row_arg, c->b.row_max, c->results_to_host ? c->host_result_dev : c->b.result,
                                       c->b.out_tok, c->dm.max_seq_len, c->dm.block, c->dm.max_draft, c->dm.mask_id,
                                       c->b.ref_conf, c->b.ref_arg);
 }

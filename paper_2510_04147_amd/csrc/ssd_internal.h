@@ -198,7 +198,7 @@ struct ssd_ctx {
     int use_graphs;
     struct FwdGraph {
         int M, ML, n_nodes, n_groups, max_blen, kernel_path;
-        int flags;       // bit 0: some node appends KV, bit 1: some node reads a cached suffix (other kernels)
+        int flags;       // bit 0: some node appends KV, bit 1: some node reads a cached suffix (other kernels), bit 2: results to the host
         int seen;
         hipGraphExec_t exec;
     };
@@ -218,6 +218,8 @@ struct ssd_ctx {
     int stage_next;
     size_t stage_bytes;
     StepResult* host_result;   // pinned
+    StepResult* host_result_dev;   // the same memory as the device sees it
+    bool results_to_host;      // the acceptance kernel writes there (decoding loops) instead of to b.result
     // profiling
     bool profiling;
     std::vector<hipEvent_t> ev_pool;
