@@ -108,3 +108,8 @@ inline bool gemm_plain_small_tiles(const void* X, const void* W, int M, int N) {
 inline bool gemm_plain_small_wins(int M, int N) {
     return M <= 64 || (long long)((N + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE) * ((M + GEMM_PLAIN_TILE - 1) / GEMM_PLAIN_TILE) <= 160;
 }
+
+// Attention: work-groups of four waves, two to a CU, where eight-wave ones would take more than one round over the 256 CUs
+// (8B shape, us, eight waves / four: 576 work-groups of 64-row blocks 33.6 / 27.7, 640 at prefix 1152 59 / 48, 1000-row
+// prompt 50 / 39, refresh of 512 rows 43 / 31; 160 work-groups 13.2 / 13.0, 32 at prefix 1000 18.2 / 19.0).
+inline bool attn_two_per_cu(long long work_groups) { return work_groups > 256; }

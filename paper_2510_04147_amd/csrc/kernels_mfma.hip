@@ -96,10 +96,10 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
 
 // ------------------------------------------------------------------------
 // a4: shared-prefix bidirectional attention on the matrix cores.
-// One work-group of ATTN_WAVES waves per (node, query head, 32-row query tile).
+// One work-group per (node, query head, 32-row query tile).
 // Keys are walked in tiles of 32, first the sequence's cached prefix [0,S), then
-// the node's own rows; wave w takes tiles w, w + ATTN_WAVES, ...; online softmax
-// in fp32; the waves' partial results are merged through LDS in wave order.
+// the node's own rows, in ATTN_STRANDS strands: strand w takes tiles w, w + ATTN_STRANDS, ...; online softmax
+// in fp32.  Strands w and w + 4 are merged first, then the four pairs, through LDS, in order.
 //   S^T[key][q] = K Q^T     : A = K fragment (rows = keys), B = Q fragment
 //   O^T[d][q]  += V^T P^T   : A = V^T fragment (rows = d),  B = P^T fragment
 // With q on the MFMA column axis every softmax statistic (running max, sum,
@@ -112,14 +112,27 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
 // The tile order depends on S and the block length only, so a row's result does
 // not depend on how many nodes the forward holds.
 // ------------------------------------------------------------------------
-#define ATTN_WAVES 8   // waves per (node, head, query tile): wave w takes key tiles w, w+8, ...
+#define ATTN_STRANDS 8
+
+// Two partial results of the softmax, (max, sum, O^T) each, on a common maximum; a strand without a tile counts for nothing.
+__device__ __forceinline__ void merge_factors(float ma, float mb, float& m, float& ca, float& cb) {
+    m = fmaxf(ma, mb);
+    ca = ma == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ma - m);
+    cb = mb == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mb - m);
+}
+__device__ __forceinline__ float merge2(float a, float ca, float b, float cb) { return __fmaf_rn(b, cb, __fmul_rn(a, ca)); }
 
 // FUSED: the kernel starts from the QKV projection's fp32 partial sums instead of ready q / k / v: it
 // adds the partial sums in split order, applies the rotary embedding to its head's queries and to
 // the node's own keys and keeps the own key / value tile in LDS in fragment order.  For forwards whose
 // nodes have at most 32 rows (one query tile) and append nothing to the cache, head size 128.
-template <int DH, bool FUSED, bool SUFFIX>
-__global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* __restrict__ fw,
+// SHARED: four waves, each of which walks two strands one after the other (the first one's result waits in LDS), so that
+// two work-groups fit a CU and one's prologue and merge overlap the other's tiles; otherwise eight waves, a strand each.
+// The same bits either way.  Bound by latency: of a work-group's 12 us at four tiles a strand its tiles take three; descriptor, partial
+// sums and merge the rest, and with the partial results of eight strands in LDS (135 KB) only one work-group fitted
+// a CU (both times: attn_two_per_cu).
+template <int DH, bool FUSED, bool SUFFIX, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 256 : 512, 2) void k_attn_mfma(const FwdHeader* __restrict__ fw,
                                                                const bf16_t* __restrict__ q,
                                                                const bf16_t* __restrict__ kown,
                                                                const bf16_t* __restrict__ vown,
@@ -131,13 +144,14 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
                                                                size_t part_stride, const float* __restrict__ cosT,
                                                                const float* __restrict__ sinT, int nodes_per_seq) {
     constexpr int KST = DH / 16, DT = DH / 32;
+    constexpr int WAVES = SHARED ? 4 : 8, T = WAVES * 64;
     constexpr int NE = DT * 16;                                      // O^T values per lane
-    constexpr int EPW = NE / ATTN_WAVES;                             // of which each wave merges EPW
+    constexpr int EPW = NE / WAVES;                                  // of which each wave merges EPW
     static_assert(EPW % 4 == 0, "the merge writes groups of four head channels");
     static_assert(!FUSED || DH == 128, "the fused rotary stage is laid out for head size 128");
-    __shared__ float mrg[ATTN_WAVES][NE + 2][64];                    // every wave's partial (O^T, max, sum)
+    __shared__ float mrg[4][NE + 2][64];                             // the pairs' partials (O^T, max, sum)
     __shared__ __attribute__((aligned(16))) bf16_t qs[32][DH + 8];   // the query tile, shared by the waves
-    // FUSED: the node's own key and value tile, fragment order, in the (not yet used) merge area
+    // FUSED: the node's own key and value tile, fragment order, at the front of the (not yet used) merge area
     bf16_t* ks_own = (bf16_t*)&mrg[0][0][0];
     bf16_t* vs_own = ks_own + 32 * DH;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -199,7 +213,7 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
     const int cache_tiles = pre_tiles + suf_tiles, n_tiles = cache_tiles + ((nd.blen + 31) >> 5);
     auto cache_tile = [&](int t) { return !SUFFIX || t < pre_tiles ? t : suf_first + (t - pre_tiles); };
     // positions that are not keys of this node hold other or stale data: masked (keys) or zeroed (values)
-    auto load_k = [&](bf16x8(&kf)[KST], int t) {
+    auto load_k = [&](bf16x8(&kf)[KST], int t) SSD_INLINE {
         const bf16_t* kp;
         if (t >= cache_tiles)
             kp = (FUSED ? ks_own : ko + (size_t)(t - cache_tiles) * 32 * DH) + lane * 8;
@@ -208,7 +222,7 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
 #pragma unroll
         for (int ks = 0; ks < KST; ++ks) kf[ks] = *(const bf16x8*)(kp + ks * 512);
     };
-    auto load_v = [&](bf16x8(&vf)[DT][2], int t) {
+    auto load_v = [&](bf16x8(&vf)[DT][2], int t) SSD_INLINE {
         const bf16_t* vp;
         if (t >= cache_tiles)
             vp = (FUSED ? vs_own : vo + (size_t)(t - cache_tiles) * 32 * DH) + lane * 8;
@@ -219,7 +233,7 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
 #pragma unroll
             for (int st = 0; st < 2; ++st) vf[dt][st] = *(const bf16x8*)(vp + (dt * 2 + st) * 512);
     };
-    bf16x8 kf[KST], kn[KST], vf[DT][2], vn[DT][2];
+    bf16x8 kf[KST], kn[KST], vf[DT][2], vn[SHARED ? 1 : DT][2];
     // the first tile's loads go out before anything else (FUSED: unless it is the own tile, which is
     // not in LDS yet)
     const bool first_later = FUSED && wave >= cache_tiles;
@@ -232,7 +246,10 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
         // halves; v: channels [8cg, 8cg+8).  Rows past the end of the block take row 0's values
         // (queries: never written back; keys: masked) or zeros (values).
         constexpr int HALF = DH / 2;
-        const int tid = threadIdx.x, r = tid >> 4, cg = tid & 15;
+        const int tid = threadIdx.x, cg = tid & 15;
+#pragma unroll
+        for (int r0 = 0; r0 < 32; r0 += T / 16) {
+        const int r = r0 + (tid >> 4);
         const bool rvalid = r < nd.blen;
         const int row = nd.row0 + (rvalid ? r : 0), pos = nd.S + (rvalid ? r : 0);
         const int nkv = Hkv * DH, nqkv = nq + 2 * nkv;
@@ -286,10 +303,11 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
             vb[j] = rvalid ? f2bf_m(vv[j]) : (uint16_t)0;
             vs_own[vfrag_off(r, cg * 8 + j, DH)] = vb[j];             // scattered 2-byte LDS stores, 8 per thread
         }
+        }
     } else {
         // the query tile, after the first key/value loads are on their way; rows past the end of the
         // block are read from row 0 and never written back
-        for (int idx = threadIdx.x; idx < 32 * (DH / 8); idx += ATTN_WAVES * 64) {
+        for (int idx = threadIdx.x; idx < 32 * (DH / 8); idx += T) {
             const int r = idx / (DH / 8), c8 = idx % (DH / 8);
             const int rin = qt * 32 + r;
             const int grow = nd.row0 + (rin < nd.blen ? rin : 0);
@@ -301,105 +319,161 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void k_attn_mfma(const FwdHeader* 
         load_k(kf, wave);
         load_v(vf, wave);
     }
-    for (int t = wave; t < n_tiles; t += ATTN_WAVES) {
-        const bool own = t >= cache_tiles;
-        // first key of the tile: a row of the node (own) or a cache position
-        const int t0 = (own ? t - cache_tiles : cache_tile(t)) * 32;
-        // keys t0 + [0, lim_a) and t0 + [lo_b, lim_b) of this tile exist
-        const int lim_a = (own ? nd.blen : nd.S) - t0;
-        const int lo_b = own ? 32 : blk_end - t0, lim_b = own ? 0 : node_T - t0;
-        auto valid = [&](int key) { return key < lim_a || (SUFFIX && key >= lo_b && key < lim_b); };
-        const bool all_valid = lim_a >= 32 || (SUFFIX && lo_b <= 0 && lim_b >= 32);
-        // ---- this wave's next tile, in flight while this one is processed
-        if (t + ATTN_WAVES < n_tiles) {
-            load_k(kn, t + ATTN_WAVES);
-            load_v(vn, t + ATTN_WAVES);
-        }
-        // ---- S^T = K Q^T
-        floatx16 sacc;
+    const float sc = scale * 1.44269504f;                            // scores to powers of two
+    // one strand, whose first keys are on their way (and, unless SHARED, values: there they are loaded with the tile)
+    auto walk = [&](int strand, bool v_loaded) SSD_INLINE {
+        for (int t = strand; t < n_tiles; t += ATTN_STRANDS) {
+            const bool own = t >= cache_tiles;
+            // first key of the tile: a row of the node (own) or a cache position
+            const int t0 = (own ? t - cache_tiles : cache_tile(t)) * 32;
+            // keys t0 + [0, lim_a) and t0 + [lo_b, lim_b) of this tile exist
+            const int lim_a = (own ? nd.blen : nd.S) - t0;
+            const int lo_b = own ? 32 : blk_end - t0, lim_b = own ? 0 : node_T - t0;
+            auto valid = [&](int key) { return key < lim_a || (SUFFIX && key >= lo_b && key < lim_b); };
+            const bool all_valid = lim_a >= 32 || (SUFFIX && lo_b <= 0 && lim_b >= 32);
+            if (SHARED && !(v_loaded && t == strand)) load_v(vf, t);
+            // ---- this strand's next tile, in flight while this one is processed
+            if (t + ATTN_STRANDS < n_tiles) {
+                load_k(kn, t + ATTN_STRANDS);
+                if constexpr (!SHARED) load_v(vn, t + ATTN_STRANDS);
+            }
+            // ---- S^T = K Q^T
+            floatx16 sacc;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+            for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < KST; ++ks) {
-            const bf16x8 qf = *(const bf16x8*)&qs[lm][ks * 16 + lh * 8];
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf, sacc, 0, 0, 0);
-        }
-        // ---- online softmax over this lane's 16 keys (key = t0 + 8*(i/4) + 4*lh + i%4)
-        float mx = -INFINITY;
+            for (int ks = 0; ks < KST; ++ks) {
+                const bf16x8 qf = *(const bf16x8*)&qs[lm][ks * 16 + lh * 8];
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf, sacc, 0, 0, 0);
+            }
+            // ---- online softmax over this lane's 16 keys (key = t0 + 8*(i/4) + 4*lh + i%4)
+            if (!all_valid) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int key = (i >> 2) * 8 + lh * 4 + (i & 3);
-            sacc[i] = valid(key) ? sacc[i] * scale : -INFINITY;
-            mx = fmaxf(mx, sacc[i]);
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m_run, mx);
-        const float corr = fast_exp(m_run - m_new);
-        m_run = m_new;
-        float psum = 0.f;
-        bf16x8 pf[2];
+                for (int i = 0; i < 16; ++i)
+                    if (!valid((i >> 2) * 8 + lh * 4 + (i & 3))) sacc[i] = -INFINITY;
+            }
+            float mx = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float p = fast_exp(sacc[i] - m_new);                  // 0 for masked keys
-            psum += p;
-            pf[i >> 3][i & 7] = (__bf16)p;
-        }
-        l_part = l_part * corr + psum;
-        if (!all_valid) {
-            // positions that are not keys hold other data: zero them so 0 * garbage cannot produce NaN
+            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
+            mx = fmaxf(mx, other_half(mx, lh));
+            const float m_new = fmaxf(m_run, mx * sc);
+            const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            float psum = 0.f;
+            bf16x8 pf[2];
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+            for (int i = 0; i < 16; ++i) {
+                const float p = __builtin_amdgcn_exp2f(__fmaf_rn(sacc[i], sc, -m_new));   // 0 for masked keys
+                psum += p;
+                pf[i >> 3][i & 7] = (__bf16)p;
+            }
+            l_part = __fmaf_rn(l_part, corr, psum);
+            if (!all_valid) {
+                // positions that are not keys hold other data: zero them so 0 * garbage cannot produce NaN
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int st = 0; st < 2; ++st)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const int key = (2 * st + (j >> 2)) * 8 + lh * 4 + (j & 3);
+                            if (!valid(key)) vf[dt][st][j] = (__bf16)0.f;
+                        }
+            }
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[dt][i] *= corr;
 #pragma unroll
                 for (int st = 0; st < 2; ++st)
+                    oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][st], pf[st], oacc[dt], 0, 0, 0);
+            }
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int key = (2 * st + (j >> 2)) * 8 + lh * 4 + (j & 3);
-                        if (!valid(key)) vf[dt][st][j] = (__bf16)0.f;
-                    }
+            for (int ks = 0; ks < KST; ++ks) kf[ks] = kn[ks];
+            if constexpr (!SHARED) {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int st = 0; st < 2; ++st) vf[dt][st] = vn[dt][st];
+            }
         }
+    };
+    walk(wave, true);
+    // ---- merge: strands w and w + 4, then the four pairs (fixed, independent of the forward's shape)
+    float* const mf = &mrg[0][0][0];
+    if constexpr (SHARED) {
+        // strand w waits in LDS (FUSED: behind the own tile, which other waves may still need, and one channel tile in registers)
+        constexpr int HELD = FUSED ? 1 : 0, PARK = (DT - HELD) * 16;
+        static_assert((FUSED ? 4096 : 0) + 4 * PARK * 64 <= 4 * (NE + 2) * 64, "the waiting strands fit the merge area");
+        float* const park = mf + (FUSED ? 4096 : 0) + wave * PARK * 64 + lane;
+        const int strand = wave + 4;
+        if (strand < n_tiles) load_k(kf, strand);
+        floatx16 held[HELD ? HELD : 1];
+        const float ma = m_run, la = l_part;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[dt][i] *= corr;
-#pragma unroll
-            for (int st = 0; st < 2; ++st)
-                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][st], pf[st], oacc[dt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int ks = 0; ks < KST; ++ks) kf[ks] = kn[ks];
+        for (int e = 0; e < PARK; ++e) park[e * 64] = oacc[e >> 4][e & 15];
+        if constexpr (HELD) held[0] = oacc[DT - 1];
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int st = 0; st < 2; ++st) vf[dt][st] = vn[dt][st];
+            for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+        m_run = -INFINITY;
+        l_part = 0.f;
+        walk(strand, false);
+        float ca, cb, m;
+        merge_factors(ma, m_run, m, ca, cb);
+        m_run = m;
+        l_part = merge2(la, ca, l_part, cb);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const float first = HELD && e >= PARK ? held[0][e & 15] : park[(e < PARK ? e : 0) * 64];
+            oacc[e >> 4][e & 15] = merge2(first, ca, oacc[e >> 4][e & 15], cb);
+        }
+        __syncthreads();                                            // nobody needs the own tile or a waiting strand any more
+    } else {
+        if constexpr (FUSED) __syncthreads();                       // the own tile shared the merge area
+        if (wave >= 4) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) mrg[wave - 4][e][lane] = oacc[e >> 4][e & 15];
+            mrg[wave - 4][NE][lane] = m_run;
+            mrg[wave - 4][NE + 1][lane] = l_part;
+        }
+        __syncthreads();
+        if (wave < 4) {
+            float ca, cb, m;
+            merge_factors(m_run, mrg[wave][NE][lane], m, ca, cb);
+            m_run = m;
+            l_part = merge2(l_part, ca, mrg[wave][NE + 1][lane], cb);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) oacc[e >> 4][e & 15] = merge2(oacc[e >> 4][e & 15], ca, mrg[wave][e][lane], cb);
+        }
     }
-    // ---- merge the waves' partial results: every wave publishes its partial, then wave w folds
-    // values [w*EPW, (w+1)*EPW) of all waves in wave order (fixed, independent of the forward's shape)
-    if constexpr (FUSED) __syncthreads();                           // the own tile shared the merge area
+    if (wave < 4) {
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mrg[wave][dt * 16 + i][lane] = oacc[dt][i];
-    mrg[wave][NE][lane] = m_run;
-    mrg[wave][NE + 1][lane] = l_part;
+        for (int e = 0; e < NE; ++e) mrg[wave][e][lane] = oacc[e >> 4][e & 15];
+        mrg[wave][NE][lane] = m_run;
+        mrg[wave][NE + 1][lane] = l_part;
+    }
     __syncthreads();
+    // wave w folds values [w*EPW, (w+1)*EPW) of all pairs in order
     float m_all = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < ATTN_WAVES; ++w) m_all = fmaxf(m_all, mrg[w][NE][lane]);
-    float cw[ATTN_WAVES], l = 0.f;
+    for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, mrg[w][NE][lane]);
+    float cw[4], l = 0.f;
 #pragma unroll
-    for (int w = 0; w < ATTN_WAVES; ++w) {
+    for (int w = 0; w < 4; ++w) {
         const float mw = mrg[w][NE][lane];
-        cw[w] = mw == -INFINITY ? 0.f : fast_exp(mw - m_all);            // a wave without a tile counts for nothing
-        l += mrg[w][NE + 1][lane] * cw[w];
+        cw[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
+        l = __fmaf_rn(mrg[w][NE + 1][lane], cw[w], l);
     }
-    l += __shfl_xor(l, 32, 64);
+    l += other_half(l, lh);
     const float inv = 1.0f / l;
     float o[EPW];
 #pragma unroll
     for (int e = 0; e < EPW; ++e) {
         float acc = 0.f;
 #pragma unroll
-        for (int w = 0; w < ATTN_WAVES; ++w) acc += mrg[w][wave * EPW + e][lane] * cw[w];
+        for (int w = 0; w < 4; ++w) acc = __fmaf_rn(mrg[w][wave * EPW + e][lane], cw[w], acc);
         o[e] = acc * inv;
     }
     if (qvalid) {
@@ -432,11 +506,17 @@ bool launch_attn_mfma(const ssd_ctx* c, int n_nodes, int nodes_per_seq, int max_
     c->b.fwd, (const bf16_t*)c->b.q, (const bf16_t*)c->b.kown, (const bf16_t*)c->b.vown, (const bf16_t*)c->b.kcache, \
         (const bf16_t*)c->b.vcache, (bf16_t*)c->b.attn, d.Hq, d.Hkv, layer, d.max_seqs, d.seq_stride(), d.vt_rows(), scale, \
         c->b.part, n_part, ps, c->b.rope_cos, c->b.rope_sin, nodes_per_seq
-#define SSD_ATTN_LAUNCH(DH_, FUSED_)                                                                       \
-    do {                                                                                                   \
-        if (suffix) k_attn_mfma<DH_, FUSED_, true><<<grid, ATTN_WAVES * 64, 0, st>>>(SSD_ATTN_ARGS);      \
-        else k_attn_mfma<DH_, FUSED_, false><<<grid, ATTN_WAVES * 64, 0, st>>>(SSD_ATTN_ARGS);            \
+#define SSD_ATTN_RUN(DH_, FUSED_, SUFFIX_)                                                                              \
+    do {                                                                                                               \
+        if (shared) k_attn_mfma<DH_, FUSED_, SUFFIX_, true><<<grid, 256, 0, st>>>(SSD_ATTN_ARGS);                      \
+        else k_attn_mfma<DH_, FUSED_, SUFFIX_, false><<<grid, 512, 0, st>>>(SSD_ATTN_ARGS);                            \
     } while (0)
+#define SSD_ATTN_LAUNCH(DH_, FUSED_)                                                                                   \
+    do {                                                                                                               \
+        if (suffix) SSD_ATTN_RUN(DH_, FUSED_, true);                                                                   \
+        else SSD_ATTN_RUN(DH_, FUSED_, false);                                                                         \
+    } while (0)
+    const bool shared = attn_two_per_cu((long long)grid.x * grid.y);
     if (n_part >= 0) {
         if (!attn_mfma_can_fuse_rope(c, max_blen)) return false;
         SSD_ATTN_LAUNCH(128, true);
@@ -447,6 +527,7 @@ bool launch_attn_mfma(const ssd_ctx* c, int n_nodes, int nodes_per_seq, int max_
     else
         return false;
 #undef SSD_ATTN_LAUNCH
+#undef SSD_ATTN_RUN
 #undef SSD_ATTN_ARGS
     return true;
 }
