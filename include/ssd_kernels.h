@@ -23,7 +23,7 @@ extern "C" {
 /* One linear step of layer `layer` (ignored for SSD_LIN_LM) with the kernel path the context
  * currently selects: x and out are device pointers, x in cfg.dtype, row-major, M <= max_rows.
  * x may start anywhere that suits its type; from a 16-byte boundary it takes the fastest kernels, with the same results.
- * Split-K partial sums are added in split order, as the forward's consumers do.
+ * Split-K partial sums are added as the forward's consumers do: the first half of them in split order, the second half, then both.
  * Asynchronous on the context's stream.  Errors: SSD_EINVAL, SSD_ERANGE. */
 int ssd_k_linear(ssd_ctx* ctx, int which, int layer, const void* x, int M, void* out);
 
@@ -42,7 +42,7 @@ int ssd_k_write_cache(ssd_ctx* ctx, int seq, int layer, int pos0, int n, const v
 /* The attention step of layer `layer` (Section 3.1's f_theta restricted to the scope of Eq. 5: cached
  * prefix + the node's own rows, bidirectional) with exactly the kernels the forward runs, on a
  * caller-supplied QKV projection: qkv device fp32 [n_part, M, (Hq + 2 Hkv) * dh], the projection's
- * split-K partial sums (added in split order; n_part = 1: the projection itself), M = sum of the
+ * split-K partial sums (added by halves as above; n_part = 1: the projection itself), M = sum of the
  * nodes' blen, `nodes` a host array.  fused = 0: the rotary stage runs as a kernel of its own, then
  * the attention kernel of the context's kernel path; out_q (cfg.dtype [M, Hq * dh]) and out_k / out_v
  * (cfg.dtype [M, Hkv, dh]; both or neither) optionally receive the rotary stage's outputs, i.e. the
@@ -54,7 +54,7 @@ int ssd_k_attention(ssd_ctx* ctx, int layer, int n_nodes, const ssd_k_node* node
                     int fused, void* out_attn, void* out_q, void* out_k, void* out_v);
 
 /* The residual + RMSNorm step (Section 3.1's f_theta): h (device fp32 [M, d_model], in and out) += the
- * n_part split-K partial sums `partials` (device fp32 [n_part, M, d_model], added in order; n_part may be
+ * n_part split-K partial sums `partials` (device fp32 [n_part, M, d_model], the first half's sum, then the second's; n_part may be
  * 0), then out (cfg.dtype [M, d_model]) = h / sqrt(mean(h^2) + rms_eps) * gain (device fp32 [d_model]).
  * Asynchronous.  Errors: SSD_EINVAL, SSD_ERANGE. */
 int ssd_k_norm(ssd_ctx* ctx, float* h, const float* partials, int n_part, const float* gain, int M, void* out);

@@ -15,12 +15,14 @@
 // grid that is a whole number of rounds over the 256 CUs (gemm_wide_tile).  8B shape, us, before (256 x 128 in eight waves,
 // two chains per output, which fill the register file at half the tile) / now: gate/up 512 rows 123 / 86, 576 rows 117 /
 // 100, 640 rows 121 / 103, 1000 rows 186 / 171; QKV 640 rows 69.5 / 59, down 512 rows 61 / 50, 640 rows 77 / 66.
+// HALF (fp32 partial sums): half of the k-slices one after the other, each a chain of its own, added as the consumers add partial
+// sums: two leave the kernel instead of one per slice (gemm_halves_tile).
 // Fragments are read and loads issued one by one between MFMAs (all of a step's reads first and loads where the compiler left
 // them: 1.58 us a chunk); eight waves on 256 x 256, two per SIMD, are no faster than four.
-template <int WN, int WM, int R, int TW, int EPI, int NSX, int NSW>
+template <int WN, int WM, int R, int TW, int EPI, int NSX, int NSW, bool HALF>
 __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, const uint4* Wp, void* outv, int M, int N, int K,
                                                            int k_len, size_t split_stride, int mask_id, int n_tiles_out,
-                                                           int n_blocks, int n_split, int m_chunks) {
+                                                           int n_blocks, int n_split, int m_chunks, int n_slices) {
     constexpr int NW = WN * WM, KC = 64, KSTEPS = KC / 16, NB = WN * R, MT = WM * TW, ROWS = MT * 32;
     constexpr int WB = NB * KSTEPS * 1024, XB = ROWS * KC * 2, XBASE = NSW * WB;        // bytes of a stage; the activations' ring
     constexpr int WL = WB / 1024 / NW, XL = XB / 1024 / NW;                             // loads of a stage per wave
@@ -44,9 +46,11 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         bx = (t / m_chunks) % n_blocks;
         bz = t / (m_chunks * n_blocks);
     }
-    const int m0 = by * ROWS, kbeg = bz * k_len, nchunks = k_len / KC;
+    // HALF: this work-group walks one half of the n_slices k-slices, one after the other, and adds their sums
+    const int nch = k_len / KC, first = HALF ? bz * ((n_slices + 1) >> 1) : bz;
+    const int slices = HALF ? (bz == 0 ? (n_slices + 1) >> 1 : n_slices >> 1) : 1;
+    const int m0 = by * ROWS, kbeg = first * k_len, nchunks = nch * slices;
     const int KS = K >> 4, NT = N >> 5;
-    const int rot = gemm_k_start(bx * (NB * 32), bz, nchunks);
     // Load i of this wave is piece wave + NW i of a stage, 1 KB: of the n-tiles' fragments, or eight rows of the
     // activations, the 16-byte piece s of row r in slot s ^ (r / 2 % 8) of its line, so that the 32 rows of a
     // fragment spread over all LDS banks.  n-tiles and rows past the end read the last one (never stored).
@@ -57,15 +61,25 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         const int r = (wave + NW * i) * 8 + (lane >> 3), s = (lane & 7) ^ ((r >> 1) & 7);
         xoff[i] = (unsigned)(m0 + r < M ? r : M - 1 - m0) * (unsigned)(K * 2) + s * 16;
     }
-    auto issue_w = [&](int i, int slot, int at) SSD_INLINE {        // at: the chunk, rotated
+    auto issue_w = [&](int i, int slot, int at) SSD_INLINE {        // at: the chunk, counted from kbeg, rotated within its slice
         const int p = wave + NW * i, t = bx * NB + p / KSTEPS, n = t < NT ? t : NT - 1;
         load_to_lds<false>(lds0 + slot * WB + p * 1024, lane * 16, Wp + ((size_t)n * KS + (kbeg >> 4) + at * KSTEPS + p % KSTEPS) * 64);
     };
     auto issue_x = [&](int i, int slot, int at) SSD_INLINE {
         load_to_lds<false>(lds0 + XBASE + slot * XB + (wave + NW * i) * 1024, xoff[i], xrow0 + (size_t)at * (KC * 2));
     };
-    auto after = [&](int at) SSD_INLINE { return at + 1 == nchunks ? 0 : at + 1; };
-    int atx = rot, atw = rot;                            // the next chunks to load, rotated
+    struct Walk { int at, done, slice; };                // the next chunk to load: where, how many of its slice before it
+    auto begin = [&](int slice) SSD_INLINE { return slice * nch + gemm_k_start(bx * (NB * 32), first + slice, nch); };
+    auto advance = [&](Walk& w) SSD_INLINE {
+        if (HALF && ++w.done == nch) {
+            w.done = 0;
+            w.at = begin(++w.slice);
+        } else {
+            ++w.at;
+            if (w.at == (w.slice + 1) * nch) w.at -= nch;
+        }
+    };
+    Walk wx{begin(0), 0, 0}, ww = wx;
 
     floatx16 acc[R][TW];
 #pragma unroll
@@ -74,6 +88,24 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         for (int t = 0; t < TW; ++t)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[r][t][i] = 0.f;
+    floatx16 total[HALF ? R : 1][HALF ? TW : 1];         // the finished slices
+    if constexpr (HALF)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int t = 0; t < TW; ++t) total[r][t] = acc[r][t];
+    auto close = [&]() SSD_INLINE {                      // the end of a slice
+        if constexpr (HALF)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int t = 0; t < TW; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        total[r][t][i] += acc[r][t][i];
+                        acc[r][t][i] = 0.f;
+                    }
+    };
     const int sw = (lm >> 1) & 7;
     struct Frags { bf16x8 w[R], x[TW]; } fa, fb;
     auto read1 = [&](Frags& f, auto jc, int slotx, int slotw, int ks) SSD_INLINE {       // fragment j of a step: weights, then rows
@@ -97,8 +129,8 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
             constexpr int a = l0 + i * (l1 - l0) / NM, b = l0 + (i + 1) * (l1 - l0) / NM;
             static_for<a, b>([&](auto kc) SSD_INLINE {
                 constexpr int k = decltype(kc)::value;
-                if constexpr (k < XL) { if (loadx) issue_x(k, slotx, atx); }
-                else { if (loadw) issue_w(k - XL, slotw, atw); }
+                if constexpr (k < XL) { if (loadx) issue_x(k, slotx, wx.at); }
+                else { if (loadw) issue_w(k - XL, slotw, ww.at); }
             });
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -110,17 +142,17 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         if (u < nchunks) {
             if (u < NSX) {
 #pragma unroll
-                for (int i = 0; i < XL; ++i) issue_x(i, u, atx);
-                atx = after(atx);
+                for (int i = 0; i < XL; ++i) issue_x(i, u, wx.at);
+                advance(wx);
             }
 #pragma unroll
-            for (int i = 0; i < WL; ++i) issue_w(i, u, atw);
-            atw = after(atw);
+            for (int i = 0; i < WL; ++i) issue_w(i, u, ww.at);
+            advance(ww);
         }
     if (nchunks >= NSW) wait_and_meet<XL*(NSX - 1) + WL * (NSW - 1)>();
     else wait_and_meet<0>();
     static_for<0, R + TW>([&](auto jc) SSD_INLINE { read1(fa, jc, 0, 0, 0); });
-    int sx = 0, sw_ = 0;
+    int sx = 0, sw_ = 0, in_slice = 0;
     constexpr std::integral_constant<int, 0> Q0{};
     constexpr std::integral_constant<int, 1> Q1{};
     constexpr std::integral_constant<int, 2> Q2{};
@@ -137,9 +169,13 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         sx = sx + 1 == NSX ? 0 : sx + 1;
         sw_ = sw_ + 1 == NSW ? 0 : sw_ + 1;
         step(Q0, fb, fa, sx, sw_, px, pw, true, loadx, loadw);
+        if (HALF && ++in_slice == nch) {
+            close();
+            in_slice = 0;
+        }
         three_steps(px, pw, loadx, loadw);
-        atx = after(atx);
-        atw = after(atw);
+        advance(wx);
+        advance(ww);
     };
     three_steps(0, 0, false, false);
     int c = 1;
@@ -152,6 +188,7 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         period(c - 1 + NSX < nchunks, false);
     }
     step(Q0, fb, fa, 0, 0, 0, 0, false, false, false);
+    close();
     __syncthreads();                                     // the epilogue reuses the ring
 
     // ---- epilogue.  Lane (lm, lh) holds, per tile, rows n = 8*(i/4) + 4*lh + i%4 of column m = lm.
@@ -159,7 +196,7 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
         constexpr int j = decltype(ic)::value, r = j / TW, ti = j % TW;
         const int nt = bx * NB + wn * R + r, mt0 = m0 + (wm * TW + ti) * 32;
         const bool ok = nt < NT;                         // tiles and rows past the end are computed, but not stored
-        const floatx16& v = acc[r][ti];
+        const floatx16& v = HALF ? total[HALF ? r : 0][HALF ? ti : 0] : acc[r][ti];
         [[maybe_unused]] const int m = mt0 + lm;
         if constexpr (EPI == EPI_F32) {
             // through LDS into row order (4 KB per wave and parity of the tile), so that a store covers whole 128-byte
@@ -199,13 +236,14 @@ __global__ __launch_bounds__(WN* WM * 64) void k_gemm_rows(const bf16_t* X, cons
     });
 }
 
-template <int WN, int WM, int R, int TW, int EPI>
+// HALF: a work-group per half of the a.split k-slices instead of one per slice
+template <int WN, int WM, int R, int TW, int EPI, bool HALF = false>
 static bool launch_rows(const GemmArgs& a) {
     constexpr int wst = WN * R * 4, xst = WM * TW * 4;                                  // KB of a stage
     constexpr int NSX = 2 * (wst + xst) + (wst + xst) <= 160 ? (160 / (wst + xst) >= 4 ? 4 : 160 / (wst + xst)) : 2;
     constexpr int left = (160 - NSX * xst) / wst, NSW = left > 4 ? 4 : left;
     constexpr size_t smem = (size_t)(NSX * xst + NSW * wst) * 1024;
-    auto kern = k_gemm_rows<WN, WM, R, TW, EPI, NSX, NSW>;
+    auto kern = k_gemm_rows<WN, WM, R, TW, EPI, NSX, NSW, HALF>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
@@ -213,13 +251,18 @@ static bool launch_rows(const GemmArgs& a) {
         attr_done = true;
     }
     const int n_blocks = (a.N / 32 + WN * R - 1) / (WN * R), m_chunks = (a.M + WM * TW * 32 - 1) / (WM * TW * 32);
-    hipLaunchKernelGGL(kern, dim3(n_blocks * m_chunks * a.split), dim3(WN * WM * 64), smem, a.st, a.X, a.Wp, a.out, a.M, a.N, a.K,
-                       a.K / a.split, a.split_stride, a.mask_id, a.n_tiles_out, n_blocks, a.split, m_chunks);
+    const int parts = HALF ? 2 : a.split;
+    hipLaunchKernelGGL(kern, dim3(n_blocks * m_chunks * parts), dim3(WN * WM * 64), smem, a.st, a.X, a.Wp, a.out, a.M, a.N, a.K,
+                       a.K / a.split, a.split_stride, a.mask_id, a.n_tiles_out, n_blocks, parts, m_chunks, a.split);
     return true;
 }
 
 template <int EPI>
 static bool launch_tile(const GemmArgs& a, int tile) {
+    if constexpr (EPI == EPI_F32) {
+        if (tile == GEMM_HALVES_256x128) return launch_rows<2, 2, 4, 2, EPI, true>(a);
+        if (tile == GEMM_HALVES_192x128) return launch_rows<2, 2, 3, 2, EPI, true>(a);
+    }
     switch (tile) {
         case GEMM_256x256: return launch_rows<2, 2, 4, 4, EPI>(a);
         case GEMM_192x320: return launch_rows<2, 2, 3, 5, EPI>(a);

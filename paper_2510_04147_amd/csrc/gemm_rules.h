@@ -13,6 +13,8 @@ inline int gemm_full_pass(int M) {
 // The large tiles of k_gemm_rows, weight rows x activation rows.  The small ones, 256 x 96, 128 and 160, are named by their
 // 3, 4 or 5 row tiles of 32.
 enum GemmWideTile { GEMM_256x256 = 256256, GEMM_192x320 = 192320, GEMM_192x256 = 192256 };
+// Tiles that walk one half of the k-slices and add their sums, so that two partial sums leave the kernel.
+enum GemmHalvesTile { GEMM_HALVES_256x128 = 2256128, GEMM_HALVES_192x128 = 2192128 };
 
 // One of the large tiles where it is the fastest way for M rows, or 0: gemm_rows_tile() and gemm_few_row_pass() choose.
 // nch: chunks of 64 columns in a k-slice; wn: as below.
@@ -22,7 +24,7 @@ enum GemmWideTile { GEMM_256x256 = 256256, GEMM_192x320 = 192320, GEMM_192x256 =
 // 192 x 320 77 / 100, 195; 256 x 256 at 192 work-groups 89, at 512 and 768 - / - , 184 / 318).  Over the four matrices of the 8B and
 // the 7B class and the LM head, 193 to 2304 rows, the choice was within 4 % of the fastest tile but for 8 % at down, 256 rows.
 // At least 128 work-groups: fewer leave half of the chip idle, and the few-row kernel's narrower n-blocks spread better.
-inline int gemm_wide_tile(int M, int N, int nch, int split, int wn) {
+inline int gemm_wide_tile(int M, int N, int nch, int split, int wn, long long* time = nullptr) {
     if (M <= 192) return 0;
     struct Kind { int code, nt, mt, a, b; };
     static const Kind kinds[6] = {{GEMM_256x256, 8, 8, 840, 620}, {GEMM_192x320, 6, 10, 656, 750}, {GEMM_192x256, 6, 8, 625, 560},
@@ -38,7 +40,31 @@ inline int gemm_wide_tile(int M, int N, int nch, int split, int wn) {
     // the few-row kernel's passes of 160 or 192 rows
     const int mt = gemm_full_pass(M);
     const long long wgs = (long long)((N / 32 + wn - 1) / wn) * split * ((M + mt * 32 - 1) / (mt * 32));
-    if (wgs >= 256 && (wgs + 255) / 256 * (4000 + (long long)nch * (mt == 6 ? 630 : 560)) * wn / 3 < best_time) return 0;
+    const long long few = (wgs + 255) / 256 * (4000 + (long long)nch * (mt == 6 ? 630 : 560)) * wn / 3;
+    if (wgs >= 256 && few < best_time) { best = 0; best_time = few; }
+    if (time) *time = best_time;
+    return best;
+}
+
+// One of the tiles that walk half of the k-slices (fp32 partial sums only), or 0.  They hold two accumulators per output, so the
+// tile is half as large and the kernel alone no faster (8B down, 1000 rows 97 us in eight slices / 102 in halves; 640 rows 70 /
+// 75; 7B class down, 2304 rows 278 / 292); what they save is the other partial sums: 0.08 us to write and 0.16 us to read
+// per MB each (norm of 1000 rows x 4096: 26 us with eight, 11 with two).  Time of a launch as above, with ns of their own.
+inline int gemm_halves_tile(int M, int N, int nch, int split, int wn) {
+    if (M <= 192 || split <= 2) return 0;
+    struct Kind { int code, nt, mt, a, b; };
+    static const Kind kinds[2] = {{GEMM_HALVES_256x128, 8, 4, 750, 250}, {GEMM_HALVES_192x128, 6, 4, 550, 170}};
+    const long long fixed = 6000, kb = (long long)M * N * 4 / 1000, chunks = (long long)nch * ((split + 1) / 2);
+    long long best_time = -1;
+    gemm_wide_tile(M, N, nch, split, wn, &best_time);
+    if (best_time < 0) return 0;
+    best_time += split * kb * 24 / 100;
+    int best = 0;
+    for (const Kind& k : kinds) {
+        const long long wgs = (long long)((N / 32 + k.nt - 1) / k.nt) * 2 * ((M + k.mt * 32 - 1) / (k.mt * 32));
+        const long long t = (wgs + 255) / 256 * (fixed + chunks * k.a) + wgs * chunks * k.b / 256 + 2 * kb * 16 / 100;
+        if (wgs >= 128 && t < best_time) { best = k.code; best_time = t; }
+    }
     return best;
 }
 

@@ -123,7 +123,7 @@ __device__ __forceinline__ void merge_factors(float ma, float mb, float& m, floa
 __device__ __forceinline__ float merge2(float a, float ca, float b, float cb) { return __fmaf_rn(b, cb, __fmul_rn(a, ca)); }
 
 // FUSED: the kernel starts from the QKV projection's fp32 partial sums instead of ready q / k / v: it
-// adds the partial sums in split order, applies the rotary embedding to its head's queries and to
+// adds the partial sums by halves, applies the rotary embedding to its head's queries and to
 // the node's own keys and keeps the own key / value tile in LDS in fragment order.  For forwards whose
 // nodes have at most 32 rows (one query tile) and append nothing to the cache, head size 128.
 // SHARED: four waves, each of which walks two strands one after the other (the first one's result waits in LDS), so that
@@ -255,26 +255,33 @@ __global__ __launch_bounds__(SHARED ? 256 : 512, 2) void k_attn_mfma(const FwdHe
         const int nkv = Hkv * DH, nqkv = nq + 2 * nkv;
         const float* src = part + (size_t)row * nqkv;
         const int i0 = cg * 4;
-        // two splits of all six column groups in flight at once, added in split order: one wait on the far memory the
+        // two splits of all six column groups in flight at once: one wait on the far memory the
         // other XCDs' sums come from instead of one per group and split (40 rows of the 8B shape 12.7 -> 11.8 us, 4
         // sequences x 160 rows 62.8 -> 60.5; four splits, 2304 rows of the 7B class 136 -> 115)
         const int col[6] = {head * DH + i0, head * DH + HALF + i0, nq + kvh * DH + i0, nq + kvh * DH + HALF + i0,
                             nq + nkv + kvh * DH + cg * 8, nq + nkv + kvh * DH + cg * 8 + 4};
         const float4 c4 = *(const float4*)(cosT + (size_t)pos * HALF + i0), s4 = *(const float4*)(sinT + (size_t)pos * HALF + i0);
         float4 x[6], y[6];
-        auto add = [&]() {
+        auto get = [&](float4(&v)[6], int sp) SSD_INLINE {
 #pragma unroll
-            for (int i = 0; i < 6; ++i) { x[i].x += y[i].x; x[i].y += y[i].y; x[i].z += y[i].z; x[i].w += y[i].w; }
+            for (int i = 0; i < 6; ++i) v[i] = *(const float4*)(src + sp * part_stride + col[i]);
         };
+        auto add = [&](float4(&v)[6], const float4(&w)[6]) SSD_INLINE {
 #pragma unroll
-        for (int i = 0; i < 6; ++i) x[i] = *(const float4*)(src + col[i]);
-        if (n_part > 1) {
-            for (int sp = 1;; ++sp) {
-#pragma unroll
-                for (int i = 0; i < 6; ++i) y[i] = *(const float4*)(src + sp * part_stride + col[i]);
-                add();
-                if (sp + 1 >= n_part) break;
-            }
+            for (int i = 0; i < 6; ++i) { v[i].x += w[i].x; v[i].y += w[i].y; v[i].z += w[i].z; v[i].w += w[i].w; }
+        };
+        // the first half of the partial sums, then the second half's sum
+        get(x, 0);
+        if (n_part == 2) {
+            get(y, 1);
+            add(x, y);
+        } else if (n_part > 1) {
+            const int half = (n_part + 1) >> 1;
+            float4 z[6];
+            for (int sp = 1; sp < half; ++sp) { get(y, sp); add(x, y); }
+            get(y, half);
+            for (int sp = half + 1; sp < n_part; ++sp) { get(z, sp); add(y, z); }
+            add(x, y);
         }
         const float qa[4] = {x[0].x, x[0].y, x[0].z, x[0].w}, qb[4] = {x[1].x, x[1].y, x[1].z, x[1].w};
         const float ka[4] = {x[2].x, x[2].y, x[2].z, x[2].w}, kb[4] = {x[3].x, x[3].y, x[3].z, x[3].w};

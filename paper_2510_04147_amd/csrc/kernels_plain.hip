@@ -67,7 +67,8 @@ __device__ __forceinline__ int rank_among(float c, unsigned long long set, int l
     return rank;
 }
 
-// a2/a6/a9: h += sum of split-K partial sums (fixed order s = 0, 1, ...), then RMSNorm.
+// a2/a6/a9: h += split-K partial sums (the sum of the first half of them, then the second's: a GEMM that walks half of the
+// slices itself leaves two), then RMSNorm.
 // One work-group of NORM_T threads per row; every thread owns up to NORM_J float4 groups of the
 // row and issues all partial-sum loads of a group before the first add, so a 4096-wide row has
 // its whole input (the row and every partial sum) in flight at once.
@@ -94,9 +95,20 @@ __device__ __forceinline__ void norm_row(float* hr, const float* pr, size_t part
             float4 pv[NP > 0 ? NP : 1];
 #pragma unroll
             for (int s = 0; s < NP; ++s) pv[s] = ((const float4*)(pr + s * part_stride))[i4];
+            // the sum of the first half of them, then the second's
+            constexpr int HALF = (NP + 1) / 2;
+            auto add = [](float4& x, const float4& y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+            if constexpr (NP > 0) {
+                float4 t = pv[0];
 #pragma unroll
-            for (int s = 0; s < NP; ++s) {
-                v[j].x += pv[s].x; v[j].y += pv[s].y; v[j].z += pv[s].z; v[j].w += pv[s].w;
+                for (int s = 1; s < HALF; ++s) add(t, pv[s]);
+                add(v[j], t);
+            }
+            if constexpr (NP > 1) {
+                float4 t = pv[HALF];
+#pragma unroll
+                for (int s = HALF + 1; s < NP; ++s) add(t, pv[s]);
+                add(v[j], t);
             }
             if (NP != 0) ((float4*)hr)[i4] = v[j];
             ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
@@ -134,10 +146,15 @@ __global__ __launch_bounds__(NORM_T) void k_norm(float* __restrict__ h, const fl
         case 4: norm_row<T, 4>(hr, pr, part_stride, gain, xr, d, eps); break;
         case 8: norm_row<T, 8>(hr, pr, part_stride, gain, xr, d, eps); break;
         default: {
-            // any other split count: fold the partial sums into h first, in order
+            // any other split count: fold the partial sums into h first, by halves
             for (int i = threadIdx.x; i < d; i += NORM_T) {
                 float v = hr[i];
-                for (int s = 0; s < n_part; ++s) v += pr[s * part_stride + i];
+                const int half = (n_part + 1) >> 1;
+                for (int s = 0; s < n_part; s = s == 0 && n_part > 1 ? half : n_part) {
+                    float t = pr[s * part_stride + i];
+                    for (int u = s + 1; u < (s == 0 ? half : n_part); ++u) t += pr[u * part_stride + i];
+                    v += t;
+                }
                 hr[i] = v;
             }
             __syncthreads();
@@ -231,7 +248,7 @@ __global__ __launch_bounds__(EMBED ? NORM_T : 64) void k_rows(const FwdHeader* _
 }
 
 // Rotary embedding (rotate-half pairing) of Q and K from the fp32 projection (the sum of its
-// split-K partial sums, in split order), conversion to the operand type, the fragment-order copies
+// split-K partial sums, by halves), conversion to the operand type, the fragment-order copies
 // of the nodes' own keys and values, and the cache write for nodes that own finished tokens.
 // One work-group per (node, 32-row tile, head of Q, K or V): 32 rows x 8 column groups.  Bound by the partial sums'
 // bytes; with a split's loads in flight together and the cached values written four positions at a time
@@ -255,17 +272,26 @@ __global__ __launch_bounds__(256) void k_rope(const FwdHeader* __restrict__ fw, 
     const int nq = Hq * DH, nkv = Hkv * DH, nqkv = nq + 2 * nkv;
     const float* src = part + (size_t)row * nqkv;
     const size_t cbase = (((size_t)layer * max_seqs + nd.seq) * Hkv) * (size_t)seq_stride * DH;
-    // G groups of four values, group j from column col[j], added in split order; a split's groups are in flight together
+    // G groups of four values, group j from column col[j], partial sums added by halves; a split's groups are in flight together
     auto load = [&](auto gc, const int* col, float* dst) {
         constexpr int G = decltype(gc)::value;
-        float4 a[G], b[G];
+        float4 a[G], b[G], t[G];
+        auto add = [&](float4& x, const float4& y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+        const int half = (n_part + 1) >> 1;
 #pragma unroll
         for (int j = 0; j < G; ++j) a[j] = *(const float4*)(src + col[j]);
         for (int sp = 1; sp < n_part; ++sp) {
 #pragma unroll
             for (int j = 0; j < G; ++j) b[j] = *(const float4*)(src + sp * part_stride + col[j]);
 #pragma unroll
-            for (int j = 0; j < G; ++j) { a[j].x += b[j].x; a[j].y += b[j].y; a[j].z += b[j].z; a[j].w += b[j].w; }
+            for (int j = 0; j < G; ++j) {
+                if (sp == half) { t[j] = a[j]; a[j] = b[j]; }
+                else add(a[j], b[j]);
+            }
+        }
+        if (n_part > 1) {
+#pragma unroll
+            for (int j = 0; j < G; ++j) { add(t[j], a[j]); a[j] = t[j]; }
         }
 #pragma unroll
         for (int j = 0; j < G; ++j) { dst[4 * j] = a[j].x; dst[4 * j + 1] = a[j].y; dst[4 * j + 2] = a[j].z; dst[4 * j + 3] = a[j].w; }
@@ -1092,8 +1118,14 @@ __global__ void k_sum_partials(const float* __restrict__ part, int n_part, size_
                                size_t n) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    float v = part[i];
-    for (int s = 1; s < n_part; ++s) v += part[s * part_stride + i];
+    const int half = (n_part + 1) >> 1;
+    float v = part[i], u = 0.f;
+    for (int s = 1; s < half; ++s) v += part[s * part_stride + i];
+    if (half < n_part) {
+        u = part[half * part_stride + i];
+        for (int s = half + 1; s < n_part; ++s) u += part[s * part_stride + i];
+        v += u;
+    }
     out[i] = v;
 }
 

@@ -436,7 +436,7 @@ struct Upload {           // block state to push before the forward (stateless A
     SeqState st;
 };
 
-// out = X * W^T.  EPI_F32 writes *n_split partial sums (the consumer adds them in order);
+// out = X * W^T.  EPI_F32 writes *n_split partial sums (the consumer adds them by halves);
 // EPI_SWIGLU treats W as [gate; up] and writes silu(gate)*up; EPI_LMHEAD writes *n_split
 // per-tile (max, arg, sumexp) triples per row.
 static void gemm(ssd_ctx* c, int cls, int epi, const void* X, const Wt& W, void* out, int M, int* n_split) {

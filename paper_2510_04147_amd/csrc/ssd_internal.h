@@ -141,7 +141,7 @@ struct Buffers {
     void* attn;          // [max_rows, nq] T
     void* act;           // [max_rows, F] T
     float* part;         // [SSD_MAX_SPLIT, max_rows, max(d, nqkv)] fp32 split-K partial sums of the
-                         // QKV, O and down projections (summed in order by the consumer)
+                         // QKV, O and down projections (summed by the consumer: the first half of them in order, the second half, then both)
     void* packed;        // fragment-order copies of the weights (bf16 models)
     float* lm_part;      // [max_rows, n_vtiles, 3] (max, arg as float bits, sumexp)
     float* row_max;      // [max_rows]
@@ -252,7 +252,7 @@ void launch_lm_merge(const ssd_ctx* c, int M, int n_tiles, hipStream_t st);
 void launch_lm_merge_to(const ssd_ctx* c, int M, int n_tiles, const float* part, float* row_max, int* row_arg,
                         float* row_conf, hipStream_t st);
 int lm_tiles_plain(int V);
-// out[M,N] = sum over the first n_part split-K partial buffers, in split order
+// out[M,N] = sum over the first n_part split-K partial buffers, by halves
 void launch_sum_partials(const ssd_ctx* c, int M, int N, int n_part, float* out, hipStream_t st);
 void launch_int_to_float(const int* src, float* dst, int n, hipStream_t st);
 // kernel-level entry points: caller-supplied keys / values into the cache; a forward's own keys / values back out
