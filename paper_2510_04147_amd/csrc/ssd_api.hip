@@ -505,10 +505,11 @@ static int run_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int 
         HIPCHK(c, hipGetLastError());
         return SSD_OK;
     }
-    int max_blen = 0;
+    int max_blen = 0, head_nodes = 0, head_blen = 0;     // head: the nodes whose rows get logits, the first ones
     bool any_write_kv = false, any_suffix = false;
     for (int i = 0; i < hd.n_nodes; ++i) {
         max_blen = std::max(max_blen, hd.nodes[i].blen);
+        if (hd.nodes[i].row0 < ML) { head_nodes = i + 1; head_blen = max_blen; }
         any_write_kv |= hd.nodes[i].write_kv != 0;
         any_suffix |= hd.nodes[i].T > hd.nodes[i].S + hd.nodes[i].blen;
     }
@@ -536,7 +537,7 @@ static int run_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int 
         if (uniform) nodes_per_seq = first_run;
     }
 
-    // ---- the kernel sequence: a function of (M, ML, n_nodes, n_groups, max_blen, kernel path) only
+    // ---- the kernel sequence: a function of (M, ML, n_nodes, n_groups, max_blen, head_nodes, head_blen, kernel path) only
     auto launch_all = [&]() {
         {
             ProfScope ps(c, KC_ROWS);
@@ -557,16 +558,20 @@ static int run_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int 
                                attn_mfma_can_fuse_rope(c, max_blen);
             if (!fused) { ProfScope ps(c, KC_ROPE); launch_rope(c, hd.n_nodes, max_blen, l, ns, st); }
             if (last_kv_only) break;
+            // behind the last layer's keys and values only the rows that get logits go on (a refresh of 512 rows of the 8B
+            // shape with a block of 8: 200 of its 9000 us are the other rows' share of that layer)
+            const bool head = l == d.L - 1;
+            const int R = head ? ML : M, nodes = head ? head_nodes : hd.n_nodes, blen = head ? head_blen : max_blen;
             {
                 ProfScope ps(c, KC_ATTN);
                 if (!(c->kernel_path >= 1 && d.dtype == SSD_BF16 &&
-                      launch_attn_mfma(c, hd.n_nodes, nodes_per_seq, max_blen, l, fused ? ns : -1, any_suffix, st)))
-                    launch_attn_plain(c, M, l, st);
+                      launch_attn_mfma(c, nodes, nodes_per_seq, blen, l, fused ? ns : -1, any_suffix, st)))
+                    launch_attn_plain(c, R, l, st);
             }
-            gemm(c, KC_GEMM_O, EPI_F32, c->b.attn, w.wo, c->b.part, M, &ns);
-            { ProfScope ps(c, KC_NORM); launch_norm(c, M, w.norm2, ns, st); }
-            gemm(c, KC_GEMM_GU, EPI_SWIGLU, c->b.xn, w.wgu, c->b.act, M, &ns);
-            gemm(c, KC_GEMM_DOWN, EPI_F32, c->b.act, w.wdown, c->b.part, M, &ns);
+            gemm(c, KC_GEMM_O, EPI_F32, c->b.attn, w.wo, c->b.part, R, &ns);
+            { ProfScope ps(c, KC_NORM); launch_norm(c, R, w.norm2, ns, st); }
+            gemm(c, KC_GEMM_GU, EPI_SWIGLU, c->b.xn, w.wgu, c->b.act, R, &ns);
+            gemm(c, KC_GEMM_DOWN, EPI_F32, c->b.act, w.wdown, c->b.part, R, &ns);
             n_part = ns;
         }
         if (ML > 0) {
@@ -583,9 +588,10 @@ static int run_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int 
     if (c->use_graphs && !c->profiling && st != nullptr) {      // the legacy default stream cannot be captured
         for (auto& g : c->graphs)
             if (g.M == M && g.ML == ML && g.n_nodes == hd.n_nodes && g.n_groups == hd.n_groups &&
-                g.max_blen == max_blen && g.kernel_path == c->kernel_path && g.flags == gflags) { fg = &g; break; }
+                g.max_blen == max_blen && g.head_nodes == head_nodes && g.head_blen == head_blen &&
+                g.kernel_path == c->kernel_path && g.flags == gflags) { fg = &g; break; }
         if (!fg && c->graphs.size() < 64) {
-            c->graphs.push_back({M, ML, hd.n_nodes, hd.n_groups, max_blen, c->kernel_path, gflags, 0, nullptr});
+            c->graphs.push_back({M, ML, hd.n_nodes, hd.n_groups, max_blen, head_nodes, head_blen, c->kernel_path, gflags, 0, nullptr});
             fg = &c->graphs.back();
         }
     }

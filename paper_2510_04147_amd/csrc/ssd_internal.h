@@ -197,7 +197,7 @@ struct ssd_ctx {
     // device memory, so a shape's second forward is captured and later ones replay the graph.
     int use_graphs;
     struct FwdGraph {
-        int M, ML, n_nodes, n_groups, max_blen, kernel_path;
+        int M, ML, n_nodes, n_groups, max_blen, head_nodes, head_blen, kernel_path;
         int flags;       // bit 0: some node appends KV, bit 1: some node reads a cached suffix (other kernels), bit 2: results to the host
         int seen;
         hipGraphExec_t exec;
