@@ -193,7 +193,7 @@ __global__ __launch_bounds__(1024) void k_stage(const int* __restrict__ src, Sta
 // ------------------------------------------------------------------------
 template <typename T, bool EMBED>
 __global__ __launch_bounds__(EMBED ? NORM_T : 64) void k_rows(const FwdHeader* __restrict__ fw, int n_nodes, const SeqState* __restrict__ state,
-                                                             const int* __restrict__ raw_tok, int* __restrict__ row_node,
+                                                             const int* __restrict__ raw_tok, NodeDesc* __restrict__ row_desc,
                                                              int* __restrict__ out_tok, int mask_id, int max_seq_len,
                                                              const float* __restrict__ ref_conf, const int* __restrict__ ref_arg,
                                                              const T* __restrict__ embed, float* __restrict__ h,
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(EMBED ? NORM_T : 64) void k_rows(const FwdHeader* _
             if (in) tok = __builtin_amdgcn_readlane(dtok, 63 - __clzll(in));
         }
         if (threadIdx.x == 0) {
-            row_node[row] = ni;
+            row_desc[row] = nd;
             sh_tok = tok;
         }
     }
@@ -380,107 +380,133 @@ __global__ __launch_bounds__(256) void k_rope(const FwdHeader* __restrict__ fw, 
 // a4 (plain): one wave per (row, query head).  Keys = the sequence's cached
 // prefix [0,S), its cached suffix behind the block if it has one, then the node's own rows; online softmax in fp32 over
 // key tiles of 64 in position order.  Bound by latency: keys and values are read 16 bytes per lane (a row's chain of
-// FMAs stays in channel and key order) with a tile's loads in flight together.  64 cached keys and a block of 32, head
-// size 64, 4 heads: 26 -> 8.2 us.
-template <typename T>
-__global__ __launch_bounds__(64) void k_attn_plain(const FwdHeader* __restrict__ fw, const int* __restrict__ row_node,
-                                                   const T* __restrict__ q, const T* __restrict__ kown,
-                                                   const T* __restrict__ vown, const T* __restrict__ kcache,
-                                                   const T* __restrict__ vcache, T* __restrict__ out, int Hq,
-                                                   int Hkv, int dh, int layer, int max_seqs, int seq_stride,
-                                                   int vt_rows) {
+// FMAs stays in channel and key order), a tile's values and the next tile's keys in flight while its scores are computed, and the
+// row's descriptor lies ready (64 cached keys and a block of 32, head size 64, 4 heads, us, node looked up by two trips,
+// keys and values one trip after the other / this: 7.5 / 5.4).
+template <typename T, int DH>
+__global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ row_desc, const T* __restrict__ q,
+                                                   const T* __restrict__ kown, const T* __restrict__ vown,
+                                                   const T* __restrict__ kcache, const T* __restrict__ vcache,
+                                                   T* __restrict__ out, int Hq, int Hkv, int layer, int max_seqs,
+                                                   int seq_stride, int vt_rows) {
+    constexpr int CH = DH / 64;                              // channels per lane: lane, lane + 64
     const int row = blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
-    const NodeDesc nd = fw->nodes[row_node[row]];
-    const int kvh = head / (Hq / Hkv);
-    const int nq = Hq * dh;
-    __shared__ __attribute__((aligned(16))) float qs[128];
-    for (int i = lane; i < dh; i += 64) qs[i] = ld_f(q + (size_t)row * nq + head * dh + i);
+    __shared__ __attribute__((aligned(16))) float qs[DH];
+    const int kvh = head / (Hq / Hkv), nq = Hq * DH;
+    float q0[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) q0[c] = ld_f(q + (size_t)row * nq + head * DH + c * 64 + lane);
+    const NodeDesc nd = row_desc[row];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) qs[c * 64 + lane] = q0[c];
     __syncthreads();
-    const size_t cbase = ((((size_t)layer * max_seqs + nd.seq) * Hkv) + kvh) * (size_t)seq_stride * dh;
+    const size_t cbase = ((((size_t)layer * max_seqs + nd.seq) * Hkv) + kvh) * (size_t)seq_stride * DH;
     const T* kc = kcache + cbase;
     const T* vc = vcache + cbase;
-    const T* ko = kown + (size_t)kvh * vt_rows * dh;
-    const T* vo = vown + (size_t)kvh * vt_rows * dh;
+    const T* ko = kown + (size_t)kvh * vt_rows * DH;
+    const T* vo = vown + (size_t)kvh * vt_rows * DH;
     // keys: the cached prefix [0, S), the cached suffix [S + blen, T) if the sequence has one, the node's own rows
     const int n_suf = max(nd.T - (nd.S + nd.blen), 0), n_cache = nd.S + n_suf;
     const int n_keys = n_cache + nd.blen;
     auto cache_pos = [&](int j) { return j < nd.S ? j : j + nd.blen; };
-    const float scale = 1.0f / sqrtf((float)dh);
-    float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
+    auto load_k = [&](float4(&kv)[DH / 4], int t0) __attribute__((always_inline)) {
+        const int j = min(t0 + lane, n_keys - 1);            // past the last key: that one, not counted
+        const bool pre = j < n_cache;
+        const T* kp = pre ? kc : ko;
+        const int p = pre ? cache_pos(j) : nd.vrow0 + j - n_cache;
+#pragma unroll
+        for (int i = 0; i < DH / 4; ++i) kv[i] = ld4_f(kp + kfrag_off(p, i * 4, DH));
+    };
+    // where key jk lies, and how many keys from it on lie at consecutive positions (uniform over the wave)
+    auto place = [&](int jk, int end, const T*& vp, int& pp) __attribute__((always_inline)) {
+        const bool pre = jk < n_cache;
+        vp = pre ? vc : vo;
+        pp = pre ? cache_pos(jk) : nd.vrow0 + jk - n_cache;
+        return min(end - jk, jk < nd.S ? nd.S - jk : pre ? n_cache - jk : n_keys - jk);
+    };
+    // 32 keys at consecutive positions from a multiple of four on: four of a channel lie together
+    auto load_v = [&](float4(&v)[8][CH], int jk, int end) __attribute__((always_inline)) {
+        if (jk >= end) return false;
+        const T* vp;
+        int pp;
+        if (place(jk, end, vp, pp) < 32 || (pp & 3)) return false;
+#pragma unroll
+        for (int g = 0; g < 8; ++g)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) v[g][c] = ld4_f(vp + vfrag_off(pp + 4 * g, c * 64 + lane, DH));
+        return true;
+    };
+    const float scale = 1.0f / sqrtf((float)DH);
+    float m = -INFINITY, l = 0.f, o[CH] = {};
+    constexpr bool AHEAD = DH == 64;                         // 128 channels: no registers for the next tile's keys
+    float4 kv[DH / 4], kn[AHEAD ? DH / 4 : 1], va[8][CH], vb[8][CH];
+    load_k(kv, 0);
     for (int t0 = 0; t0 < n_keys; t0 += 64) {
+        const int end = min(t0 + 64, n_keys);
+        const bool fast_a = load_v(va, t0, end), fast_b = load_v(vb, t0 + 32, end);
+        if constexpr (AHEAD)
+            if (t0 + 64 < n_keys) load_k(kn, t0 + 64);
         const int j = t0 + lane;
-        float s = -INFINITY;
-        if (j < n_keys) {
-            const bool pre = j < n_cache;
-            const T* kp = pre ? kc : ko;
-            const int p = pre ? cache_pos(j) : nd.vrow0 + j - n_cache;
-            float acc = 0.f;
-            for (int i0 = 0; i0 < dh; i0 += 64) {            // eight consecutive channels lie together; all 64 in flight
-                float4 kv[16];
+        float acc = 0.f;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) kv[i] = ld4_f(kp + kfrag_off(p, i0 + i * 4, dh));
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float4 qv = *(const float4*)&qs[i0 + i * 4];
-                    acc += qv.x * kv[i].x; acc += qv.y * kv[i].y; acc += qv.z * kv[i].z; acc += qv.w * kv[i].w;
-                }
-            }
-            s = acc * scale;
+        for (int i = 0; i < DH / 4; ++i) {
+            const float4 qv = *(const float4*)&qs[i * 4];
+            acc += qv.x * kv[i].x; acc += qv.y * kv[i].y; acc += qv.z * kv[i].z; acc += qv.w * kv[i].w;
         }
+        const float s = j < n_keys ? acc * scale : -INFINITY;
         const float m_new = fmaxf(m, wave_max(s));
         const float p = j < n_keys ? expf(s - m_new) : 0.f;
         const float corr = expf(m - m_new);
         l = l * corr + wave_sum(p);
-        o0 *= corr;
-        o1 *= corr;
-        const int cnt = min(64, n_keys - t0);
-        auto weight = [&](int jj) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), jj)); };
-        int jj = 0;
-        while (jj < cnt) {
-            const int jk = t0 + jj;                          // uniform over the wave, like everything it decides
-            const bool pre = jk < n_cache;
-            const T* vp = pre ? vc : vo;
-            const int pp = pre ? cache_pos(jk) : nd.vrow0 + jk - n_cache;
-            // keys from here on that stay in this run of consecutive positions
-            const int run = min(cnt - jj, jk < nd.S ? nd.S - jk : pre ? n_cache - jk : n_keys - jk);
-            if (run >= 32 && (pp & 3) == 0) {                // four consecutive positions of a channel lie together
-                float4 a[8], b[8];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) o[c] *= corr;
+        auto weight = [&](int jj) { return lane_value(p, jj); };
+        auto half = [&](const float4(&v)[8][CH], bool fast, int jj0) __attribute__((always_inline)) {
+            if (fast) {
 #pragma unroll
                 for (int g = 0; g < 8; ++g) {
-                    a[g] = ld4_f(vp + vfrag_off(pp + 4 * g, lane, dh));
-                    if (dh > 64) b[g] = ld4_f(vp + vfrag_off(pp + 4 * g, lane + 64, dh));
-                }
+                    const float w0 = weight(jj0 + 4 * g), w1 = weight(jj0 + 4 * g + 1), w2 = weight(jj0 + 4 * g + 2), w3 = weight(jj0 + 4 * g + 3);
 #pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    const float w0 = weight(jj + 4 * g), w1 = weight(jj + 4 * g + 1), w2 = weight(jj + 4 * g + 2), w3 = weight(jj + 4 * g + 3);
-                    o0 += w0 * a[g].x; o0 += w1 * a[g].y; o0 += w2 * a[g].z; o0 += w3 * a[g].w;
-                    if (dh > 64) { o1 += w0 * b[g].x; o1 += w1 * b[g].y; o1 += w2 * b[g].z; o1 += w3 * b[g].w; }
+                    for (int c = 0; c < CH; ++c) { o[c] += w0 * v[g][c].x; o[c] += w1 * v[g][c].y; o[c] += w2 * v[g][c].z; o[c] += w3 * v[g][c].w; }
                 }
-                jj += 32;
-            } else if (run >= 8) {
-                float a[8], b[8];
-#pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    a[g] = ld_f(vp + vfrag_off(pp + g, lane, dh));
-                    if (dh > 64) b[g] = ld_f(vp + vfrag_off(pp + g, lane + 64, dh));
-                }
-#pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    o0 += weight(jj + g) * a[g];
-                    if (dh > 64) o1 += weight(jj + g) * b[g];
-                }
-                jj += 8;
-            } else {
-                o0 += weight(jj) * ld_f(vp + vfrag_off(pp, lane, dh));
-                if (dh > 64) o1 += weight(jj) * ld_f(vp + vfrag_off(pp, lane + 64, dh));
-                ++jj;
+                return;
             }
-        }
+            const int stop = min(t0 + jj0 + 32, n_keys) - t0;
+            int jj = jj0;
+            while (jj < stop) {
+                const T* vp;
+                int pp;
+                if (place(t0 + jj, t0 + stop, vp, pp) >= 8) {
+                    float a[8][CH];
+#pragma unroll
+                    for (int g = 0; g < 8; ++g)
+#pragma unroll
+                        for (int c = 0; c < CH; ++c) a[g][c] = ld_f(vp + vfrag_off(pp + g, c * 64 + lane, DH));
+#pragma unroll
+                    for (int g = 0; g < 8; ++g)
+#pragma unroll
+                        for (int c = 0; c < CH; ++c) o[c] += weight(jj + g) * a[g][c];
+                    jj += 8;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) o[c] += weight(jj) * ld_f(vp + vfrag_off(pp, c * 64 + lane, DH));
+                    ++jj;
+                }
+            }
+        };
+        half(va, fast_a, 0);
+        half(vb, fast_b, 32);
         m = m_new;
+        if (t0 + 64 < n_keys) {
+            if constexpr (AHEAD)
+#pragma unroll
+                for (int i = 0; i < DH / 4; ++i) kv[i] = kn[i];
+            else load_k(kv, t0 + 64);
+        }
     }
-    T* op = out + (size_t)row * nq + head * dh;
-    st_f(op + lane, o0 / l);
-    if (dh > 64) st_f(op + lane + 64, o1 / l);
+    T* op = out + (size_t)row * nq + head * DH;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) st_f(op + c * 64 + lane, o[c] / l);
 }
 
 // ------------------------------------------------------------------------
@@ -1010,7 +1036,7 @@ void launch_stage(const ssd_ctx* c, const void* pinned, const StageLayout& lay, 
 
 template <typename T, bool EMBED>
 static void rows_t(const ssd_ctx* c, int M, int n_nodes, const float* gain, hipStream_t st) {
-    k_rows<T, EMBED><<<M, EMBED ? NORM_T : 64, 0, st>>>(c->b.fwd, n_nodes, c->b.state, c->b.raw_tok, c->b.row_node, c->b.out_tok,
+    k_rows<T, EMBED><<<M, EMBED ? NORM_T : 64, 0, st>>>(c->b.fwd, n_nodes, c->b.state, c->b.raw_tok, c->b.row_desc, c->b.out_tok,
                                                        c->dm.mask_id, c->dm.max_seq_len, c->b.ref_conf, c->b.ref_arg,
                                                        (const T*)c->embed, c->b.h, gain, (T*)c->b.xn, c->dm.d, c->dm.V, c->dm.eps);
 }
@@ -1046,21 +1072,22 @@ void launch_rope(const ssd_ctx* c, int n_nodes, int max_blen, int layer, int n_p
 #undef SSD_ROPE_ARGS
 }
 
-void launch_attn_plain(const ssd_ctx* c, int M, int layer, hipStream_t st) {
+template <typename T>
+static void attn_plain_t(const ssd_ctx* c, int M, int layer, hipStream_t st) {
     const Dims& d = c->dm;
-    dim3 grid(M, d.Hq);
-    if (d.dtype == SSD_F32)
-        k_attn_plain<float><<<grid, 64, 0, st>>>(c->b.fwd, c->b.row_node, (const float*)c->b.q,
-                                                 (const float*)c->b.kown, (const float*)c->b.vown,
-                                                 (const float*)c->b.kcache, (const float*)c->b.vcache,
-                                                 (float*)c->b.attn, d.Hq, d.Hkv, d.dh, layer, d.max_seqs,
-                                                 d.seq_stride(), d.vt_rows());
-    else
-        k_attn_plain<bf16_t><<<grid, 64, 0, st>>>(c->b.fwd, c->b.row_node, (const bf16_t*)c->b.q,
-                                                  (const bf16_t*)c->b.kown, (const bf16_t*)c->b.vown,
-                                                  (const bf16_t*)c->b.kcache, (const bf16_t*)c->b.vcache,
-                                                  (bf16_t*)c->b.attn, d.Hq, d.Hkv, d.dh, layer, d.max_seqs,
-                                                  d.seq_stride(), d.vt_rows());
+    const dim3 grid(M, d.Hq);
+    auto run = [&](auto dh) {
+        k_attn_plain<T, decltype(dh)::value><<<grid, 64, 0, st>>>(c->b.row_desc, (const T*)c->b.q, (const T*)c->b.kown, (const T*)c->b.vown,
+                                                                  (const T*)c->b.kcache, (const T*)c->b.vcache, (T*)c->b.attn, d.Hq, d.Hkv,
+                                                                  layer, d.max_seqs, d.seq_stride(), d.vt_rows());
+    };
+    if (d.dh == 128) run(std::integral_constant<int, 128>{});
+    else run(std::integral_constant<int, 64>{});
+}
+
+void launch_attn_plain(const ssd_ctx* c, int M, int layer, hipStream_t st) {
+    if (c->dm.dtype == SSD_F32) attn_plain_t<float>(c, M, layer, st);
+    else attn_plain_t<bf16_t>(c, M, layer, st);
 }
 
 template <typename T>
@@ -1189,11 +1216,11 @@ void launch_write_cache(const ssd_ctx* c, int seq, int layer, int pos0, int n, c
 
 // The nodes' own keys and values of a forward, from fragment order back to row-major [M, Hkv, dh].
 template <typename T>
-__global__ void k_read_own_kv(const FwdHeader* __restrict__ fw, const int* __restrict__ row_node,
+__global__ void k_read_own_kv(const NodeDesc* __restrict__ row_desc,
                               const T* __restrict__ kown, const T* __restrict__ vown, T* __restrict__ k,
                               T* __restrict__ v, int Hkv, int dh, int vt_rows) {
     const int row = blockIdx.x, kvh = blockIdx.y;
-    const NodeDesc nd = fw->nodes[row_node[row]];
+    const NodeDesc nd = row_desc[row];
     const int prow = nd.vrow0 + (row - nd.row0);
     const size_t hb = (size_t)kvh * vt_rows * dh;
     for (int ch = threadIdx.x; ch < dh; ch += blockDim.x) {
@@ -1207,10 +1234,10 @@ void launch_read_own_kv(const ssd_ctx* c, int M, void* k, void* v, hipStream_t s
     const Dims& d = c->dm;
     dim3 grid(M, d.Hkv);
     if (d.dtype == SSD_F32)
-        k_read_own_kv<float><<<grid, 128, 0, st>>>(c->b.fwd, c->b.row_node, (const float*)c->b.kown, (const float*)c->b.vown,
+        k_read_own_kv<float><<<grid, 128, 0, st>>>(c->b.row_desc, (const float*)c->b.kown, (const float*)c->b.vown,
                                                    (float*)k, (float*)v, d.Hkv, d.dh, d.vt_rows());
     else
-        k_read_own_kv<bf16_t><<<grid, 128, 0, st>>>(c->b.fwd, c->b.row_node, (const bf16_t*)c->b.kown,
+        k_read_own_kv<bf16_t><<<grid, 128, 0, st>>>(c->b.row_desc, (const bf16_t*)c->b.kown,
                                                     (const bf16_t*)c->b.vown, (bf16_t*)k, (bf16_t*)v, d.Hkv, d.dh, d.vt_rows());
 }
 

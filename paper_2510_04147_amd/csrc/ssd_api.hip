@@ -139,7 +139,7 @@ static size_t carve(const Dims& d, char* base, Buffers* b) {
     t.row_max = (float*)take(R * 4);
     t.row_arg = (int*)take(R * 4);
     t.row_conf = (float*)take(R * 4);
-    t.row_node = (int*)take(R * 4);
+    t.row_desc = (NodeDesc*)take(R * sizeof(NodeDesc));
     t.raw_tok = (int*)take(R * 4);
     const size_t cache = (size_t)d.L * d.max_seqs * d.Hkv * d.seq_stride() * d.dh * e;
     t.kcache = take(cache);

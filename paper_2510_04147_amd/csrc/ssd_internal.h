@@ -147,7 +147,7 @@ struct Buffers {
     float* row_max;      // [max_rows]
     int* row_arg;        // [max_rows]
     float* row_conf;     // [max_rows]
-    int* row_node;       // [max_rows]
+    NodeDesc* row_desc;  // [max_rows] the node a row belongs to
     int* raw_tok;        // [max_rows]
     void* kcache;        // [L][max_seqs][Hkv][seq_stride * dh] T, keys after rotary, fragment order
     void* vcache;        // [L][max_seqs][Hkv][seq_stride * dh] T, values, fragment order
