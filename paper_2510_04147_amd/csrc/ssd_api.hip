@@ -817,6 +817,16 @@ struct EventPair {
     }
 };
 
+// Behind every forward of a decoding loop, whatever its groups: waits for it and adds the stream time since ev.a to *ms.
+static int finish_forward(ssd_ctx* c, const EventPair& ev, double* ms) {
+    HIPCHK(c, hipEventRecord(ev.b, c->stream));
+    HIPCHK(c, hipEventSynchronize(ev.b));
+    float t = 0;
+    HIPCHK(c, hipEventElapsedTime(&t, ev.a, ev.b));
+    *ms += t;
+    return SSD_OK;
+}
+
 // While one lives the acceptance kernel writes its results straight into the pinned memory the decoding loop reads after the
 // round's event, where a copy behind the kernel would go through the copy engine (64 tokens of the fp32 parity model: 4 % less time).
 struct ResultsToHost {
@@ -848,10 +858,9 @@ static int generate_dual(ssd_ctx* c, int n, const int32_t* const* prompts, const
     const auto t_begin = std::chrono::steady_clock::now();
     ssd_stats sta;
     memset(&sta, 0, sizeof sta);
-    EventPair evp;
-    HIPCHK(c, evp.create());
+    EventPair ev;
+    HIPCHK(c, ev.create());
     ResultsToHost to_host(c);
-    const hipEvent_t ev0 = evp.a, ev1 = evp.b;
     const int n_blocks = (gen_len + block - 1) / block;
     std::vector<std::vector<int32_t>> x(n);
     int blk[SSD_MAX_SEQS], n_masked[SSD_MAX_SEQS], n_dr[SSD_MAX_SEQS], since[SSD_MAX_SEQS];
@@ -942,12 +951,9 @@ static int generate_dual(ssd_ctx* c, int n, const int32_t* const* prompts, const
             c->total_len[i] = T;
         }
         if (hd.M > d.max_rows) { set_err(c, "generate: forward exceeds max_rows"); return SSD_ERANGE; }
-        (void)hipEventRecord(ev0, c->stream);
+        HIPCHK(c, hipEventRecord(ev.a, c->stream));
         if ((rc = run_forward(c, hd, raw.data(), (int)raw.size(), nullptr, 0, nullptr)) != SSD_OK) return rc;
-        (void)hipEventRecord(ev1, c->stream);
-        if (hipEventSynchronize(ev1) != hipSuccess) { set_err(c, "generate: sync failed: %s", hipGetErrorString(hipGetLastError())); return SSD_EHIP; }
-        float ms = 0; (void)hipEventElapsedTime(&ms, ev0, ev1);
-        sta.decode_ms += ms;
+        if ((rc = finish_forward(c, ev, &sta.decode_ms)) != SSD_OK) return rc;
         sta.forwards++;
         for (int i = 0; i < n; ++i) {
             if (master_of[i] < 0) continue;
@@ -1017,21 +1023,18 @@ extern "C" __attribute__((visibility("default"))) int ssd_generate(ssd_ctx* c, i
     const auto t_begin = std::chrono::steady_clock::now();
     ssd_stats sta;
     memset(&sta, 0, sizeof sta);
-    EventPair evp;
-    HIPCHK(c, evp.create());
+    EventPair ev;
+    HIPCHK(c, ev.create());
     ResultsToHost to_host(c);
-    const hipEvent_t ev0 = evp.a, ev1 = evp.b;
     auto done = [&](int rc) { return rc; };
     int rc;
     // prompt prefill, one segment per forward
     for (int i = 0; i < n; ++i) {
         c->cached_len[i] = 0;
-        (void)hipEventRecord(ev0, c->stream);
+        HIPCHK(c, hipEventRecord(ev.a, c->stream));
         if ((rc = ssd_prefill_kv(c, i, prompts[i], prompt_len[i], 0)) != SSD_OK) return done(rc);
-        (void)hipEventRecord(ev1, c->stream);
-        if (hipEventSynchronize(ev1) != hipSuccess) { set_err(c, "generate: sync failed"); return done(SSD_EHIP); }
-        float ms = 0; (void)hipEventElapsedTime(&ms, ev0, ev1);
-        sta.kv_ms += ms; sta.kv_passes++;
+        if ((rc = finish_forward(c, ev, &sta.kv_ms)) != SSD_OK) return done(rc);
+        sta.kv_passes++;
     }
     const int n_blocks = (gen_len + block - 1) / block;
     enum { FRESH, DECODE, APPEND, DONE };
@@ -1110,13 +1113,11 @@ extern "C" __attribute__((visibility("default"))) int ssd_generate(ssd_ctx* c, i
                 }
             }
         if (hd.M > d.max_rows) { set_err(c, "generate: forward exceeds max_rows"); return done(SSD_ERANGE); }
-        (void)hipEventRecord(ev0, c->stream);
+        HIPCHK(c, hipEventRecord(ev.a, c->stream));
         if ((rc = run_forward(c, hd, nullptr, 0, nullptr, 0, nullptr)) != SSD_OK) return done(rc);
-        if (any_decode)
-            (void)hipEventRecord(ev1, c->stream);
-        if (hipEventSynchronize(ev1) != hipSuccess) { set_err(c, "generate: sync failed: %s", hipGetErrorString(hipGetLastError())); return done(SSD_EHIP); }
-        float ms = 0; (void)hipEventElapsedTime(&ms, ev0, ev1);
-        if (any_decode) { sta.decode_ms += ms; sta.forwards++; } else { sta.kv_ms += ms; sta.kv_passes++; }
+        if ((rc = finish_forward(c, ev, any_decode ? &sta.decode_ms : &sta.kv_ms)) != SSD_OK) return done(rc);
+        if (any_decode) sta.forwards++;
+        else sta.kv_passes++;
         for (int gi = 0; gi < hd.n_groups; ++gi) {
             const GroupDesc& g = hd.groups[gi];
             const int i = g.seq;
@@ -1159,8 +1160,9 @@ extern "C" __attribute__((visibility("default"))) int ssd_generate(ssd_ctx* c, i
         }
     }
     for (int i = 0; i < n; ++i)
-        HIPCHK(c, hipMemcpy(out_tokens + (size_t)i * gen_len, c->b.out_tok + (size_t)i * d.max_seq_len, (size_t)gen_len * 4,
-                            hipMemcpyDeviceToHost));
+        HIPCHK(c, hipMemcpyAsync(out_tokens + (size_t)i * gen_len, c->b.out_tok + (size_t)i * d.max_seq_len, (size_t)gen_len * 4,
+                                 hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     sta.total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_begin).count();
     if (stats) *stats = sta;
     return done(SSD_OK);
