@@ -139,3 +139,12 @@ inline bool gemm_plain_small_wins(int M, int N) {
 // (8B shape, us, eight waves / four: 576 work-groups of 64-row blocks 33.6 / 27.7, 640 at prefix 1152 59 / 48, 1000-row
 // prompt 50 / 39, refresh of 512 rows 43 / 31; 160 work-groups 13.2 / 13.0, 32 at prefix 1000 18.2 / 19.0).
 inline bool attn_two_per_cu(long long work_groups) { return work_groups > 256; }
+
+// Plain attention, one wave per row and query head: whether a wave takes a SIMD's whole register file for loads in flight.  The 1024
+// SIMDs have one wave each up to 1024 waves; two channels per lane (head size 128) hold twice the values, in bf16 at no gain.
+// Rotary stage and attention, us, deep / not, prefix 384: head size 64, fp32 1024 waves 34.3 / 39.9, 1536 44.3 / 42.8, 4096 71 / 54,
+// bf16 1024 waves 34.5 / 35.8, 1536 46.7 / 38.3; head size 128, fp32 512 waves 35.5 / 38.5, 768 40.1 / 40.7 (prefix 16: 29.4 / 25.6),
+// 1024 45 / 42, 5120 122 / 94, bf16 256 waves 45 / 39, 5120 177 / 81.
+inline bool attn_plain_deep(long long waves, int head_dim, int element_bytes) {
+    return head_dim == 64 ? waves <= 1024 : element_bytes == 4 && waves <= 512;
+}

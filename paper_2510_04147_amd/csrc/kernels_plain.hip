@@ -379,11 +379,14 @@ __global__ __launch_bounds__(256) void k_rope(const FwdHeader* __restrict__ fw, 
 
 // a4 (plain): one wave per (row, query head).  Keys = the sequence's cached
 // prefix [0,S), its cached suffix behind the block if it has one, then the node's own rows; online softmax in fp32 over
-// key tiles of 64 in position order.  Bound by latency: keys and values are read 16 bytes per lane (a row's chain of
-// FMAs stays in channel and key order), a tile's values and the next tile's keys in flight while its scores are computed, and the
-// row's descriptor lies ready (64 cached keys and a block of 32, head size 64, 4 heads, us, node looked up by two trips,
-// keys and values one trip after the other / this: 7.5 / 5.4).
-template <typename T, int DH>
+// key tiles of 64 in position order.  Keys and values are read 16 bytes per lane; a row's chain of
+// FMAs stays in channel and key order, whatever the variant.
+// DEEP: for launches that give a SIMD at most one wave, bound by latency.  A tile's values and the next tile's keys are in flight
+// while its scores are computed, which takes the SIMD's whole register file (64 cached keys and a block of 32, head size 64, 4
+// heads, us, node looked up by two trips, keys and values one trip after the other / this: 7.5 / 5.4).  Otherwise a tile's keys, 64
+// channels at a time, then its values, 32 keys at a time: 115 to 144 registers, three or four waves to a SIMD that hide each
+// other's trips (both times: attn_plain_deep).
+template <typename T, int DH, bool DEEP>
 __global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ row_desc, const T* __restrict__ q,
                                                    const T* __restrict__ kown, const T* __restrict__ vown,
                                                    const T* __restrict__ kcache, const T* __restrict__ vcache,
@@ -409,13 +412,14 @@ __global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ 
     const int n_suf = max(nd.T - (nd.S + nd.blen), 0), n_cache = nd.S + n_suf;
     const int n_keys = n_cache + nd.blen;
     auto cache_pos = [&](int j) { return j < nd.S ? j : j + nd.blen; };
-    auto load_k = [&](float4(&kv)[DH / 4], int t0) __attribute__((always_inline)) {
+    constexpr int KG = DEEP ? DH / 4 : 16;                   // groups of four channels of a key that are loaded together
+    auto load_k = [&](float4(&kv)[KG], int t0, int g0) __attribute__((always_inline)) {
         const int j = min(t0 + lane, n_keys - 1);            // past the last key: that one, not counted
         const bool pre = j < n_cache;
         const T* kp = pre ? kc : ko;
         const int p = pre ? cache_pos(j) : nd.vrow0 + j - n_cache;
 #pragma unroll
-        for (int i = 0; i < DH / 4; ++i) kv[i] = ld4_f(kp + kfrag_off(p, i * 4, DH));
+        for (int i = 0; i < KG; ++i) kv[i] = ld4_f(kp + kfrag_off(p, (g0 + i) * 4, DH));
     };
     // where key jk lies, and how many keys from it on lie at consecutive positions (uniform over the wave)
     auto place = [&](int jk, int end, const T*& vp, int& pp) __attribute__((always_inline)) {
@@ -425,33 +429,44 @@ __global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ 
         return min(end - jk, jk < nd.S ? nd.S - jk : pre ? n_cache - jk : n_keys - jk);
     };
     // 32 keys at consecutive positions from a multiple of four on: four of a channel lie together
+    auto load32 = [&](float4(&v)[8][CH], const T* vp, int pp) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < 8; ++g)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) v[g][c] = ld4_f(vp + vfrag_off(pp + 4 * g, c * 64 + lane, DH));
+    };
     auto load_v = [&](float4(&v)[8][CH], int jk, int end) __attribute__((always_inline)) {
         if (jk >= end) return false;
         const T* vp;
         int pp;
         if (place(jk, end, vp, pp) < 32 || (pp & 3)) return false;
-#pragma unroll
-        for (int g = 0; g < 8; ++g)
-#pragma unroll
-            for (int c = 0; c < CH; ++c) v[g][c] = ld4_f(vp + vfrag_off(pp + 4 * g, c * 64 + lane, DH));
+        load32(v, vp, pp);
         return true;
     };
     const float scale = 1.0f / sqrtf((float)DH);
     float m = -INFINITY, l = 0.f, o[CH] = {};
-    constexpr bool AHEAD = DH == 64;                         // 128 channels: no registers for the next tile's keys
-    float4 kv[DH / 4], kn[AHEAD ? DH / 4 : 1], va[8][CH], vb[8][CH];
-    load_k(kv, 0);
+    constexpr bool AHEAD = DEEP && DH == 64;                 // 128 channels: no registers for the next tile's keys
+    float4 kv[KG], kn[AHEAD ? KG : 1], va[8][CH], vb[8][CH];
+    if constexpr (DEEP) load_k(kv, 0, 0);
     for (int t0 = 0; t0 < n_keys; t0 += 64) {
         const int end = min(t0 + 64, n_keys);
-        const bool fast_a = load_v(va, t0, end), fast_b = load_v(vb, t0 + 32, end);
+        bool fast_a = false, fast_b = false;
+        if constexpr (DEEP) {
+            fast_a = load_v(va, t0, end);
+            fast_b = load_v(vb, t0 + 32, end);
+        }
         if constexpr (AHEAD)
-            if (t0 + 64 < n_keys) load_k(kn, t0 + 64);
+            if (t0 + 64 < n_keys) load_k(kn, t0 + 64, 0);
         const int j = t0 + lane;
         float acc = 0.f;
+#pragma unroll 1
+        for (int g0 = 0; g0 < DH / 4; g0 += KG) {
+            if constexpr (!DEEP) load_k(kv, t0, g0);
 #pragma unroll
-        for (int i = 0; i < DH / 4; ++i) {
-            const float4 qv = *(const float4*)&qs[i * 4];
-            acc += qv.x * kv[i].x; acc += qv.y * kv[i].y; acc += qv.z * kv[i].z; acc += qv.w * kv[i].w;
+            for (int i = 0; i < KG; ++i) {
+                const float4 qv = *(const float4*)&qs[(g0 + i) * 4];
+                acc += qv.x * kv[i].x; acc += qv.y * kv[i].y; acc += qv.z * kv[i].z; acc += qv.w * kv[i].w;
+            }
         }
         const float s = j < n_keys ? acc * scale : -INFINITY;
         const float m_new = fmaxf(m, wave_max(s));
@@ -461,22 +476,25 @@ __global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ 
 #pragma unroll
         for (int c = 0; c < CH; ++c) o[c] *= corr;
         auto weight = [&](int jj) { return lane_value(p, jj); };
-        auto half = [&](const float4(&v)[8][CH], bool fast, int jj0) __attribute__((always_inline)) {
-            if (fast) {
+        auto add32 = [&](const float4(&v)[8][CH], int jj) __attribute__((always_inline)) {
 #pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    const float w0 = weight(jj0 + 4 * g), w1 = weight(jj0 + 4 * g + 1), w2 = weight(jj0 + 4 * g + 2), w3 = weight(jj0 + 4 * g + 3);
+            for (int g = 0; g < 8; ++g) {
+                const float w0 = weight(jj + 4 * g), w1 = weight(jj + 4 * g + 1), w2 = weight(jj + 4 * g + 2), w3 = weight(jj + 4 * g + 3);
 #pragma unroll
-                    for (int c = 0; c < CH; ++c) { o[c] += w0 * v[g][c].x; o[c] += w1 * v[g][c].y; o[c] += w2 * v[g][c].z; o[c] += w3 * v[g][c].w; }
-                }
-                return;
+                for (int c = 0; c < CH; ++c) { o[c] += w0 * v[g][c].x; o[c] += w1 * v[g][c].y; o[c] += w2 * v[g][c].z; o[c] += w3 * v[g][c].w; }
             }
-            const int stop = min(t0 + jj0 + 32, n_keys) - t0;
-            int jj = jj0;
+        };
+        // the tile's keys [jj, stop) whose values are not on their way
+        auto walk = [&](int jj, int stop) __attribute__((always_inline)) {
             while (jj < stop) {
                 const T* vp;
                 int pp;
-                if (place(t0 + jj, t0 + stop, vp, pp) >= 8) {
+                const int run = place(t0 + jj, t0 + stop, vp, pp);
+                if (!DEEP && run >= 32 && (pp & 3) == 0) {
+                    load32(va, vp, pp);
+                    add32(va, jj);
+                    jj += 32;
+                } else if (run >= 8) {
                     float a[8][CH];
 #pragma unroll
                     for (int g = 0; g < 8; ++g)
@@ -494,14 +512,18 @@ __global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ 
                 }
             }
         };
-        half(va, fast_a, 0);
-        half(vb, fast_b, 32);
+        if constexpr (DEEP) {
+            if (fast_a) add32(va, 0);
+            else walk(0, min(32, n_keys - t0));
+            if (fast_b) add32(vb, 32);
+            else walk(32, min(64, n_keys - t0));
+        } else walk(0, min(64, n_keys - t0));
         m = m_new;
-        if (t0 + 64 < n_keys) {
+        if (DEEP && t0 + 64 < n_keys) {
             if constexpr (AHEAD)
 #pragma unroll
-                for (int i = 0; i < DH / 4; ++i) kv[i] = kn[i];
-            else load_k(kv, t0 + 64);
+                for (int i = 0; i < KG; ++i) kv[i] = kn[i];
+            else load_k(kv, t0 + 64, 0);
         }
     }
     T* op = out + (size_t)row * nq + head * DH;
@@ -1076,13 +1098,15 @@ template <typename T>
 static void attn_plain_t(const ssd_ctx* c, int M, int layer, hipStream_t st) {
     const Dims& d = c->dm;
     const dim3 grid(M, d.Hq);
-    auto run = [&](auto dh) {
-        k_attn_plain<T, decltype(dh)::value><<<grid, 64, 0, st>>>(c->b.row_desc, (const T*)c->b.q, (const T*)c->b.kown, (const T*)c->b.vown,
+    auto run = [&](auto dh, auto deep) {
+        k_attn_plain<T, decltype(dh)::value, decltype(deep)::value><<<grid, 64, 0, st>>>(c->b.row_desc, (const T*)c->b.q, (const T*)c->b.kown, (const T*)c->b.vown,
                                                                   (const T*)c->b.kcache, (const T*)c->b.vcache, (T*)c->b.attn, d.Hq, d.Hkv,
                                                                   layer, d.max_seqs, d.seq_stride(), d.vt_rows());
     };
-    if (d.dh == 128) run(std::integral_constant<int, 128>{});
-    else run(std::integral_constant<int, 64>{});
+    const bool deep = attn_plain_deep((long long)M * d.Hq, d.dh, sizeof(T));
+    if (d.dh == 64) deep ? run(std::integral_constant<int, 64>{}, std::true_type{}) : run(std::integral_constant<int, 64>{}, std::false_type{});
+    else if constexpr (sizeof(T) == 4) deep ? run(std::integral_constant<int, 128>{}, std::true_type{}) : run(std::integral_constant<int, 128>{}, std::false_type{});
+    else run(std::integral_constant<int, 128>{}, std::false_type{});
 }
 
 void launch_attn_plain(const ssd_ctx* c, int M, int layer, hipStream_t st) {
