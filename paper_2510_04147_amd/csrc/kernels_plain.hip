@@ -542,12 +542,27 @@ __global__ __launch_bounds__(64) void k_attn_plain(const NodeDesc* __restrict__ 
 #define PBN GEMM_PLAIN_TILE
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Four consecutive values, or zeros.  VEC: the address is a multiple of four elements.
-template <bool VEC, typename T>
-__device__ __forceinline__ float4 get4(const T* p, bool ok = true) {
+// Four consecutive values as they lie in memory, to wait in registers.
+template <typename T> struct Four;
+template <> struct Four<float> { typedef float4 type; };
+template <> struct Four<bf16_t> { typedef uint2 type; };
+__device__ __forceinline__ float4 widen(const float4& v) { return v; }
+__device__ __forceinline__ float4 widen(const uint2& v) {
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
+// The four from p on, or zeros.  VEC: the address is a multiple of four elements.
+template <bool VEC>
+__device__ __forceinline__ float4 get_four(const float* p, bool ok) {
     if (!ok) return make_float4(0.f, 0.f, 0.f, 0.f);
-    if constexpr (VEC) return ld4_f(p);
-    else return make_float4(ld_f(p), ld_f(p + 1), ld_f(p + 2), ld_f(p + 3));
+    if constexpr (VEC) return *(const float4*)p;
+    else return make_float4(p[0], p[1], p[2], p[3]);
+}
+template <bool VEC>
+__device__ __forceinline__ uint2 get_four(const bf16_t* p, bool ok) {
+    if (!ok) return make_uint2(0, 0);
+    if constexpr (VEC) return *(const uint2*)p;
+    else return make_uint2(p[0] | ((uint32_t)p[1] << 16), p[2] | ((uint32_t)p[3] << 16));
 }
 // One step of one chain: lane (q, j) = (lane / 16, lane % 16) holds columns 4q ... 4q + 3 of weight row j and of row j of X;
 // it ends up with weight rows 4q ... 4q + 3 of row j.
@@ -590,9 +605,12 @@ __device__ __forceinline__ void lm_row_partial(const float (&v)[NJ], int n0, int
     }
 }
 
-// 64x64 tile per work-group, 2x2 waves of 32x32: 2x2 MFMA tiles.  A step's operands are loaded while the step before it is
-// multiplied.  Bound: the caches; every operand is requested by the two waves that need it.  160 rows, K = 12288,
-// N = 4096, us, FMAs through LDS / this: 697 / 462.
+// 64x64 tile per work-group, 2x2 waves of 32x32: 2x2 MFMA tiles.  LINE steps' operands are loaded while the LINE steps before them
+// are multiplied: in bf16 the four steps of a 128-byte line, which one at a time fetch it four times once the work-groups of a CU
+// need more lines than its L1 holds.  Bound: the caches; every operand is requested by the two waves that need it.  160 rows, K = 12288,
+// N = 4096, us, fp32, FMAs through LDS / this: 697 / 462; bf16, FMAs / one step at a time / this: 192 rows 763 / 737 / 368, gate/up
+// of 18944 channels, K = 3584, 256 rows 1485 / 1600 / 862.  (fp32 by lines of two steps: 407 against 486 where the grid is one
+// round, 1807 against 1587 where it is several.)
 template <typename T, int EPI, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, const T* __restrict__ W,
                                                     void* __restrict__ outv, int M, int N, int K, int up_off,
@@ -602,7 +620,8 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, con
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, j = lane & 15;
     const int m0 = blockIdx.y * PBM + (wave >> 1) * 32, n0 = blockIdx.x * PBN + (wave & 1) * 32;
     floatx4 acc[NU][2][2], tot[NU][2][2];                 // [gate, up][n-tile][m-tile]: a chain, the chains before it
-    float4 w[2][NU][2], x[2][2];
+    constexpr int LINE = sizeof(T) == 2 ? 4 : 1;          // steps whose operands are loaded together
+    typename Four<T>::type w[2][LINE][NU][2], x[2][LINE][2];
     const T *xr[2], *wr[NU][2];                           // rows past the end read the last one (never stored)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -611,12 +630,15 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, con
         for (int u = 0; u < NU; ++u) wr[u][t] = W + (size_t)(u * up_off + min(n0 + t * 16 + j, N - 1)) * K;
     }
     auto load = [&](int buf, int s) __attribute__((always_inline)) {
-        const int k = s * 16 + q * 4;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            x[buf][t] = get4<VEC>(xr[t] + k, k < K);
+        for (int i = 0; i < LINE; ++i) {
+            const int k = (s + i) * 16 + q * 4;
 #pragma unroll
-            for (int u = 0; u < NU; ++u) w[buf][u][t] = get4<VEC>(wr[u][t] + k, k < K);
+            for (int t = 0; t < 2; ++t) {
+                x[buf][i][t] = get_four<VEC>(xr[t] + k, k < K);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) w[buf][i][u][t] = get_four<VEC>(wr[u][t] + k, k < K);
+            }
         }
     };
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -637,18 +659,23 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, con
     };
     load(0, 0);
     int left = len;
-    for (int s0 = 0; s0 < steps; s0 += 2)
+    for (int s0 = 0; s0 < steps; s0 += 2 * LINE)
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            if (s0 + c >= steps) break;
-            load(c ^ 1, s0 + c + 1);                      // past the end: zeros, unused
+            const int s = s0 + c * LINE;
+            if (s >= steps) break;
+            load(c ^ 1, s + LINE);                        // past the end: zeros, unused
 #pragma unroll
-            for (int u = 0; u < NU; ++u)
+            for (int i = 0; i < LINE; ++i) {
+                if (s + i >= steps) break;
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+                for (int u = 0; u < NU; ++u)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) acc[u][a][b] = mfma_step(w[c][u][a], x[c][b], acc[u][a][b]);
-            if (--left == 0) { close(); left = len; }
+                    for (int a = 0; a < 2; ++a)
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) acc[u][a][b] = mfma_step(widen(w[c][i][u][a]), widen(x[c][i][b]), acc[u][a][b]);
+                if (--left == 0) { close(); left = len; }
+            }
         }
     close();
 #pragma unroll
@@ -691,6 +718,8 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const T* __restrict__ X, con
 // flight together (K up to 512 in one trip).  Operands must be 16-byte aligned.
 // Measured, fp32, 32 rows (K x N, us, FMAs of 8x16 tiles through LDS / this): 256 x 768 5.5 / 3.6, 256 and 768 x 256 8.7 / 4.5,
 // gate/up 256 x 768 6.7 / 4.6, LM head 256 x 1024 9.0 / 6.2; four chains instead of eight, twice the steps each: 4.6, 6.1, 6.6, 10.5.
+// bf16 waits in registers as it lies in memory (36 to 49 instead of 52 to 74; gate/up 512 x 1536, us, FMAs / widened at once / this:
+// 96 rows 13.6 / 15.2 / 13.3, 256 rows 28.5 / 32.2 / 24.5).
 template <typename T, int EPI>
 __global__ __launch_bounds__(EPI == EPI_F32 ? 512 : 1024) void k_gemm_plain_small(
     const T* __restrict__ X, const T* __restrict__ W, void* __restrict__ outv, int M, int N, int K, int up_off, int mask_id,
@@ -713,20 +742,20 @@ __global__ __launch_bounds__(EPI == EPI_F32 ? 512 : 1024) void k_gemm_plain_smal
 #pragma unroll
     for (int g = 0; g < GW; ++g) acc[g] = {0.f, 0.f, 0.f, 0.f};
     for (int s = 0; s < cnt; s += BATCH) {
-        float4 w[GW][BATCH], x[BATCH];
+        typename Four<T>::type w[GW][BATCH], x[BATCH];
 #pragma unroll
         for (int i = 0; i < BATCH; ++i)
             if (s + i < cnt) {
                 const bool ok = (s + i) * 16 < kleft;
-                x[i] = get4<true>(xr + (s + i) * 16, ok);
+                x[i] = get_four<true>(xr + (s + i) * 16, ok);
 #pragma unroll
-                for (int g = 0; g < GW; ++g) w[g][i] = get4<true>(wr[g] + (s + i) * 16, ok);
+                for (int g = 0; g < GW; ++g) w[g][i] = get_four<true>(wr[g] + (s + i) * 16, ok);
             }
 #pragma unroll
         for (int i = 0; i < BATCH; ++i)
             if (s + i < cnt)
 #pragma unroll
-                for (int g = 0; g < GW; ++g) acc[g] = mfma_step(w[g][i], x[i], acc[g]);
+                for (int g = 0; g < GW; ++g) acc[g] = mfma_step(widen(w[g][i]), widen(x[i]), acc[g]);
     }
 #pragma unroll
     for (int g = 0; g < GW; ++g) *(floatx4*)&part[h * GW + g][chain][j][q * 4] = acc[g];
