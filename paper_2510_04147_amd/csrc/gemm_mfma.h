@@ -407,7 +407,7 @@ bool gemm_f32_wn4(const GemmArgs& a);     // narrow outputs, long K (down) and e
 bool gemm_swiglu_wn3(const GemmArgs& a);
 bool gemm_swiglu_wn4(const GemmArgs& a);
 bool gemm_lmhead_wn4(const GemmArgs& a);
-// the kernel for many rows (gemm_rows.h) with the tile that gemm_wide_tile() or gemm_rows_tile() says
+// the kernel for many rows (gemm_rows.h) with the tile that gemm_tile() says
 bool gemm_rows_f32(const GemmArgs& a, int tile);
 bool gemm_rows_swiglu(const GemmArgs& a, int tile);
 bool gemm_rows_lmhead(const GemmArgs& a, int tile);

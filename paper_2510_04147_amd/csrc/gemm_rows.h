@@ -12,11 +12,11 @@
 // Bound by the matrix cores' power: a chunk of the 192 x 320 tile takes 1.43 us (1.41 PFLOP/s over the chip), without its
 // loads 1.22 us (1.65; MFMAs alone on random operands, from registers, reach 1.65 to 1.75 and on zeros 2.3), and a
 // launch about 10 us on top: ramp, first chunk, epilogue.  Why these tiles: bytes per operation are what the loads cost, and a
-// grid that is a whole number of rounds over the 256 CUs (gemm_wide_tile).  8B shape, us, before (256 x 128 in eight waves,
+// grid that is a whole number of rounds over the 256 CUs (gemm_tile).  8B shape, us, before (256 x 128 in eight waves,
 // two chains per output, which fill the register file at half the tile) / now: gate/up 512 rows 123 / 86, 576 rows 117 /
 // 100, 640 rows 121 / 103, 1000 rows 186 / 171; QKV 640 rows 69.5 / 59, down 512 rows 61 / 50, 640 rows 77 / 66.
 // HALF (fp32 partial sums): half of the k-slices one after the other, each a chain of its own, added as the consumers add partial
-// sums: two leave the kernel instead of one per slice (gemm_halves_tile).
+// sums: two leave the kernel instead of one per slice (gemm_tile).
 // Fragments are read and loads issued one by one between MFMAs (all of a step's reads first and loads where the compiler left
 // them: 1.58 us a chunk); eight waves on 256 x 256, two per SIMD, are no faster than four.
 template <int WN, int WM, int R, int TW, int EPI, int NSX, int NSW, bool HALF>
@@ -267,9 +267,9 @@ static bool launch_tile(const GemmArgs& a, int tile) {
         case GEMM_256x256: return launch_rows<2, 2, 4, 4, EPI>(a);
         case GEMM_192x320: return launch_rows<2, 2, 3, 5, EPI>(a);
         case GEMM_192x256: return launch_rows<2, 2, 3, 4, EPI>(a);
-        case 3: return launch_rows<4, 1, 2, 3, EPI>(a);
-        case 4: return launch_rows<2, 2, 4, 2, EPI>(a);
-        case 5: return launch_rows<4, 1, 2, 5, EPI>(a);
+        case GEMM_256x96: return launch_rows<4, 1, 2, 3, EPI>(a);
+        case GEMM_256x128: return launch_rows<2, 2, 4, 2, EPI>(a);
+        case GEMM_256x160: return launch_rows<4, 1, 2, 5, EPI>(a);
     }
     return false;
 }

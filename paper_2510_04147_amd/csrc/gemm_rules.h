@@ -10,92 +10,6 @@ inline int gemm_full_pass(int M) {
     return tiles <= 6 ? tiles : (M + 191) / 192 < (M + 159) / 160 ? 6 : 5;
 }
 
-// The large tiles of k_gemm_rows, weight rows x activation rows.  The small ones, 256 x 96, 128 and 160, are named by their
-// 3, 4 or 5 row tiles of 32.
-enum GemmWideTile { GEMM_256x256 = 256256, GEMM_192x320 = 192320, GEMM_192x256 = 192256 };
-// Tiles that walk one half of the k-slices and add their sums, so that two partial sums leave the kernel.
-enum GemmHalvesTile { GEMM_HALVES_256x128 = 2256128, GEMM_HALVES_192x128 = 2192128 };
-
-// One of the large tiles where it is the fastest way for M rows, or 0: gemm_rows_tile() and gemm_few_row_pass() choose.
-// nch: chunks of 64 columns in a k-slice; wn: as below.
-// Time of a launch = rounds over the 256 CUs x (fixed + chunks x a) + share of the chip's work-group slots x chunks x b, since
-// a round that fills the chip only partly draws less power and clocks higher.  Fitted, ns, to gate/up of the 8B shape at 193
-// to 2304 rows (64 chunks; one round of half the chip / of the whole chip, two rounds of it, us: 192 x 256 68 / 86, 171;
-// 192 x 320 77 / 100, 195; 256 x 256 at 192 work-groups 89, at 512 and 768 - / - , 184 / 318).  Over the four matrices of the 8B and
-// the 7B class and the LM head, 193 to 2304 rows, the choice was within 4 % of the fastest tile but for 8 % at down, 256 rows.
-// At least 128 work-groups: fewer leave half of the chip idle, and the few-row kernel's narrower n-blocks spread better.
-inline int gemm_wide_tile(int M, int N, int nch, int split, int wn, long long* time = nullptr) {
-    if (M <= 192) return 0;
-    struct Kind { int code, nt, mt, a, b; };
-    static const Kind kinds[6] = {{GEMM_256x256, 8, 8, 840, 620}, {GEMM_192x320, 6, 10, 656, 750}, {GEMM_192x256, 6, 8, 625, 560},
-                                  {0, 8, 4, 560, 250}, {0, 8, 5, 690, 230}, {0, 8, 3, 470, 190}};
-    const long long fixed = 10000;
-    int best = 0;
-    long long best_time = -1;
-    for (const Kind& k : kinds) {
-        const long long wgs = (long long)((N / 32 + k.nt - 1) / k.nt) * split * ((M + k.mt * 32 - 1) / (k.mt * 32));
-        const long long t = (wgs + 255) / 256 * (fixed + (long long)nch * k.a) + wgs * nch * k.b / 256;
-        if (wgs >= 128 && (best_time < 0 || t < best_time)) { best = k.code; best_time = t; }
-    }
-    // the few-row kernel's passes of 160 or 192 rows
-    const int mt = gemm_full_pass(M);
-    const long long wgs = (long long)((N / 32 + wn - 1) / wn) * split * ((M + mt * 32 - 1) / (mt * 32));
-    const long long few = (wgs + 255) / 256 * (4000 + (long long)nch * (mt == 6 ? 630 : 560)) * wn / 3;
-    if (wgs >= 256 && few < best_time) { best = 0; best_time = few; }
-    if (time) *time = best_time;
-    return best;
-}
-
-// One of the tiles that walk half of the k-slices (fp32 partial sums only), or 0.  They hold two accumulators per output, so the
-// tile is half as large and the kernel alone no faster (8B down, 1000 rows 97 us in eight slices / 102 in halves; 640 rows 70 /
-// 75; 7B class down, 2304 rows 278 / 292); what they save is the other partial sums: 0.08 us to write and 0.16 us to read
-// per MB each (norm of 1000 rows x 4096: 26 us with eight, 11 with two).  Time of a launch as above, with ns of their own.
-inline int gemm_halves_tile(int M, int N, int nch, int split, int wn) {
-    if (M <= 192 || split <= 2) return 0;
-    struct Kind { int code, nt, mt, a, b; };
-    static const Kind kinds[2] = {{GEMM_HALVES_256x128, 8, 4, 750, 250}, {GEMM_HALVES_192x128, 6, 4, 550, 170}};
-    const long long fixed = 6000, kb = (long long)M * N * 4 / 1000, chunks = (long long)nch * ((split + 1) / 2);
-    long long best_time = -1;
-    gemm_wide_tile(M, N, nch, split, wn, &best_time);
-    if (best_time < 0) return 0;
-    best_time += split * kb * 24 / 100;
-    int best = 0;
-    for (const Kind& k : kinds) {
-        const long long wgs = (long long)((N / 32 + k.nt - 1) / k.nt) * 2 * ((M + k.mt * 32 - 1) / (k.mt * 32));
-        const long long t = (wgs + 255) / 256 * (fixed + chunks * k.a) + wgs * chunks * k.b / 256 + 2 * kb * 16 / 100;
-        if (wgs >= 128 && t < best_time) { best = k.code; best_time = t; }
-    }
-    return best;
-}
-
-// Row tiles (of 32 rows) per work-group of k_gemm_rows with 256 weight rows, or 0: the few-row kernel takes the call, in
-// n-blocks of wn tiles.  Asked where no large tile is the fastest.
-// Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of them;
-// beyond that it re-streams them per pass (8B shape, 193 rows, us, few-row / 128 rows: gate/up 80 / 57, QKV 46 / 33, down 40 /
-// 33).  Fewer than 128 work-groups leave half of the chip idle: then the
-// few-row kernel's narrower n-blocks spread better.  Among the tiles the fewest rounds over the 256 CUs win, a
-// round of 96, 128 or 160 rows costing 0.84 : 1 : 1.11 (gate/up at 256 to 640 rows: 48, 57 and 65 us a round).
-// The few-row kernel's 96-row n-blocks, where they fill the chip, count along: a round of 160 or 192 rows costs 0.65 or
-// 0.75 there (320 and 384 rows in two passes: 82 and 89 us).
-// X, the activations, must start on 16 bytes (their rows then do: K is a multiple of 64): the kernels copy them to LDS in
-// 16-byte pieces (launch_gemm_mfma sees to it that they do).
-inline int gemm_rows_tile(const void* X, int M, int N, int split, int wn) {
-    if (M <= 192 || ((uintptr_t)X & 15)) return 0;
-    const int n_blocks = (N / 32 + 7) / 8, cost[3] = {84, 100, 111};
-    int best = 0, best_cost = 0;
-    for (int mt = 3; mt <= 5; ++mt) {
-        const long long wgs = (long long)n_blocks * split * ((M + mt * 32 - 1) / (mt * 32));
-        const long long c = (wgs + 255) / 256 * cost[mt - 3];
-        if (wgs >= 128 && (best == 0 || c < best_cost)) { best = mt; best_cost = (int)c; }
-    }
-    const long long blocks = (long long)((N / 32 + wn - 1) / wn) * split;
-    if (wn == 3 && blocks >= 256) {
-        const int mt = gemm_full_pass(M);
-        if ((blocks * ((M + mt * 32 - 1) / (mt * 32)) + 255) / 256 * (mt == 6 ? 75 : 65) < best_cost) return 0;
-    }
-    return best;
-}
-
 // How the few-row kernel takes M rows: `passes` passes of `mt` row tiles of 32 rows.
 struct GemmPass {
     int mt, passes;
@@ -117,6 +31,59 @@ inline GemmPass gemm_few_row_pass(int M, int N, int split, int wn) {
     while (mt > 1 && (long long)blocks * ((tiles + mt - 1) / mt) < 128) --mt;
     const int passes = (tiles + mt - 1) / mt;
     return GemmPass{mt, passes, passes > 1};
+}
+
+// The tiles of k_gemm_rows, weight rows x activation rows.  HALVES: tiles that walk one half of the k-slices and add their sums, so that
+// two partial sums leave the kernel (fp32 partial sums in more than two slices only).
+enum GemmTile {
+    GEMM_FEW_ROWS = 0,                                       // not one of them: the few-row kernel
+    GEMM_256x96 = 256096, GEMM_256x128 = 256128, GEMM_256x160 = 256160, GEMM_192x256 = 192256, GEMM_192x320 = 192320, GEMM_256x256 = 256256,
+    GEMM_HALVES_192x128 = 2192128, GEMM_HALVES_256x128 = 2256128
+};
+
+// What a GEMM writes: split-K partial sums, activated channels, the LM head's partial results.
+enum GemmOut { GEMM_SUMS, GEMM_CHANNELS, GEMM_LM };
+
+// The kernel for M rows of a matrix with N weight rows and `split` k-slices of nch chunks of 64 columns; wn: n-tiles of the few-row
+// kernel's work-groups.  Up to 192 rows the few-row kernel needs one pass over the weights and every CU streams its own share of
+// them.  For more rows the way with the least estimated time:
+//     rounds over the 256 CUs x (round + chunks x chunk) + share of the chip's work-group slots x chunks x full + weights x w
+//     + 0.69 ns per 1000 partial sums, written and read again by the consumer (0.17 us per MB)
+// `full` on top of `chunk` because a round that fills the chip only partly draws less power and clocks higher.  Few-row kernel: chunk
+// and full grow with the loads (n-tiles + row tiles) and the products (n-tiles x row tiles) of a work-group; several slices cost 12 %
+// more, and of the LM head, whose work-groups share a CU in pairs, an even number of passes 8 % less, an odd one 20 % more.
+// Fitted to the times of kernel and consumer inside forwards of seven shapes (widths 1024, 1600, 2048, 3072, 3584, 4096 and 5120, five
+// matrices each, 193 to 2304 rows, 805 calls with every way each; one way's time is met within 5 to 10 % rms).  The choice is 0.15 %
+// slower than the fastest way on average, 0.7 % at the 95th percentile, 8 % at most (rules of their own for the large, the small and the
+// halving tiles: 1.4, 8.4 and 21 %); a shape left out of the fit lost 0.1 to 0.4 %.  8B shape, attention output
+// and a layer's norms, us, best without halves / halves: 512 rows 55 / 59, 640 rows 54.8 / 54.4, 1000 rows 75 / 72; down 512 rows 79 / 94,
+// 640 rows 103 / 100, 1000 rows 143 / 128.
+// At least 112 work-groups: with fewer, half of the chip idle, the few-row kernel's narrower n-blocks spread better (120 work-groups, 2560
+// wide, attention output and norms at 193 rows: few-row kernel 34.3, 256 x 96 30.9).
+inline int gemm_tile(int M, int N, int nch, int split, int wn, GemmOut out) {
+    if (M <= 192) return GEMM_FEW_ROWS;
+    struct Kind { int code, nt, mt; double round, chunk, full, w; };         // tiles of 32 rows; ns
+    static const Kind kinds[8] = {
+        {GEMM_256x96, 8, 3, 6663, 446, 132, .161}, {GEMM_256x128, 8, 4, 7910, 463, 232, .142}, {GEMM_256x160, 8, 5, 8614, 489, 369, .110},
+        {GEMM_192x256, 6, 8, 9117, 578, 437, .111}, {GEMM_192x320, 6, 10, 9540, 716, 537, .088}, {GEMM_256x256, 8, 8, 10682, 617, 753, .078},
+        {GEMM_HALVES_192x128, 6, 4, 7927, 438, 197, .113}, {GEMM_HALVES_256x128, 8, 4, 9289, 559, 260, .064}};
+    const double weights = (double)N * nch * split * 64 / 1000, sums = out == GEMM_SUMS ? .69 * M * N / 1000 : 0;
+    const GemmPass p = gemm_few_row_pass(M, N, split, wn);
+    const long long few_wgs = (long long)((N / 32 + wn - 1) / wn) * split * p.passes;
+    int best = GEMM_FEW_ROWS;
+    double least = ((few_wgs + 255) / 256 * (4996 + nch * (26.8 * (wn + p.mt) + 10.7 * wn * p.mt)) +
+                    few_wgs * nch * 6.9 * wn * p.mt / 256 + weights * .08) *
+                       (split > 1 ? 1.12 : out == GEMM_LM && few_wgs > 256 ? (p.passes % 2 ? 1.2 : .92) : 1.03) +
+                   split * sums;
+    for (const Kind& k : kinds) {
+        const bool half = k.code >= GEMM_HALVES_192x128;
+        if (half && (out != GEMM_SUMS || split <= 2)) continue;
+        const int parts = half ? 2 : split, chunks = half ? nch * ((split + 1) / 2) : nch;
+        const long long wgs = (long long)((N / 32 + k.nt - 1) / k.nt) * parts * ((M + k.mt * 32 - 1) / (k.mt * 32));
+        const double t = (wgs + 255) / 256 * (k.round + chunks * k.chunk) + wgs * chunks * k.full / 256 + weights * k.w + parts * sums;
+        if (wgs >= 112 && t < least) { best = k.code; least = t; }
+    }
+    return best;
 }
 
 // Plain GEMM: k_gemm_plain_small may take the call while k_gemm_plain's 64x64 tiles would give a CU at most one work-group.

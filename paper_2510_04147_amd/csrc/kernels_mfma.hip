@@ -77,8 +77,7 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
         // (768 tiles) exactly one work-group per CU
         *n_split = 1;
         const int wn = (N / 32) % 3 == 0 ? 3 : 4;
-        if (const int t = gemm_wide_tile(M, N, K / KC, 1, wn)) return gemm_rows_swiglu(a, t);
-        if (const int rt = gemm_rows_tile(X, M, N, 1, wn)) return gemm_rows_swiglu(a, rt);
+        if (const int t = gemm_tile(M, N, K / KC, 1, wn, GEMM_CHANNELS)) return gemm_rows_swiglu(a, t);
         a.pass = gemm_few_row_pass(M, N, 1, wn);
         return wn == 3 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);
     }
@@ -86,8 +85,7 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
         *n_split = lm_tiles_mfma(N);
         a.mask_id = c->dm.mask_id;
         a.n_tiles_out = N / 32;
-        if (const int t = gemm_wide_tile(M, N, K / KC, 1, 4)) return gemm_rows_lmhead(a, t);
-        if (const int rt = gemm_rows_tile(X, M, N, 1, 4)) return gemm_rows_lmhead(a, rt);
+        if (const int t = gemm_tile(M, N, K / KC, 1, 4, GEMM_LM)) return gemm_rows_lmhead(a, t);
         a.pass = gemm_few_row_pass(M, N, 1, 4);
         return gemm_lmhead_wn4(a);
     }

@@ -26,12 +26,10 @@ bool launch_gemm_mfma_f32(const ssd_ctx* c, const bf16_t* x, const uint4* wp, vo
     const int split = pick_split(K, KC, want);
     *n_split = split;
     GemmArgs a{x, wp, out, M, N, K, split, stride, -1, 0, {}, st};
-    if (const int t = gemm_halves_tile(M, N, K / split / KC, split, wn)) {
-        *n_split = 2;
+    if (const int t = gemm_tile(M, N, K / split / KC, split, wn, GEMM_SUMS)) {
+        if (t >= GEMM_HALVES_192x128) *n_split = 2;
         return gemm_rows_f32(a, t);
     }
-    if (const int t = gemm_wide_tile(M, N, K / split / KC, split, wn)) return gemm_rows_f32(a, t);
-    if (const int rt = gemm_rows_tile(x, M, N, split, wn)) return gemm_rows_f32(a, rt);
     a.pass = gemm_few_row_pass(M, N, split, wn);
     return wn == 3 ? gemm_f32_wn3(a) : wn == 2 ? gemm_f32_wn2(a) : gemm_f32_wn4(a);
 }

@@ -42,7 +42,7 @@ def test_passes_equal_single_tiles(shape):
 
 
 def test_unaligned_rows_equal_aligned_ones():
-    """Row counts of the many-row kernel with x off a 16-byte boundary: the few-row kernel takes the call, same rows."""
+    """x off a 16-byte boundary: the call copies it to one first, same rows."""
     from paper_2510_04147_amd import binding
     cfg = synth.model_config("8b", n_layers=1, d_model=896, d_ffn=9232, vocab=21152)
     w = synth.gen_weights(cfg, 5, device="cuda")

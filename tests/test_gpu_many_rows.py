@@ -18,9 +18,11 @@ pytestmark = pytest.mark.gpu
 SHAPES = [dict(d_model=832, d_ffn=8240, vocab=18016), dict(d_model=896, d_ffn=9232, vocab=21152),
           dict(d_model=960, d_ffn=9008, vocab=17952), dict(d_model=192, d_ffn=8208, vocab=16416),
           # attention output in four slices of eight chunks, down in eight of twelve
-          dict(d_model=2048, n_q_heads=16, n_kv_heads=4, d_ffn=6144, vocab=1056)]
+          dict(d_model=2048, n_q_heads=16, n_kv_heads=4, d_ffn=6144, vocab=1056),
+          # QKV in two slices of 19 chunks, attention output in four of twelve, down in eight of nine
+          dict(d_model=2432, n_q_heads=24, n_kv_heads=8, d_ffn=4608, vocab=1056)]
 ROWS = (192, 193, 224, 256, 257, 289, 385, 480, 513, 640, 641, 801, 1281)
-ROWS64 = (193, 257, 480, 641, 1281)                # also compared with fp64
+ROWS64 = (193, 257, 289, 480, 641, 1281)                # also compared with fp64
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"k{s['d_model']}")

@@ -35,23 +35,22 @@ def linears(cfg):
 
 def test_rows_and_shapes_reach_every_large_tile(tmp_path):
     (tmp_path / "p.cpp").write_text(
-        '#include <cstdio>\n#include "gemm_rules.h"\nint main() { int M, N, n, s, w; while (std::scanf("%d %d %d %d %d", &M, &N, &n, &s, &w) == 5) '
-        'std::printf("%d\\n", gemm_wide_tile(M, N, n, s, w)); }')
+        '#include <cstdio>\n#include "gemm_rules.h"\nint main() { int M, N, n, s, w, o; while (std::scanf("%d %d %d %d %d %d", &M, &N, &n, &s, &w, &o) == 6) '
+        'std::printf("%d\\n", gemm_tile(M, N, n, s, w, (GemmOut)o)); }')
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "p.cpp"), "-o", str(tmp_path / "p")], check=True)
 
     def ask(calls):
-        out = subprocess.run([str(tmp_path / "p")], input="".join("%d %d %d %d %d\n" % c for c in calls), capture_output=True, text=True, check=True)
+        out = subprocess.run([str(tmp_path / "p")], input="".join("%d %d %d %d %d %d\n" % c for c in calls), capture_output=True, text=True, check=True)
         return [int(v) for v in out.stdout.split()]
 
     seen = set()
     for m in SHAPES:
         for _, epi, K, _, N, split, wn in linears(synth.model_config("8b", **m)):
             nch = K // split // 64
-            for M, t in zip(ROWS, ask([(M, N, nch, split, wn) for M in ROWS])):
-                assert t in (0, *WIDE), (M, N, t)
-                if t:
+            for M, t in zip(ROWS, ask([(M, N, nch, split, wn, ("f32", "swiglu", "lm").index(epi)) for M in ROWS])):
+                if t in WIDE:
                     block = t // 1000
-                    assert -(-N // block) * split * -(-M // (t % 1000)) >= 128, (M, N, t)
+                    assert -(-N // block) * split * -(-M // (t % 1000)) >= 112, (M, N, t)
                     seen.add((epi, t, nch, N % block != 0, M % (t % 1000) != 0))
     for epi in ("f32", "swiglu", "lm"):
         for t in WIDE:
@@ -60,8 +59,8 @@ def test_rows_and_shapes_reach_every_large_tile(tmp_path):
             assert {s[4] for s in seen if s[1] == t} == {False, True}, t
             assert any(s[3] for s in mine), (epi, t)
     assert {s[2] for s in seen} == {1, 2, 3, 4, 5, 6}
-    # never for rows that one pass of the few-row kernel takes, nor for grids that leave half of the chip idle
-    assert not any(ask([(M, 24576, 64, 1, 3) for M in (1, 32, 160, 192)] + [(M, 1024, 64, 1, 2) for M in (193, 640, 1000)]))
+    # no tile of the many-row kernel for rows that one pass of the few-row kernel takes, nor for grids that leave half of the chip idle
+    assert not any(ask([(M, 24576, 64, 1, 3, 1) for M in (1, 32, 160, 192)] + [(M, 1024, 64, 1, 2, 1) for M in (193, 640, 1000)]))
 
 
 @pytest.mark.gpu
