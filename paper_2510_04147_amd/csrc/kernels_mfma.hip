@@ -128,7 +128,9 @@ __device__ __forceinline__ float merge2(float a, float ca, float b, float cb) { 
 // two work-groups fit a CU and one's prologue and merge overlap the other's tiles; otherwise eight waves, a strand each.
 // The same bits either way.  Bound by latency: of a work-group's 12 us at four tiles a strand its tiles take three; descriptor, partial
 // sums and merge the rest, and with the partial results of eight strands in LDS (135 KB) only one work-group fitted
-// a CU (both times: attn_two_per_cu).
+// a CU (both times: attn_two_per_cu).  The eight waves, which have the CU to themselves, put all strands' results there in one trip
+// (pairs first, in a trip of their own / this, us: 32 rows at prefix 384, 32 heads 10.8 / 10.5, two nodes 11.3 / 10.7, 193-row prompt of
+// 24 heads 9.7 / 9.2).
 template <int DH, bool FUSED, bool SUFFIX, bool SHARED>
 __global__ __launch_bounds__(SHARED ? 256 : 512, 2) void k_attn_mfma(const FwdHeader* __restrict__ fw,
                                                                const bf16_t* __restrict__ q,
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(SHARED ? 256 : 512, 2) void k_attn_mfma(const FwdHe
     constexpr int EPW = NE / WAVES;                                  // of which each wave merges EPW
     static_assert(EPW % 4 == 0, "the merge writes groups of four head channels");
     static_assert(!FUSED || DH == 128, "the fused rotary stage is laid out for head size 128");
-    __shared__ float mrg[4][NE + 2][64];                             // the pairs' partials (O^T, max, sum)
+    __shared__ float mrg[SHARED ? 4 : 8][NE + 2][64];                // the pairs' partials (O^T, max, sum); unless SHARED, the strands'
     __shared__ __attribute__((aligned(16))) bf16_t qs[32][DH + 8];   // the query tile, shared by the waves
     // FUSED: the node's own key and value tile, fragment order, at the front of the (not yet used) merge area
     bf16_t* ks_own = (bf16_t*)&mrg[0][0][0];
@@ -435,41 +437,29 @@ __global__ __launch_bounds__(SHARED ? 256 : 512, 2) void k_attn_mfma(const FwdHe
             oacc[e >> 4][e & 15] = merge2(first, ca, oacc[e >> 4][e & 15], cb);
         }
         __syncthreads();                                            // nobody needs the own tile or a waiting strand any more
-    } else {
-        if constexpr (FUSED) __syncthreads();                       // the own tile shared the merge area
-        if (wave >= 4) {
+    } else if constexpr (FUSED) __syncthreads();                    // the own tile shared the merge area
 #pragma unroll
-            for (int e = 0; e < NE; ++e) mrg[wave - 4][e][lane] = oacc[e >> 4][e & 15];
-            mrg[wave - 4][NE][lane] = m_run;
-            mrg[wave - 4][NE + 1][lane] = l_part;
-        }
-        __syncthreads();
-        if (wave < 4) {
-            float ca, cb, m;
-            merge_factors(m_run, mrg[wave][NE][lane], m, ca, cb);
-            m_run = m;
-            l_part = merge2(l_part, ca, mrg[wave][NE + 1][lane], cb);
-#pragma unroll
-            for (int e = 0; e < NE; ++e) oacc[e >> 4][e & 15] = merge2(oacc[e >> 4][e & 15], ca, mrg[wave][e][lane], cb);
-        }
-    }
-    if (wave < 4) {
-#pragma unroll
-        for (int e = 0; e < NE; ++e) mrg[wave][e][lane] = oacc[e >> 4][e & 15];
-        mrg[wave][NE][lane] = m_run;
-        mrg[wave][NE + 1][lane] = l_part;
-    }
+    for (int e = 0; e < NE; ++e) mrg[wave][e][lane] = oacc[e >> 4][e & 15];
+    mrg[wave][NE][lane] = m_run;
+    mrg[wave][NE + 1][lane] = l_part;
     __syncthreads();
     // wave w folds values [w*EPW, (w+1)*EPW) of all pairs in order
-    float m_all = -INFINITY;
+    float mw[4], ca[4], cb[4], m_all = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, mrg[w][NE][lane]);
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (SHARED) mw[w] = mrg[w][NE][lane];
+        else merge_factors(mrg[w][NE][lane], mrg[w + 4][NE][lane], mw[w], ca[w], cb[w]);
+        m_all = fmaxf(m_all, mw[w]);
+    }
+    auto pair = [&](int w, int e) SSD_INLINE {
+        if constexpr (SHARED) return mrg[w][e][lane];
+        else return merge2(mrg[w][e][lane], ca[w], mrg[w + 4][e][lane], cb[w]);
+    };
     float cw[4], l = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const float mw = mrg[w][NE][lane];
-        cw[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m_all);
-        l = __fmaf_rn(mrg[w][NE + 1][lane], cw[w], l);
+        cw[w] = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - m_all);
+        l = __fmaf_rn(pair(w, NE + 1), cw[w], l);
     }
     l += other_half(l, lh);
     const float inv = 1.0f / l;
@@ -478,7 +468,7 @@ __global__ __launch_bounds__(SHARED ? 256 : 512, 2) void k_attn_mfma(const FwdHe
     for (int e = 0; e < EPW; ++e) {
         float acc = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) acc = __fmaf_rn(mrg[w][wave * EPW + e][lane], cw[w], acc);
+        for (int w = 0; w < 4; ++w) acc = __fmaf_rn(pair(w, wave * EPW + e), cw[w], acc);
         o[e] = acc * inv;
     }
     if (qvalid) {
