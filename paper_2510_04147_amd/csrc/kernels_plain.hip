@@ -272,26 +272,36 @@ __global__ __launch_bounds__(256) void k_rope(const FwdHeader* __restrict__ fw, 
     const int nq = Hq * DH, nkv = Hkv * DH, nqkv = nq + 2 * nkv;
     const float* src = part + (size_t)row * nqkv;
     const size_t cbase = (((size_t)layer * max_seqs + nd.seq) * Hkv) * (size_t)seq_stride * DH;
-    // G groups of four values, group j from column col[j], partial sums added by halves; a split's groups are in flight together
+    // G groups of four values, group j from column col[j], partial sums added by halves; a split's groups are in flight together,
+    // and two or three splits where there are two or four
     auto load = [&](auto gc, const int* col, float* dst) {
         constexpr int G = decltype(gc)::value;
         float4 a[G], b[G], t[G];
-        auto add = [&](float4& x, const float4& y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
-        const int half = (n_part + 1) >> 1;
+        auto get = [&](float4(&v)[G], int sp) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < G; ++j) a[j] = *(const float4*)(src + col[j]);
-        for (int sp = 1; sp < n_part; ++sp) {
+            for (int j = 0; j < G; ++j) v[j] = *(const float4*)(src + sp * part_stride + col[j]);
+        };
+        auto add = [&](float4(&v)[G], const float4(&w)[G]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < G; ++j) b[j] = *(const float4*)(src + sp * part_stride + col[j]);
-#pragma unroll
-            for (int j = 0; j < G; ++j) {
-                if (sp == half) { t[j] = a[j]; a[j] = b[j]; }
-                else add(a[j], b[j]);
-            }
-        }
-        if (n_part > 1) {
-#pragma unroll
-            for (int j = 0; j < G; ++j) { add(t[j], a[j]); a[j] = t[j]; }
+            for (int j = 0; j < G; ++j) { v[j].x += w[j].x; v[j].y += w[j].y; v[j].z += w[j].z; v[j].w += w[j].w; }
+        };
+        get(a, 0);
+        if (n_part == 2) {
+            get(b, 1);
+            add(a, b);
+        } else if (n_part == 4) {
+            get(b, 1);
+            get(t, 2);
+            add(a, b);
+            get(b, 3);
+            add(t, b);
+            add(a, t);
+        } else if (n_part > 1) {
+            const int half = (n_part + 1) >> 1;
+            for (int sp = 1; sp < half; ++sp) { get(b, sp); add(a, b); }
+            get(t, half);
+            for (int sp = half + 1; sp < n_part; ++sp) { get(b, sp); add(t, b); }
+            add(a, t);
         }
 #pragma unroll
         for (int j = 0; j < G; ++j) { dst[4 * j] = a[j].x; dst[4 * j + 1] = a[j].y; dst[4 * j + 2] = a[j].z; dst[4 * j + 3] = a[j].w; }
