@@ -41,6 +41,15 @@ enum GemmTile {
     GEMM_HALVES_192x128 = 2192128, GEMM_HALVES_256x128 = 2256128
 };
 
+// n-tiles of the few-row kernel's work-groups for gate/up: three where they divide the matrix (the 8B shape, 768 tiles: a work-group on
+// every CU), for one row tile, whose loads smaller blocks spread better over the CUs, and for rows of one pass where at least 160 blocks
+// remain.  Blocks of four / three, us: 1184 tiles, of which 40 CUs get two blocks of four, 8 rows 56.1 / 46.9, 32 rows 58.4 / 49.1, 192 rows
+// 90 / 83; 512 tiles 32 rows 25.3 / 21.9, 192 rows 40.2 / 37.9; 400 tiles 32 rows 15.6 / 14.0, 192 rows 21.3 / 22.9.
+inline int gemm_channels_block(int M, int N) {
+    const int tiles = N / 32;
+    return tiles % 3 == 0 || M <= 32 || (M <= 192 && tiles >= 480) ? 3 : 4;
+}
+
 // What a GEMM writes: split-K partial sums, activated channels, the LM head's partial results.
 enum GemmOut { GEMM_SUMS, GEMM_CHANNELS, GEMM_LM };
 

@@ -73,10 +73,9 @@ bool launch_gemm_mfma(const ssd_ctx* c, int epi, const void* X, const Wt& W, voi
     GemmArgs a{x, wp, out, M, N, K, 1, 0, -1, 0, {}, st};
     if (epi == EPI_SWIGLU) {
         // W = [2F, d] packed with gate and up rows interleaved per 16 channels: N/32 tiles of 16
-        // channels each, any number of them per work-group; 96-row n-blocks give the 8B shape
-        // (768 tiles) exactly one work-group per CU
+        // channels each, any number of them per work-group
         *n_split = 1;
-        const int wn = (N / 32) % 3 == 0 ? 3 : 4;
+        const int wn = gemm_channels_block(M, N);
         if (const int t = gemm_tile(M, N, K / KC, 1, wn, GEMM_CHANNELS)) return gemm_rows_swiglu(a, t);
         a.pass = gemm_few_row_pass(M, N, 1, wn);
         return wn == 3 ? gemm_swiglu_wn3(a) : gemm_swiglu_wn4(a);

@@ -71,6 +71,21 @@ def test_choices_that_measure_at_least_5_percent_faster_than_another_kind(rules)
         assert ask(shape, (193, 224, 256, 288), CHANNELS) == [FEW] * 4
 
 
+def test_gate_up_blocks(tmp_path):
+    """Blocks of three tiles where they divide the matrix, for one row tile, and up to 192 rows with at least 160 of them; the row
+    counts and shapes of test_gpu_few_row_passes.py meet blocks of three that do not divide the matrix, and of four."""
+    (tmp_path / "p.cpp").write_text('#include <cstdio>\n#include "gemm_rules.h"\nint main() { int M, N; while (std::scanf("%d %d", &M, &N) == 2) '
+                                    'std::printf("%d\\n", gemm_channels_block(M, N)); }')
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "p.cpp"), "-o", str(tmp_path / "p")], check=True)
+    ask = lambda calls: [int(v) for v in subprocess.run([str(tmp_path / "p")], input="".join("%d %d\n" % c for c in calls), capture_output=True,
+                                                        text=True, check=True).stdout.split()]
+    assert ask([(M, 24576) for M in (1, 32, 33, 192, 193, 2304)]) == [3] * 6
+    assert ask([(M, 37888) for M in (1, 32, 33, 192, 193)]) == [3, 3, 3, 3, 4]
+    assert ask([(M, 400 * 32) for M in (1, 32, 33, 192, 193)]) == [3, 3, 4, 4, 4]
+    from test_gpu_few_row_passes import SHAPES as MODELS
+    assert any(2 * m["d_ffn"] // 32 % 3 for m in MODELS)
+
+
 def test_gpu_test_reaches_every_tile(rules):
     """Row counts and shapes of test_gpu_many_rows.py, through the whole rule: every height of the 256-row blocks with every epilogue,
     the fp32 one with K whole and in 2, 4 and 8 slices, and every height among the row counts compared with fp64."""
