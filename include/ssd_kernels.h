@@ -22,7 +22,9 @@ extern "C" {
 
 /* One linear step of layer `layer` (ignored for SSD_LIN_LM) with the kernel path the context
  * currently selects: x and out are device pointers, x in cfg.dtype, row-major, M <= max_rows.
- * x may start anywhere that suits its type; from a 16-byte boundary it takes the fastest kernels, with the same results.
+ * x may start anywhere that suits its type; from a 16-byte boundary it takes the fastest kernels, with the same results.  (The
+ * matrix-core kernels read 16 bytes at a time: rows that start elsewhere are copied into the context's workspace first, to an
+ * activation buffer that every forward writes anew.)
  * Split-K partial sums are added as the forward's consumers do: the first half of them in split order, the second half, then both.
  * Asynchronous on the context's stream.  Errors: SSD_EINVAL, SSD_ERANGE. */
 int ssd_k_linear(ssd_ctx* ctx, int which, int layer, const void* x, int M, void* out);

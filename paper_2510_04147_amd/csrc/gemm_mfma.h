@@ -381,7 +381,7 @@ static bool launch_one(const GemmArgs& a) {
 }
 
 // Row tiles of 32 rows per pass: 1 (a stepwise forward of one block) to 6; other row counts round up
-// (padding rows are zero and never stored).  The rows of a pass share nothing but the weight fragments,
+// (rows past the end repeat the last one and are never stored).  The rows of a pass share nothing but the weight fragments,
 // so a row's sums do not depend on the tile it is computed in.
 template <int WN, int EPI, bool CACHED>
 static bool launch_mt(const GemmArgs& a) {

@@ -39,7 +39,9 @@ static thread_local std::string g_create_err;
 // library runs on, held until the process ends.  `scratch` is a host-side stand-in for the symbol;
 // the device address comes from hipGetSymbolAddress, once per device, and only that pointer is
 // ever handed to kernels or copies.
-static __device__ __align__(256) unsigned char scratch[SSD_STATIC_SCRATCH_BYTES];
+// Behind the documented bytes lies room for rows that start off a 16-byte boundary, which the matrix-core kernels do not read.
+#define SSD_STATIC_ROW_BYTES (4u << 20)
+static __device__ __align__(256) unsigned char scratch[SSD_STATIC_SCRATCH_BYTES + SSD_STATIC_ROW_BYTES];
 #define SSD_MAX_DEVICES 64
 static void* g_scratch_ptr[SSD_MAX_DEVICES];          // per device, nullptr until resolved
 
@@ -537,7 +539,9 @@ static int run_forward(ssd_ctx* c, const FwdHeader& hd, const int32_t* raw, int 
         if (uniform) nodes_per_seq = first_run;
     }
 
-    // ---- the kernel sequence: a function of (M, ML, n_nodes, n_groups, max_blen, head_nodes, head_blen, kernel path) only
+    // ---- the kernel sequence: a function of (M, ML, n_nodes, n_groups, max_blen, head_nodes, head_blen, kernel path), of whether a
+    // node appends KV or reads a cached suffix and of where the results go: what a graph is found by (FwdGraph, its flags included).
+    // nodes_per_seq only places work-groups: whatever value was captured, the sums are the same
     auto launch_all = [&]() {
         {
             ProfScope ps(c, KC_ROWS);
@@ -828,7 +832,8 @@ static int finish_forward(ssd_ctx* c, const EventPair& ev, double* ms) {
 }
 
 // While one lives the acceptance kernel writes its results straight into the pinned memory the decoding loop reads after the
-// round's event, where a copy behind the kernel would go through the copy engine (64 tokens of the fp32 parity model: 4 % less time).
+// round's event, where a copy behind the kernel would go through the copy engine (64 tokens of the fp32 parity model 2.79 ms with the copy, 2.74 without;
+// 32 tokens of the 8B shape the same).
 struct ResultsToHost {
     ssd_ctx* c;
     explicit ResultsToHost(ssd_ctx* c_) : c(c_) { c->results_to_host = true; }
@@ -1355,8 +1360,25 @@ extern "C" __attribute__((visibility("default"))) int ssd_k_lm_head_static(ssd_c
     int* row_arg = (int*)((char*)sp + part_bytes);
     float* o = (float*)out;
     int tiles = 1;
-    if (!(c->kernel_path >= 1 && d.dtype == SSD_BF16 &&
-          launch_gemm_mfma(c, EPI_LMHEAD, x, c->lm_head, part, M, &tiles, c->stream))) {
+    bool done = c->kernel_path >= 1 && d.dtype == SSD_BF16;
+    if (done) {
+        // rows off a 16-byte boundary go through the array, as many at a time as it holds (launch_gemm_mfma would copy them
+        // to the workspace, which this call leaves alone); a row's result does not depend on the others
+        const bool copy = ((uintptr_t)x & 15) != 0;
+        const size_t row = (size_t)d.d * 2;
+        const int step = copy ? (int)std::min((size_t)M, SSD_STATIC_ROW_BYTES / row) : M;
+        for (int m0 = 0; m0 < M && done; m0 += step) {
+            const int m = std::min(step, M - m0);
+            const void* rows = (const char*)x + m0 * row;
+            if (copy) {
+                void* to = (char*)sp + SSD_STATIC_SCRATCH_BYTES;
+                HIPCHK(c, hipMemcpyAsync(to, rows, m * row, hipMemcpyDeviceToDevice, c->stream));
+                rows = to;
+            }
+            done = launch_gemm_mfma(c, EPI_LMHEAD, rows, c->lm_head, part + (size_t)m0 * tiles * 3, m, &tiles, c->stream);
+        }
+    }
+    if (!done) {
         tiles = lm_tiles_plain(d.V);
         launch_gemm_plain(c, EPI_LMHEAD, x, c->lm_head.raw, part, M, d.V, d.d, c->stream);
     }

@@ -1,10 +1,10 @@
 """The small-tile plain GEMM (k_gemm_plain_small) at the edges of its tiles, alone through ssd_k_linear: row counts around
-multiples of its 8 rows and on both sides of the switch to the 64x64 tiles (tests/test_gemm_rules.py checks on the CPU that
-every epilogue meets both), output widths that fill no tile, and K that is no multiple of its 64-wide chunks or shorter
+multiples of 8 and 16 and on both sides of the limit of 256 tiles of 64x64 (tests/test_gemm_rules.py checks on the CPU that
+every epilogue meets both), output widths that fill no tile, and K that is no multiple of a step of 16 columns or shorter
 than one.
 
-Both kernels add every output in ascending k, so a call must equal the same rows sent in other calls bit for bit, whichever
-kernel they take, aligned operands or not.  Against fp64 on the identical operands the sums differ by fp32 rounding
+Both kernels add every output in the same eight chains, so a call must equal the same rows sent in other calls bit for bit,
+whichever kernel they take, aligned operands or not.  Against fp64 on the identical operands the sums differ by fp32 rounding
 only (K <= 1032 products of operands of order 0.5 * 0.02: K * 2^-24 * 0.04 < 3e-6, and up to 1e-5 through SwiGLU)."""
 import pytest
 import torch
